@@ -108,7 +108,7 @@ int sht_adjoint(crs_grid g, int lmax, int nmaps, const double* map, int64_t map_
 
 /* crs_sht_reserve: setup for the transforms of Sect. 2.1 on (g, lmax) with
  * up to nmaps maps: builds the (grid, lmax) Legendre tables and grows the
- * grid's transform workspace (hat vectors, phase array, per-tile partial sums
+ * grid's transform workspace (phase array, per-tile partial sums
  * sized for any kernel variant), so that later sht_synth / sht_adjoint calls
  * on this grid with lmax and at most nmaps maps allocate nothing.
  * Synchronises the stream.  Errors: CRS_EINVAL (NULL grid, lmax < 0,
@@ -135,19 +135,19 @@ int sht_adjoint_noalloc(crs_grid g, int lmax, int nmaps, const double* map, int6
 
 /*
  * Legendre kernel autotuning (the recurrence and contraction of Sect. 2.1,
- * the bulk of every transform).  Both transforms have several kernel
- * variants per shape: the matrix-core contraction (from a few maps on) or
- * vector FP64 code, and the number of ring pairs per lane / 64-pair tiles
- * per wave.  crs_autotune_legendre times every variant for (grid, lmax,
- * nmaps) on the given stream (setup: allocates scratch, synchronises) and
- * records the fastest synthesis and adjoint for that shape; every later
- * transform of that shape in the process (sht_synth, sht_adjoint, and the
- * operators of models and batches created afterwards) uses it.  Batches
- * (crs_batch_create) tune each of their groups themselves.  Without tuning
- * the library uses fixed rules measured on MI355X.
+ * the bulk of every transform).  Both transforms run on the matrix cores for
+ * any map count; what is chosen per shape is the number of 64-pair tiles per
+ * wave.  crs_autotune_legendre times every variant for (grid, lmax, nmaps) on
+ * the given stream (setup: allocates scratch, synchronises) and records the
+ * fastest synthesis and adjoint for that shape; every later transform of that
+ * shape in the process (sht_synth, sht_adjoint, and the operators of models
+ * and batches created afterwards) uses it.  Batches (crs_batch_create) tune
+ * each of their groups themselves.  Without tuning the library uses fixed
+ * rules measured on MI355X.
  * crs_legendre_choice writes the variant in use for a shape to out[5]:
- * synthesis on matrix cores (0/1), synthesis ring pairs per lane, adjoint on
- * matrix cores (0/1), adjoint ring pairs per lane, adjoint tiles per wave.
+ * synthesis on matrix cores (1), synthesis tiles per wave (ring pairs per
+ * lane), adjoint on matrix cores (1), adjoint ring pairs per lane and tile (1),
+ * adjoint tiles per wave.
  * Errors: CRS_EINVAL for a NULL grid / out, lmax < 0 or nmaps < 1.
  */
 int crs_autotune_legendre(crs_grid g, int lmax, int nmaps, crs_stream s);

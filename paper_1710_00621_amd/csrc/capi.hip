@@ -154,13 +154,20 @@ static void check_maps(int lmax, int nmaps, int64_t as, int64_t ms_, int64_t npi
 
 LegArgs leg_args(crs_grid g, ShtPlan& p) {
   LegArgs a;
-  a.g = p.g.p;
-  a.ls = p.ls.p;
-  a.ms = p.ms.p;
-  a.zpair = g->d_zpair.p;
+  a.bp = p.bp.p;
+  a.be = p.be.p;
+  a.gi = p.gi.p;
+  a.ep = p.ep.p;
+  a.ks = p.ks.p;
+  a.st = p.st.p;
+  a.zs = g->d_zs.p;
+  a.ys = g->d_ys.p;
   a.lmax = p.lmax;
   a.npairs = p.npairs;
   a.nring = g->nring;
+  a.nslots = g->nslots;
+  a.pol_tiles = g->pol_tiles;
+  a.pol_pairs = g->pol_pairs;
   a.skip = MapSkip{};
   return a;
 }
@@ -304,10 +311,9 @@ int crs_sht_reserve(crs_grid g, int lmax, int nmaps, crs_stream st) {
     GridWork& w = *g->work;
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 1);
     const int64_t pst = (int64_t)g->nring * (lmax + 1);
-    w.uhat.alloc((size_t)nmaps * nalm);
     w.phase.alloc((size_t)nmaps * pst);
     // the largest tile count of any adjoint variant (one 64-pair tile per wave)
-    w.vpart.alloc((size_t)((p.npairs + 63) / 64) * nmaps * nalm);
+    w.vpart.alloc((size_t)(p.nslots / 64) * nmaps * nalm);
     CRS_HIP(hipStreamSynchronize(s));
     return CRS_OK;
   });
@@ -323,14 +329,11 @@ int sht_synth(crs_grid g, int lmax, int nmaps, const double* alm, int64_t alm_st
     ShtPlan& p = get_plan(g, lmax, s);
     if (!g->work) g->work = std::make_unique<GridWork>();
     GridWork& w = *g->work;
-    const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 1);
     const int64_t pst = (int64_t)g->nring * (lmax + 1);
-    w.uhat.alloc((size_t)nmaps * nalm);
     w.phase.alloc((size_t)nmaps * pst);
-    launch_tile_sum(p.hs.p, nalm, nmaps, alm, alm_stride, 1, 0, w.uhat.p, nalm, s);
     {
       ProfScope ps(FAM_LEG_SYNTH, leg_work(p, nmaps), s);
-      launch_leg_synth(leg_choice(p.npairs, lmax, nmaps), leg_args(g, p), nmaps, w.uhat.p, nalm, w.phase.p, pst, s);
+      launch_leg_synth(leg_choice(p.npairs, lmax, nmaps), leg_args(g, p), nmaps, alm, alm_stride, w.phase.p, pst, s);
     }
     {
       ProfScope ps(FAM_RING, bytes_work(ring_bytes(g, lmax, nmaps, RING_SYNTH)), s);
@@ -354,9 +357,11 @@ int sht_adjoint(crs_grid g, int lmax, int nmaps, const double* map, int64_t map_
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 1);
     const int64_t pst = (int64_t)g->nring * (lmax + 1);
     const LegChoice lc = leg_choice(p.npairs, lmax, nmaps);
-    const int ntiles = leg_adjoint_tiles(lc, p.npairs, false);
+    const int ntiles = leg_adjoint_tiles(lc, g, false);
     w.phase.alloc((size_t)nmaps * pst);
-    w.vpart.alloc((size_t)ntiles * nmaps * nalm);
+    // one tile: the Legendre kernel's partial is the result
+    const bool direct = ntiles == 1;
+    if (!direct) w.vpart.alloc((size_t)ntiles * nmaps * nalm);
     {
       ProfScope ps(FAM_RING, bytes_work(ring_bytes(g, lmax, nmaps, RING_ADJOINT)), s);
       launch_ring(g, lmax, RING_ADJOINT, nmaps, w.phase.p, pst, map, nullptr, map_stride,
@@ -364,10 +369,11 @@ int sht_adjoint(crs_grid g, int lmax, int nmaps, const double* map, int64_t map_
     }
     {
       ProfScope ps(FAM_LEG_ADJ, leg_work(p, nmaps), s);
-      launch_leg_adjoint(lc, leg_args(g, p), nmaps, w.phase.p, pst, w.vpart.p, nalm,
-                         (int64_t)nmaps * nalm, false, s);
+      launch_leg_adjoint(lc, leg_args(g, p), nmaps, w.phase.p, pst, direct ? alm : w.vpart.p,
+                         direct ? alm_stride : nalm, (int64_t)nmaps * nalm, false, s);
     }
-    launch_tile_sum(p.hs.p, nalm, nmaps, w.vpart.p, nalm, ntiles, (int64_t)nmaps * nalm, alm, alm_stride, s);
+    if (!direct)
+      launch_tile_sum(nalm, nmaps, w.vpart.p, nalm, ntiles, (int64_t)nmaps * nalm, alm, alm_stride, s);
     return CRS_OK;
   });
 }
@@ -422,7 +428,7 @@ int sht_adjoint_noalloc(crs_grid g, int lmax, int nmaps, const double* map, int6
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 1);
     const int64_t pst = (int64_t)g->nring * (lmax + 1);
     const LegChoice lc = leg_choice(p.npairs, lmax, nmaps);
-    const int ntiles = leg_adjoint_tiles(lc, p.npairs, false);
+    const int ntiles = leg_adjoint_tiles(lc, g, false);
     const size_t phase_bytes = align256((size_t)nmaps * pst * sizeof(double2));
     const size_t part_bytes = align256((size_t)ntiles * nmaps * nalm * sizeof(double));
     CRS_CHECK(phase_bytes + part_bytes <= kNoAllocScratchBytes, CRS_EINVAL,
@@ -443,7 +449,7 @@ int sht_adjoint_noalloc(crs_grid g, int lmax, int nmaps, const double* map, int6
       ProfScope ps(FAM_LEG_ADJ, leg_work(p, nmaps), s);
       launch_leg_adjoint(lc, leg_args(g, p), nmaps, phase, pst, vpart, nalm, (int64_t)nmaps * nalm, false, s);
     }
-    launch_tile_sum(p.hs.p, nalm, nmaps, vpart, nalm, ntiles, (int64_t)nmaps * nalm, alm, alm_stride, s);
+    launch_tile_sum(nalm, nmaps, vpart, nalm, ntiles, (int64_t)nmaps * nalm, alm, alm_stride, s);
     return CRS_OK;
   });
 }
@@ -470,10 +476,10 @@ int crs_legendre_choice(crs_grid g, int lmax, int nmaps, int* out) {
     CRS_CHECK(g != nullptr && out != nullptr, CRS_EINVAL, "grid or out is NULL");
     CRS_CHECK(lmax >= 0 && nmaps >= 1, CRS_EINVAL, "lmax < 0 or nmaps < 1");
     const LegChoice c = leg_choice((g->nring + 1) / 2, lmax, nmaps);
-    out[0] = c.syn_mfma;
-    out[1] = c.syn_r;
-    out[2] = c.adj_mfma;
-    out[3] = c.adj_r;
+    out[0] = 1;
+    out[1] = c.syn_t;
+    out[2] = 1;
+    out[3] = 1;
     out[4] = c.adj_t;
     return CRS_OK;
   });

@@ -43,7 +43,7 @@ __device__ __forceinline__ double block_sum256(double acc, double* red) {
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// uhat[map][i] = c_m f_lm sum_k coef[l][band][k] x[sys][coff_k + idx_k]
+// uhat[map][i] = sum_k coef[l][band][k] x[sys][coff_k + idx_k]
 // for the packed indices of block xb of map `map` (kWorkBlock indices)
 __device__ __forceinline__ void mix_fwd_block(const double* __restrict__ x, const SysDev* __restrict__ sys,
                                               const ProbDev* __restrict__ probs, const SlotDev* __restrict__ slots,
@@ -73,8 +73,7 @@ __device__ __forceinline__ void mix_fwd_block(const double* __restrict__ x, cons
                                : xs[P.coff[k] + loc];
       acc = fma(c, xv, acc);
     }
-    const double cm = (m == 0) ? 1.0 : 1.4142135623730951;
-    uhat[(int64_t)map * nalm + i] = cm * P.ftab[tri_h(P.Lf, m) + ll] * acc;
+    uhat[(int64_t)map * nalm + i] = acc;
   }
 }
 
@@ -111,7 +110,7 @@ __global__ void k_mix_fwd_all(const double* __restrict__ x, const SysDev* __rest
                 loc - map * a.g[t].nbx);
 }
 
-// y[sys][coff_k + idx] = diag term + sum_nu coef[l][nu][k] c_m f_lm sum_t vpart_nu[t][map][idx_nu]
+// y[sys][coff_k + idx] = diag term + sum_nu coef[l][nu][k] sum_t vpart_nu[t][map][idx_nu]
 // dmode 0: no diag term; 1: (dsqrt ? C^-1/2 : C^-1) din; 2: Pi_l din.
 // (grid: one block per work-list entry over the systems, packed index u of
 // P.Lc; each thread forms all components of its (l, m), so the band partials
@@ -165,8 +164,6 @@ __global__ __launch_bounds__(256) void k_mix_back(double* __restrict__ y, const 
         acc[k] = a;
       }
     }
-    const double cm = (m == 0) ? 1.0 : 1.4142135623730951;
-    const double fs = cm * P.ftab[tri_h(P.Lf, m) + ll];
     for (int nu = 0; nu < P.nb; ++nu) {
       const int* bi = P.binfo + kBinfo * nu;
       const int L = bi[0];
@@ -191,7 +188,7 @@ __global__ __launch_bounds__(256) void k_mix_back(double* __restrict__ y, const 
       const int* vb = (!usep && P.vidx) ? P.vidx + nu * nc : nullptr;  // varying pairs: added afterwards
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        if (k < nc && ix[k] >= 0 && !(vb && vb[k] >= 0)) acc[k] = fma(cn[k] * fs, sv, acc[k]);
+        if (k < nc && ix[k] >= 0 && !(vb && vb[k] >= 0)) acc[k] = fma(cn[k], sv, acc[k]);
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -328,12 +325,11 @@ __global__ __launch_bounds__(256) void k_dq(const double* __restrict__ va, int s
   for (int m = 0; m <= Lm; ++m) {
     const int np = (m == 0) ? 1 : 2;
     const int ns = Lm - m + 1;
-    const double cm = (m == 0) ? 1.0 : 1.4142135623730951;
     for (int i = threadIdx.x; i < np * ns; i += 256) {
       const int part = i / ns, ll = i % ns, l = m + ll;
       const int64_t ik = P.coff[k] + moff_h(Lk, m) + (int64_t)part * (Lk - m + 1) + ll;
       const int64_t ib = moff_h(Lb, m) + (int64_t)part * (Lb - m + 1) + ll;
-      const double fs = beamtab[(int64_t)l * nb + nu] * cm * P.ftab[tri_h(P.Lf, m) + ll];
+      const double fs = beamtab[(int64_t)l * nb + nu];
       double sa = 0.0, sb = 0.0;
       for (int t = 0; t < bi[3]; ++t) {
         sa += VA[t * tstride + ib];
@@ -657,7 +653,7 @@ int64_t exec_plan_bytes(const std::vector<crs_model>& models, int nrhs) {
     const LegChoice c = leg_choice(npairs, L, nm);
     bytes += (int64_t)nm * nalm * 8;                          // uhat
     bytes += (int64_t)nm * g->nring * (L + 1) * 16;           // phase
-    bytes += (int64_t)leg_adjoint_tiles(c, npairs, false) * nm * nalm * 8;  // adjoint partial sums
+    bytes += (int64_t)leg_adjoint_tiles(c, g, false) * nm * nalm * 8;  // adjoint partial sums
     bytes += (int64_t)nm * g->npix * 8;                       // pixel maps (right-hand side)
   }
   bytes += 7 * ntot * 8;                                      // r, z, p, q, t, x and the caller's b
@@ -735,7 +731,7 @@ std::unique_ptr<Exec> make_exec(const std::vector<crs_model>& models, int nrhs, 
     g.phase.alloc((size_t)g.nmaps * g.pst);
     g.leg = autotune ? leg_autotune(leg_args(g.grid, *g.plan), g.nmaps, g.uhat.p, g.phase.p, s)
                      : leg_choice(g.plan->npairs, g.lmax, g.nmaps);
-    g.ntiles = leg_adjoint_tiles(g.leg, g.plan->npairs, false);
+    g.ntiles = leg_adjoint_tiles(g.leg, g.grid, false);
     std::vector<const double*> wa, wp, ta;
     for (const SlotDev& sl : g.hslots) {
       const Band& b = models[e->hsys[sl.sys].prob]->bands[sl.band];
@@ -796,7 +792,6 @@ std::unique_ptr<Exec> make_exec(const std::vector<crs_model>& models, int nrhs, 
     d.dInv = m->dInv.p;
     d.dSqrt = m->dSqrt.p;
     d.dPi = m->dPi.p;
-    d.ftab = m->ftab.p;
     d.Dinv = m->has_diag ? m->Dinv.p : nullptr;
     d.vptr = e->vptr[p].p;
     d.binfo = e->binfo[p].p;
@@ -1117,7 +1112,7 @@ void exec_prior_inv(Exec& e, const double* x, double* y, hipStream_t s) {
 }
 
 // dq[r][nu][k] = sign sum_lm ( va_r,k(lm) V(sa0 + r, nu)(lm) + vb_r,k(lm) V(sb0 + r, nu)(lm) ),
-// V(s, nu) = b_{nu,l} c_m f_lm sum_t vpart_nu[t][map(s, nu)]: the band-nu adjoint of system s.
+// V(s, nu) = b_{nu,l} sum_t vpart_nu[t][map(s, nu)]: the band-nu adjoint of system s.
 void exec_mix_grad(Exec& e, const double* va, int sa0, const double* vb, int sb0, int nrhs, double sign,
                    const double* beamtab, double* dq, hipStream_t s) {
   const crs_model m = e.probs[0];

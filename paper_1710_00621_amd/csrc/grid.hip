@@ -5,6 +5,7 @@
 // sky maps and recommends Gauss-Legendre grids where exact quadrature is
 // wanted (Sect. 2.1, Sect. 2.2 below eq:Q).
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstring>
 
@@ -156,6 +157,25 @@ void gl_nodes(int n, std::vector<double>& z, std::vector<double>& st, std::vecto
 }
 
 }  // namespace
+
+// Ring pairs in slots, tiles of 64, for the Legendre kernels: every tile runs
+// one form of the recurrence (legendre.hip), whose errors grow as 1 / sin(2
+// theta) away from its own end.  The forms meet at 45 degrees; the boundary
+// moves to the nearest whole tile if that stays within 35 and 55 degrees (no
+// padding: every HEALPix grid from Nside 64 on), else it stays at 45 degrees
+// and the polar slots are padded.
+static void slot_layout(crs_grid g) {
+  const int np = (g->nring + 1) / 2;
+  int p45 = 0;
+  while (p45 < np && g->z[p45] * g->z[p45] >= 0.5) ++p45;
+  const int c = (p45 + 32) / 64 * 64;
+  const double lo = 0.329, hi = 0.671;  // cos^2 of 55 and 35 degrees
+  const bool whole = c <= np && (c == 0 || g->z[c - 1] * g->z[c - 1] >= lo) &&
+                     (c == np || g->z[c] * g->z[c] <= hi);
+  g->pol_pairs = whole ? c : p45;
+  g->pol_tiles = (g->pol_pairs + 63) / 64;
+  g->nslots = 64 * (g->pol_tiles + (np - g->pol_pairs + 63) / 64);
+}
 
 // Uploads per-ring tables (lengths, offsets, phi0, FFT factors, twiddles).
 void grid_finalize(crs_grid g, hipStream_t s) {
@@ -316,11 +336,16 @@ void grid_finalize(crs_grid g, hipStream_t s) {
   }
   g->d_fftn.upload(fftn, s);
   g->d_bfoff.upload(bfoff, s);
-  int np = (nr + 1) / 2;
-  std::vector<double> zp(np), sp(np);
-  for (int p = 0; p < np; ++p) {
-    zp[p] = g->z[p];
-    sp[p] = g->sint[p];
+  slot_layout(g);
+  std::vector<double> zs(g->nslots, 0.0), ss(g->nslots, 1.0), ys(g->nslots, 0.0);
+  for (int p = 0; p < (nr + 1) / 2; ++p) {
+    const bool polar = p < g->pol_pairs;
+    const int i = polar ? p : p - g->pol_pairs + 64 * g->pol_tiles;
+    zs[i] = g->z[p];
+    ss[i] = g->sint[p];
+    // sin^2 theta of the ring's z as stored (1 - z is exact for z >= 1/2): the
+    // functions are those at the pixel centres the grid reports
+    ys[i] = polar ? -(1.0 - g->z[p]) * (1.0 + g->z[p]) : -g->z[p] * g->z[p];
   }
   g->d_nphi.upload(g->nphi, s);
   g->d_offset.upload(g->offset, s);
@@ -331,8 +356,9 @@ void grid_finalize(crs_grid g, hipStream_t s) {
   g->d_facm.upload(facm, s);
   g->d_twoff.upload(twoff, s);
   g->d_tw.upload(tw, s);
-  g->d_zpair.upload(zp, s);
-  g->d_spair.upload(sp, s);
+  g->d_zs.upload(zs, s);
+  g->d_ss.upload(ss, s);
+  g->d_ys.upload(ys, s);
   CRS_HIP(hipStreamSynchronize(s));
 }
 
@@ -385,116 +411,153 @@ void build_gl(crs_grid g, int nrings, int nphi) {
 }
 
 // ----------------------------------------------------------- Legendre plan
-// mu-recurrence tables.  With a_lm = sqrt((4l^2-1)/(l^2-m^2)),
-// b_lm = sqrt(((l-1)^2-m^2)/(4(l-1)^2-1)) and c_lm = a_lm b_lm the normalised
-// associated Legendre functions obey lambda_l = a_l z lambda_{l-1} - c_l lambda_{l-2}.
-// Writing lambda_l = f_l mu_l with f_m = f_{m+1} = 1, f_l = c_l f_{l-2} turns
-// this into mu_l = g_l z mu_{l-1} - mu_{l-2}, g_l = a_l f_{l-1} / f_l: one
-// multiply and one FMA per step.  Triangle layout: entry (l, m) at
-// tri(m) + l - m, tri(m) = m (L+1) - m (m-1) / 2.
-__host__ __device__ static inline int64_t tri_off(int L, int m) { return (int64_t)m * (L + 1) - (int64_t)m * (m - 1) / 2; }
+// Coefficients of the recurrence in legendre.hip.  With eta_l = (4 m^2 - 1) /
+// (4 (4 l^2 - 1)), eps_l^2 = 1/4 - eta_l; g = eps_l eps_{l-1} = 1/4 - delta with
+// delta = (eta_l / 4 + eta_{l-1} eps_l^2) / (1/4 + g).  At l = m + 2k + 1 the sums
+//     1 - eps_{l+1}^2 - eps_l^2 - g_k - g_{k+1} = (eta_l + eta_{l+1}) + (delta_k + delta_{k+1})
+//     eps_{l+1}^2 + eps_l^2 - g_k - g_{k+1} = (delta_k + delta_{k+1}) - (eta_l + eta_{l+1})
+// come out of small terms instead of cancelling to them.
+__global__ void k_rec_tables(int L, double* __restrict__ bp, double* __restrict__ be, double* __restrict__ gi,
+                             double* __restrict__ ep) {
+  const int m = blockIdx.y;
+  const int K = (L - m) / 2 + 1;
+  const double m2 = 4.0 * (double)m * m - 1.0;
+  auto eta = [&](double l) { return m2 / (4.0 * (4.0 * l * l - 1.0)); };
+  auto eps2 = [&](double l) { return (l - m) * (l + m) / (4.0 * l * l - 1.0); };
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < K; k += gridDim.x * blockDim.x) {
+    const double l = m + 2.0 * k + 1.0;
+    const double e0 = eps2(l - 1.0), e1 = eps2(l), e2 = eps2(l + 1.0), e3 = eps2(l + 2.0);
+    const double g0 = sqrt(e0 * e1), g1 = sqrt(e2 * e3);
+    const double d0 = (eta(l) * 0.25 + eta(l - 1.0) * e1) / (0.25 + g0);
+    const double d1 = (eta(l + 2.0) * 0.25 + eta(l + 1.0) * e3) / (0.25 + g1);
+    const double se = eta(l) + eta(l + 1.0);
+    const int64_t o = krow(L, m) + k;
+    bp[o] = se + (d0 + d1);
+    be[o] = (d0 + d1) - se;
+    gi[o] = 1.0 / g1;
+    // eps of l - 1 and l (row entries m + 2k, m + 2k + 1; the row ends at L + 1)
+    double* er = ep + 4 + erow(L, m);
+    er[2 * k] = sqrt(e0);
+    if (2 * k + 1 <= L + 1 - m) er[2 * k + 1] = sqrt(e1);
+    if (k == K - 1 && 2 * k + 2 <= L + 1 - m) er[2 * k + 2] = sqrt(e2);
+  }
+  if (m == 0 && blockIdx.x == 0 && threadIdx.x < 4) ep[threadIdx.x] = threadIdx.x & 1 ? 0.0 : 1.0;
+}
 
-__global__ void k_start_table(const double* __restrict__ gtab, const double* __restrict__ ftab,
-                              const double* __restrict__ zp, const double* __restrict__ sp,
-                              const double* __restrict__ pm_mant, const int* __restrict__ pm_exp,
-                              int L, int npairs, double thr, int* __restrict__ ls_out,
-                              double2* __restrict__ ms_out, double thr_lo, int* __restrict__ lu_out) {
-  int p = blockIdx.x * blockDim.x + threadIdx.x;
-  int m = blockIdx.y;
-  if (p >= npairs || m > L) return;
-  double z = zp[p], s = sp[p];
-  // lambda_mm = P_m sin^m(theta), carried as mantissa * 2^e
-  double mant = pm_mant[m];
-  long e = pm_exp[m];
-  if (m > 0) {
-    if (s == 0.0) {
-      mant = 0.0;
-    } else {
-      int se;
-      double sm = frexp(s, &se);
-      double r = 1.0;
-      long er = 0;
-      double base = sm;
-      long eb = se;
-      int k = m;
-      while (k) {
-        if (k & 1) {
+// Start of every (slot, m): the recurrence from lambda_mm with a power of two
+// carried beside it, up to the first l with |lambda_l| >= thr; (q, d) as they
+// were at the last multiple of 8 in k.  counts: triples from the first l with
+// |lambda| >= thr (0) and >= thr_lo (1) on.
+__global__ void k_start_table(const double* __restrict__ bp, const double* __restrict__ be,
+                              const double* __restrict__ gi, const double* __restrict__ ep,
+                              const double* __restrict__ zs, const double* __restrict__ ss,
+                              const double* __restrict__ ys, const double* __restrict__ pm_mant,
+                              const int* __restrict__ pm_exp, int L, int nslots, int pol_pairs, int pol_tiles,
+                              int npairs, double thr, double thr_lo, int* __restrict__ ks_out,
+                              double2* __restrict__ st_out, unsigned long long* __restrict__ counts) {
+  const int slot = blockIdx.x * blockDim.x + threadIdx.x;
+  const int m = blockIdx.y;
+  const bool polar = slot < 64 * pol_tiles;
+  const int p = polar ? (slot < pol_pairs ? slot : -1) : slot - 64 * pol_tiles + pol_pairs;
+  unsigned long long n0 = 0, n1 = 0;
+  if (slot < nslots) {
+    int ksv = INT_MAX;
+    double2 stv = make_double2(0.0, 0.0);
+    if (p >= 0 && p < npairs) {
+      const double z = zs[slot], s = ss[slot], y = ys[slot];
+      // lambda_mm = P_m sin^m(theta), carried as mantissa * 2^e
+      double mant = pm_mant[m];
+      long e = pm_exp[m];
+      if (m > 0) {
+        int se;
+        double base = frexp(s, &se), r = 1.0;
+        long er = 0, eb = se;
+        for (int j = m; j; j >>= 1) {
           int t;
-          r = frexp(r * base, &t);
-          er += eb + t;
-        }
-        k >>= 1;
-        if (k) {
-          int t;
+          if (j & 1) {
+            r = frexp(r * base, &t);
+            er += eb + t;
+          }
           base = frexp(base * base, &t);
           eb = 2 * eb + t;
         }
+        int t;
+        mant = frexp(mant * r, &t);
+        e += er + t;
       }
-      int t;
-      mant = frexp(mant * r, &t);
-      e += er + t;
+      const double* b = (polar ? bp : be) + krow(L, m);
+      const double* g = gi + krow(L, m);
+      const double* ee = ep + 4 + erow(L, m);
+      const int K = (L - m) / 2 + 1;
+      double q = mant / ee[1], d = 0.0, qm = 0.0;  // q_k, d_k and the signed q_{k-1}
+      double sq = 0.0, sd = 0.0;
+      long se = 0;
+      int lo_l = L + 1;
+      for (int k = 0; k < K; ++k) {
+        if ((k & 7) == 0) {
+          sq = q;
+          sd = d;
+          se = e;
+        }
+        const double sg = polar || !(k & 1) ? 1.0 : -1.0;  // the equator form carries (-1)^k q_k
+        const double le = fabs(ee[2 * k + 1] * (sg * q) + ee[2 * k] * qm), lo = fabs(z * q);
+        const int l = m + 2 * k;
+        if (lo_l > L && e > -2000) {
+          if (ldexp(le, (int)e) >= thr_lo) lo_l = l;
+          else if (l + 1 <= L && ldexp(lo, (int)e) >= thr_lo) lo_l = l + 1;
+        }
+        int hit = -1;
+        if (e > -2000) {
+          if (ldexp(le, (int)e) >= thr) hit = l;
+          else if (l + 1 <= L && ldexp(lo, (int)e) >= thr) hit = l + 1;
+        }
+        if (hit >= 0) {
+          ksv = k & ~7;
+          stv = make_double2(ldexp(sq, (int)se), ldexp(sd, (int)se));
+          n0 = (unsigned long long)(L - hit + 1);
+          break;
+        }
+        qm = sg * q;
+        d = fma(y + b[k], q, d);
+        q = fma(g[k], d, q);
+        if (fabs(q) > 0x1p600) {
+          q *= 0x1p-600;
+          qm *= 0x1p-600;
+          d *= 0x1p-600;
+          e += 600;
+        }
+      }
+      if (lo_l <= L) n1 = (unsigned long long)(L - lo_l + 1);
     }
+    ks_out[(size_t)m * nslots + slot] = ksv;
+    st_out[(size_t)m * nslots + slot] = stv;
   }
-  const double* g = gtab + tri_off(L, m) - m;
-  const double* f = ftab + tri_off(L, m) - m;
-  double mu_prev = 0.0, mu_cur = mant;
-  int l = m;
-  int lsv = L + 1, luv = L + 1;
-  double2 msv = make_double2(0.0, 0.0);
-  // threshold tests on |lambda_l| = f_l |mu_l| 2^e: the first l at or above
-  // thr_lo (counted, not used by the kernels) and at or above thr (start)
-  while (true) {
-    double v = fabs(f[l] * mu_cur);
-    if (luv > L && v != 0.0 && e > -2000 && ldexp(v, (int)e) >= thr_lo) luv = l;
-    if (v != 0.0 && e > -2000 && ldexp(v, (int)e) >= thr) {
-      lsv = l;
-      msv = make_double2(ldexp(mu_prev, (int)e), ldexp(mu_cur, (int)e));
-      break;
-    }
-    ++l;
-    if (l > L) break;
-    double nx = g[l] * z * mu_cur - mu_prev;
-    mu_prev = mu_cur;
-    mu_cur = nx;
-    if (fabs(mu_cur) > 0x1p600) {
-      mu_cur *= 0x1p-600;
-      mu_prev *= 0x1p-600;
-      e += 600;
-    }
+  for (int off = 32; off > 0; off >>= 1) {
+    n0 += __shfl_xor(n0, off, 64);
+    n1 += __shfl_xor(n1, off, 64);
   }
-  ls_out[(size_t)m * npairs + p] = lsv;
-  ms_out[(size_t)m * npairs + p] = msv;
-  lu_out[(size_t)m * npairs + p] = luv;
+  if ((threadIdx.x & 63) == 0 && (n0 | n1)) {
+    atomicAdd(counts, n0);
+    atomicAdd(counts + 1, n1);
+  }
 }
 
-constexpr double kSkipThreshold = 0x1p-100;  // |lambda| below this is not evaluated
+__global__ void k_fill(double* __restrict__ p, int64_t n, double v) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
+}
+
+constexpr double kSkipThreshold = 0x1p-100;  // a lane starts at most 15 l before |lambda| reaches this
 constexpr double kFp64Normal = 0x1p-1022;    // smallest normal float64
+constexpr int kTabPad = 64;                  // table words read past the last row (values unused)
 
 ShtPlan& get_plan(crs_grid g, int lmax, hipStream_t s) {
   auto it = g->plans.find(lmax);
   if (it != g->plans.end()) return *it->second;
   auto plan = std::make_unique<ShtPlan>();
-  int L = lmax;
+  const int L = lmax;
   plan->lmax = L;
   plan->npairs = (g->nring + 1) / 2;
-  int64_t ntri = (int64_t)(L + 1) * (L + 2) / 2;
-  // g carries 8 trailing zeros: the MFMA synthesis reads it in aligned groups of 8 past L
-  std::vector<double> gt(ntri + 8, 0.0), ft(ntri, 0.0);
-  for (int m = 0; m <= L; ++m) {
-    int64_t o = tri_off(L, m) - m;
-    ft[o + m] = 1.0;
-    if (m + 1 <= L) {
-      ft[o + m + 1] = 1.0;
-      gt[o + m + 1] = std::sqrt(2.0 * m + 3.0);
-    }
-    for (int l = m + 2; l <= L; ++l) {
-      double dl = l, dm = m;
-      double a = std::sqrt((4.0 * dl * dl - 1.0) / ((dl - dm) * (dl + dm)));
-      double b = std::sqrt(((dl - 1.0 - dm) * (dl - 1.0 + dm)) / (4.0 * (dl - 1.0) * (dl - 1.0) - 1.0));
-      ft[o + l] = a * b * ft[o + l - 2];
-      gt[o + l] = a * ft[o + l - 1] / ft[o + l];
-    }
-  }
+  plan->nslots = g->nslots;
   // P_m = lambda_00 prod_{k<=m} sqrt((2k+1)/(2k)) as mantissa/exponent
   std::vector<double> pmm(L + 1);
   std::vector<int> pme(L + 1);
@@ -513,45 +576,35 @@ ShtPlan& get_plan(crs_grid g, int lmax, hipStream_t s) {
       pme[m] = (int)ee;
     }
   }
-  // c_m f_lm in the packed alm layout ([m = 0: l], then per m >= 1 [cos: l][sin: l])
-  std::vector<double> hs((size_t)(L + 1) * (L + 1));
-  {
-    size_t o = 0;
-    for (int m = 0; m <= L; ++m) {
-      const double cm = m == 0 ? 1.0 : std::sqrt(2.0);
-      const int64_t t = tri_off(L, m) - m;
-      for (int part = 0; part < (m == 0 ? 1 : 2); ++part)
-        for (int l = m; l <= L; ++l) hs[o++] = cm * ft[t + l];
-    }
+  const int64_t nk = krow(L, L) + 1 + kTabPad, ne = 4 + erow(L, L) + 2 + kTabPad;
+  for (auto* t : {&plan->bp, &plan->be, &plan->gi}) {
+    t->alloc((size_t)nk);
+    hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, t->p + nk - kTabPad, (int64_t)kTabPad, 0.0);
   }
-  plan->g.upload(gt, s);
-  plan->f.upload(ft, s);
-  plan->hs.upload(hs, s);
+  plan->ep.alloc((size_t)ne);
+  hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, plan->ep.p + ne - kTabPad, (int64_t)kTabPad, 0.0);
+  hipLaunchKernelGGL(k_rec_tables, dim3((L / 2 + 256) / 256, L + 1), dim3(256), 0, s, L, plan->bp.p, plan->be.p,
+                     plan->gi.p, plan->ep.p);
+  CRS_HIP(hipGetLastError());
   DevBuf<double> dpm;
   DevBuf<int> dpe;
+  DevBuf<unsigned long long> dcnt;
+  unsigned long long cnt[2] = {0, 0};
   dpm.upload(pmm, s);
   dpe.upload(pme, s);
-  plan->ls.alloc((size_t)(L + 1) * plan->npairs);
-  plan->ms.alloc((size_t)(L + 1) * plan->npairs);
-  DevBuf<int> dlu;
-  dlu.alloc((size_t)(L + 1) * plan->npairs);
-  dim3 grid((plan->npairs + 127) / 128, L + 1);
-  hipLaunchKernelGGL(k_start_table, grid, dim3(128), 0, s, plan->g.p, plan->f.p, g->d_zpair.p,
-                     g->d_spair.p, dpm.p, dpe.p, L, plan->npairs, kSkipThreshold, plan->ls.p,
-                     plan->ms.p, kFp64Normal, dlu.p);
+  dcnt.upload(cnt, 2, s);
+  plan->ks.alloc((size_t)(L + 1) * plan->nslots);
+  plan->st.alloc((size_t)(L + 1) * plan->nslots);
+  hipLaunchKernelGGL(k_start_table, dim3((plan->nslots + 127) / 128, L + 1), dim3(128), 0, s, plan->bp.p, plan->be.p,
+                     plan->gi.p, plan->ep.p, g->d_zs.p, g->d_ss.p, g->d_ys.p, dpm.p, dpe.p, L, plan->nslots,
+                     g->pol_pairs, g->pol_tiles, plan->npairs, kSkipThreshold, kFp64Normal, plan->ks.p, plan->st.p,
+                     dcnt.p);
   CRS_HIP(hipGetLastError());
-  std::vector<int> lsh((size_t)(L + 1) * plan->npairs), luh(lsh.size());
-  CRS_HIP(hipMemcpyAsync(lsh.data(), plan->ls.p, lsh.size() * sizeof(int), hipMemcpyDeviceToHost, s));
-  CRS_HIP(hipMemcpyAsync(luh.data(), dlu.p, luh.size() * sizeof(int), hipMemcpyDeviceToHost, s));
+  CRS_HIP(hipMemcpyAsync(cnt, dcnt.p, sizeof(cnt), hipMemcpyDeviceToHost, s));
   CRS_HIP(hipStreamSynchronize(s));
-  int64_t eff = 0, eff64 = 0;
-  for (size_t i = 0; i < lsh.size(); ++i) {
-    if (lsh[i] <= L) eff += L - lsh[i] + 1;
-    if (luh[i] <= L) eff64 += L - luh[i] + 1;
-  }
-  plan->eff_triples = eff;
-  plan->fp64_triples = eff64;
-  plan->nominal_triples = (int64_t)plan->npairs * ntri;
+  plan->eff_triples = (int64_t)cnt[0];
+  plan->fp64_triples = (int64_t)cnt[1];
+  plan->nominal_triples = (int64_t)plan->npairs * ((int64_t)(L + 1) * (L + 2) / 2);
   auto& ref = *plan;
   g->plans[lmax] = std::move(plan);
   return ref;

@@ -3,10 +3,7 @@
 // preconditioner (Sect. 4.4) and the spatially varying mixing operators
 // (Sect. 2.2, eq:Q).
 //
-// Harmonic vectors are packed m-major (unpack_lm / moff_h); "hat" vectors
-// (the Legendre kernels' input) are c_m f_lm times the plain coefficients,
-// and the adjoint's per-tile partial sums become plain coefficients after the
-// same scaling (hs tables of a plan).
+// Harmonic vectors are packed m-major (unpack_lm / moff_h).
 #include <algorithm>
 
 #include "model.h"
@@ -23,10 +20,9 @@ __device__ __forceinline__ int64_t repack_idx(int L, int m, int part, int ll) {
   return moff_h(L, m) + (int64_t)part * (L - m + 1) + ll;
 }
 
-// out_hat[j][i] = hs[i] f_j[l] (in1_j + in2_j)[l, m, part]  (inputs at their own
+// out[j][i] = f_j[l] (in1_j + in2_j)[l, m, part]  (inputs at their own
 // band-limits, zero above them; in2 optional; f optional)
-__global__ void k_hat_from(double* __restrict__ out, int LO, const double* __restrict__ hs,
-                           const double* __restrict__ in1, int L1, const int64_t* __restrict__ off1, int64_t st1,
+__global__ void k_hat_from(double* __restrict__ out, int LO, const double* __restrict__ in1, int L1, const int64_t* __restrict__ off1, int64_t st1,
                            const double* __restrict__ in2, int L2, int64_t st2,
                            const double* __restrict__ F, int fst, const int* __restrict__ mc, MapSkip skip) {
   const int j = blockIdx.y;
@@ -43,14 +39,14 @@ __global__ void k_hat_from(double* __restrict__ out, int LO, const double* __res
     double v = (l <= L1) ? a[repack_idx(L1, m, part, l - m)] : 0.0;
     if (b && l <= L2) v += b[repack_idx(L2, m, part, l - m)];
     if (f) v *= f[l];
-    o[i] = hs[i] * v;
+    o[i] = v;
   }
 }
 
-// out_j[i] = (acc ? out_j[i] : 0) + alpha f_j[l] hs[i] sum_t parts[t][j][i] - g_j[l] sub_j[l, m, part]
+// out_j[i] = (acc ? out_j[i] : 0) + alpha f_j[l] sum_t parts[t][j][i] - g_j[l] sub_j[l, m, part]
 // (adjoint partial sums at band-limit LO to a plain vector; f, sub optional)
 __global__ void k_from_parts(double* __restrict__ out, const int64_t* __restrict__ offo, int LO, int acc,
-                             double alpha, const double* __restrict__ hs, const double* __restrict__ parts, int ntiles,
+                             double alpha, const double* __restrict__ parts, int ntiles,
                              int64_t tstride, const double* __restrict__ F, int fst,
                              const double* __restrict__ sub, int Ls, int64_t sst, const double* __restrict__ Gs,
                              int gst, const int* __restrict__ mc, MapSkip skip) {
@@ -68,7 +64,7 @@ __global__ void k_from_parts(double* __restrict__ out, const int64_t* __restrict
     int m, part, ll;
     unpack_lm(LO, i, m, part, ll);
     const int l = m + ll;
-    double v = alpha * hs[i] * sv;
+    double v = alpha * sv;
     if (f) v *= f[l];
     if (sb) v -= (l <= Ls ? g[l] * sb[repack_idx(Ls, m, part, ll)] : 0.0);
     o[i] = acc ? o[i] + v : v;
@@ -106,19 +102,19 @@ dim3 map_grid(int64_t npix, int nm) { return dim3((unsigned)std::min<int64_t>((n
 
 }  // namespace
 
-void launch_hat_from(double* out, int LO, const double* hs, const double* in1, int L1, const int64_t* off1,
+void launch_hat_from(double* out, int LO, const double* in1, int L1, const int64_t* off1,
                      int64_t st1, const double* in2, int L2, int64_t st2, const double* F, int fst, const int* mc,
                      int nm, MapSkip skip, hipStream_t s) {
-  hipLaunchKernelGGL(k_hat_from, alm_grid(LO, nm), dim3(256), 0, s, out, LO, hs, in1, L1, off1, st1, in2, L2, st2, F,
+  hipLaunchKernelGGL(k_hat_from, alm_grid(LO, nm), dim3(256), 0, s, out, LO, in1, L1, off1, st1, in2, L2, st2, F,
                      fst, mc, skip);
   CRS_HIP(hipGetLastError());
 }
 
-void launch_from_parts(double* out, const int64_t* offo, int LO, int acc, double alpha, const double* hs,
+void launch_from_parts(double* out, const int64_t* offo, int LO, int acc, double alpha,
                        const double* parts, int ntiles, int64_t tstride, const double* F, int fst, const double* sub,
                        int Ls, int64_t sst, const double* Gs, int gst, const int* mc, int nm, MapSkip skip,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_from_parts, alm_grid(LO, nm), dim3(256), 0, s, out, offo, LO, acc, alpha, hs, parts, ntiles,
+  hipLaunchKernelGGL(k_from_parts, alm_grid(LO, nm), dim3(256), 0, s, out, offo, LO, acc, alpha, parts, ntiles,
                      tstride, F, fst, sub, Ls, sst, Gs, gst, mc, skip);
   CRS_HIP(hipGetLastError());
 }
@@ -142,7 +138,7 @@ void ShtScratch::reserve(crs_grid g, int L, int nm, hipStream_t s) {
   }
   hat.alloc((size_t)nalm_of(L) * nm);
   phase.alloc((size_t)g->nring * (L + 1) * nm);
-  parts.alloc((size_t)leg_adjoint_tiles(c, p.npairs, false) * nalm_of(L) * nm);
+  parts.alloc((size_t)leg_adjoint_tiles(c, g, false) * nalm_of(L) * nm);
 }
 
 void scratch_synth(ShtScratch& w, crs_grid g, int L, int nm, const double* hat, double* map, MapSkip skip,
@@ -167,7 +163,7 @@ int scratch_adjoint(ShtScratch& w, crs_grid g, int L, int nm, const double* map,
   LegArgs la = leg_args(g, p);
   la.skip = skip;
   const LegChoice c = w.choice.at(std::make_pair(g, L)).second;
-  const int nt = leg_adjoint_tiles(c, p.npairs, false);
+  const int nt = leg_adjoint_tiles(c, g, false);
   const int64_t pst = (int64_t)g->nring * (L + 1);
   {
     ProfScope ps(FAM_RING, bytes_work(ring_bytes(g, L, nm, RING_ADJOINT)), s);

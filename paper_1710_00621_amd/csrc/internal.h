@@ -100,19 +100,27 @@ constexpr int kBlueMax = 8192;   // longest Bluestein convolution (power of two)
 constexpr size_t kMaxLds = 160 * 1024;  // LDS bytes one workgroup may use (gfx950)
 
 // ---------------------------------------------------------------- grids
-// Per-(grid, lmax) Legendre plan: start table and recurrence tables.
+// Per-(grid, lmax) Legendre plan: start table and recurrence tables.  Ring
+// pairs sit in slots in tiles of 64 (grid.hip): the polar ones first, padded
+// to whole tiles, then the others.
 struct ShtPlan {
   int lmax = 0;
-  int npairs = 0;
-  int64_t eff_triples = 0;     // (ring pair, l, m) triples the kernels evaluate (|lambda| >= 2^-100)
+  int npairs = 0, nslots = 0;
+  int64_t eff_triples = 0;     // (ring pair, l, m) triples with |lambda| >= 2^-100
   int64_t fp64_triples = 0;    // triples whose |lambda| reaches the float64 normal range
   int64_t nominal_triples = 0; // npairs * (L+1)(L+2)/2
-  DevBuf<double> g;            // triangle: g_lm, mu recurrence coefficient
-  DevBuf<double> f;            // triangle: f_lm, lambda = f * mu
-  DevBuf<double> hs;           // packed alm layout: c_m f_lm (plain <-> hat vectors)
-  DevBuf<int> ls;              // [L+1][npairs]: first l evaluated (L+1 = never)
-  DevBuf<double2> ms;          // [L+1][npairs]: (mu_{ls-1}, mu_ls)
+  DevBuf<double> bp, be, gi;   // rows of m (krow): recurrence coefficients b_k (polar, equator form), 1 / g_{k+1}
+  DevBuf<double> ep;           // (1, 0, 1, 0), then rows of m (erow): eps_lm, l = m .. L + 1
+  DevBuf<int> ks;              // [L+1][nslots]: first k evaluated, a multiple of 8 (INT_MAX = never)
+  DevBuf<double2> st;          // [L+1][nslots]: (q, d) there
 };
+// Row of m in the triangles of the recurrence: K = (L - m) / 2 + 1 steps per m
+// (sum over n = L - m + 1 .. L of n / 2 + 1), and L - m + 2 values of eps.
+__host__ __device__ inline int64_t krow(int L, int m) {
+  const int64_t n = L - m, a = L;
+  return (a * a / 4 + a) - (n * n / 4 + n);
+}
+__host__ __device__ inline int64_t erow(int L, int m) { return (int64_t)m * (L + 2) - (int64_t)m * (m - 1) / 2; }
 
 // Rings are launched in classes by FFT length tier (ring_tier_maxfft(t),
 // ring_tier_threads(t) threads per block) and, from tier 2 up, by Bluestein
@@ -136,7 +144,6 @@ inline int ring_tier_maxfft(int tier) {
 
 // Workspace of the public transforms (sht_synth / sht_adjoint).
 struct GridWork {
-  DevBuf<double> uhat;
   DevBuf<double2> phase;
   DevBuf<double> vpart;
 };
@@ -156,8 +163,10 @@ struct crs_grid_s {
   crs::DevBuf<int64_t> d_offset, d_twoff, d_bfoff;
   crs::DevBuf<double2> d_bf;      // Bluestein filter spectra per distinct length
   crs::DevBuf<double2> d_tw2;     // exp(-2 pi i t / kBlueMax), t < kBlueMax
-  crs::DevBuf<double> d_zpair;    // z of the north ring of each pair
-  crs::DevBuf<double> d_spair;    // sin(theta) of the north ring of each pair
+  // ring pair slots (see slot_layout): polar pairs and tiles, all slots; per
+  // slot z of the north ring, sin(theta) and y = -sin^2 or -z^2
+  int pol_pairs = 0, pol_tiles = 0, nslots = 0;
+  crs::DevBuf<double> d_zs, d_ss, d_ys;
   crs::DevBuf<double2> d_tw;      // twiddles exp(-2 pi i t / N) per distinct N
   int ring_maxn = 1;
   std::vector<crs::RingClass> ring_classes;  // by (tier, Bluestein, odd radix)
@@ -175,7 +184,7 @@ namespace crs {
 ShtPlan& get_plan(crs_grid g, int lmax, hipStream_t s);
 
 // ------------------------------------------------------------ kernels API
-// Legendre stage.  Harmonic inputs are "hat" vectors: u^ = c_m f_lm u.
+// Legendre stage on plain harmonic vectors (legendre.hip).
 // Optional skip of finished systems: map j is skipped when
 // act[kActStride * mapsys[j]] == 0 (both NULL: nothing is skipped).
 constexpr int kActStride = 8;
@@ -188,11 +197,11 @@ struct MapSkip {
 };
 
 struct LegArgs {
-  const double* g;        // triangle
-  const int* ls;          // [L+1][npairs]
-  const double2* ms;      // [L+1][npairs]
-  const double* zpair;    // [npairs]
-  int lmax, npairs, nring;
+  const double *bp, *be, *gi, *ep;  // ShtPlan tables
+  const int* ks;
+  const double2* st;
+  const double *zs, *ys;            // per slot
+  int lmax, npairs, nring, nslots, pol_tiles, pol_pairs;
   MapSkip skip;
   // optional compaction: the launch's map slots s < *mcount are the maps
   // mlist[s] (ascending), the slots past *mcount are empty; without it slot
@@ -200,17 +209,14 @@ struct LegArgs {
   const int* mlist = nullptr;
   const int* mcount = nullptr;
 };
-// Which Legendre kernels run for a (ring pairs, L, maps) shape: synthesis on
-// the matrix cores or vector FP64 with syn_r ring pairs per lane; adjoint on
-// the matrix cores with adj_t 64-pair tiles per wave or vector FP64 with
-// adj_r pairs per lane.  leg_choice gives the autotuned choice for the shape
-// if one was recorded (leg_autotune), else the measured default rules; the
-// environment variables CRS_LEG_MFMA_MIN, CRS_LEG_RS, CRS_LEG_RA and
-// CRS_LEG_TA override either (tuning and tests).  A caller takes the choice
-// once and passes the same one to leg_adjoint_tiles and the launches.
+// Tiles of 64 ring pairs per wave of the Legendre kernels for a (ring pairs,
+// L, maps) shape.  leg_choice gives the autotuned choice for the shape if one
+// was recorded (leg_autotune), else the measured default rules; the
+// environment variables CRS_LEG_TS and CRS_LEG_TA override either (tuning and
+// tests).  A caller takes the choice once and passes the same one to
+// leg_adjoint_tiles and the launches.
 struct LegChoice {
-  int syn_mfma = 0, syn_r = 1;
-  int adj_mfma = 0, adj_r = 1, adj_t = 1;
+  int syn_t = 1, adj_t = 1;
 };
 LegChoice leg_choice(int npairs, int lmax, int nmaps);
 // Times every valid variant of both transforms on the given buffers (their
@@ -218,11 +224,11 @@ LegChoice leg_choice(int npairs, int lmax, int nmaps);
 // fastest per transform for the shape.  Returns the recorded choice.
 LegChoice leg_autotune(const LegArgs& a, int nmaps, double* uhat, double2* phase, hipStream_t s);
 // phase: [nmaps][nring][L+1] double2 (cos, sin parts)
-void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const double* uhat, int64_t ustride,
+void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const double* u, int64_t ustride,
                       double2* phase, int64_t pstride, hipStream_t s);
 // Adjoint: writes ntiles partial vectors vpart[tile][map][nalm], ntiles as
 // returned here for the same choice and square flag as the launch.
-int leg_adjoint_tiles(const LegChoice& c, int npairs, bool square);
+int leg_adjoint_tiles(const LegChoice& c, crs_grid g, bool square);
 void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const double2* phase, int64_t pstride,
                         double* vpart, int64_t vstride, int64_t tstride, bool square,
                         hipStream_t s);
@@ -255,15 +261,9 @@ void launch_ring(crs_grid g, int lmax, RingMode mode, int nmaps, double2* phase,
                  const double* const* weights, int maps_per_weight, hipStream_t s,
                  MapSkip skip = MapSkip{});
 
-// Scaling between plain and hat vectors: out[map] = hs * sum_t in[t][map]
-// elementwise over the packed alm index (hs = c_m f_lm, ShtPlan::hs).
-void launch_tile_sum(const double* hs, int64_t nalm, int nmaps, const double* in, int64_t istride,
-                     int ntiles, int64_t tstride, double* out, int64_t ostride, hipStream_t s);
-// Same with the scale computed per (l, m) from the f triangle; square: f^2
-// without c_m (the M_diag setup).
-void launch_hat_scale(const double* f, int lmax, int nmaps, const double* in, int64_t istride,
-                      int ntiles, int64_t tstride, double* out, int64_t ostride, bool square,
-                      hipStream_t s);
+// out[map] = sum_t in[t][map] elementwise over the packed alm index.
+void launch_tile_sum(int64_t nalm, int nmaps, const double* in, int64_t istride, int ntiles, int64_t tstride,
+                     double* out, int64_t ostride, hipStream_t s);
 
 // Profiling hooks (no-ops unless profiling is on).  A scope brackets its
 // launches with HIP events on the stream.  On a stream that is being

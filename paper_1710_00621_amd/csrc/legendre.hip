@@ -1,22 +1,37 @@
 // Legendre stage of the spherical harmonic transforms on gfx950.
 //
 // Synthesis (first half of Y, Sect. 2.1):
-//     F^{c|s}_m(r) = sum_{l=m..L} lambda_lm(z_r) u^{c|s}_lm
+//     F^{c|s}_m(r) = c_m sum_{l=m..L} lambda_lm(z_r) u^{c|s}_lm
 // Adjoint (second half of Y^T, Sect. 3.2):
-//     v^{c|s}_lm   = sum_r lambda_lm(z_r) H^{c|s}_m(r)
-// The normalised Legendre functions are generated in registers by the
-// mu-recurrence mu_l = g_lm z mu_{l-1} - mu_{l-2} (lambda = f_lm mu, see
-// grid.hip), so the harmonic vectors handed to these kernels are "hat"
-// vectors u^ = c_m f_lm u (c_0 = 1, c_m = sqrt 2) and the adjoint returns
-// v^ with v = c_m f_lm v^.  North/south ring pairs share the recurrence:
-// lambda_lm(-z) = (-1)^(l+m) lambda_lm(z), so even and odd l-m terms are
-// accumulated separately (E, O) and F_N = E + O, F_S = E - O.
+//     v^{c|s}_lm   = c_m sum_r lambda_lm(z_r) H^{c|s}_m(r)
+// with c_0 = 1, c_m = sqrt 2.  North/south ring pairs share the functions:
+// lambda_lm(-z) = (-1)^(l+m) lambda_lm(z), so even and odd l - m (E, O) are
+// summed separately and F_N = E + O, F_S = E - O.
 //
-// Each (ring pair, m) starts at the first l where |lambda_lm| reaches 2^-100
-// (start table from grid.hip); smaller terms are not evaluated.  Lanes of a
-// wave start at different l: the wave runs one recurrence step per l for
-// all lanes and, at the (wave-uniform) l where some lane starts, injects
-// that lane's start values.
+// Recurrence.  With eps_l = sqrt((l^2 - m^2) / (4 l^2 - 1)) the functions obey
+// z lambda_l = eps_{l+1} lambda_{l+1} + eps_l lambda_{l-1}.  The kernels run it
+// two steps at a time on q_k = lambda_{m+2k+1} / z (a polynomial in z^2 times
+// sin^m, so the division is exact at the equator too):
+//     lambda_{m+2k+1} = z q_k,    lambda_{m+2k} = eps_{l+1} q_k + eps_l q_{k-1}  (l = m + 2k)
+//     z^2 q_k = g_{k+1} q_{k+1} + (eps_{l+1}^2 + eps_l^2) q_k + g_k q_{k-1},
+//               g_k = eps_l eps_{l-1}  (l = m + 2k + 1).
+// One function per two l serves both parities, which halves the work, the LDS
+// traffic and the matrix operands of generating lambda, and E and O become
+// columns of one product.  Written for the difference d_k = g_k (q_k -+ q_{k-1}),
+//     d_{k+1} = d_k + (y + b_k) q_k,    q_{k+1} = +-(q_k + d_{k+1} / g_{k+1}),
+// it takes three FP64 operations per two l with two scalar coefficients:
+// near the poles (upper signs) y = -sin^2 theta and b_k = 1 - eps_{l+1}^2 -
+// eps_l^2 - g_k - g_{k+1}, near the equator (lower signs) y = -z^2 and b_k =
+// eps_{l+1}^2 + eps_l^2 - g_k - g_{k+1}.  Both b_k and y vanish where the
+// recurrence's characteristic roots meet, so nothing cancels: against 80-bit
+// arithmetic over all rings and m the functions are 10 (Nside 64, L 128) to 35
+// (Nside 512, L 1024) times closer than the one-step recurrence in l.  Tiles
+// of 64 ring pairs use one form each (grid.hip lays the pairs out in slots so
+// that every tile lies well inside one form's range).
+//
+// Each (ring pair, m) starts at the last multiple of 8 in k at or before the
+// first l where |lambda_lm| reaches 2^-100 (start table from grid.hip); before
+// it a lane carries zeros, and lanes join at the start of a block of 8 steps.
 #include <algorithm>
 #include <climits>
 #include <map>
@@ -31,8 +46,8 @@ namespace crs {
 
 namespace {
 
-// Read-only tables and harmonic inputs are read through the constant
-// address space so that wave-uniform loads become scalar (SMEM) loads.
+// Tables and wave-uniform inputs are read through the constant address space
+// so that they become scalar (SMEM) loads.
 typedef __attribute__((address_space(4))) const double cdouble;
 __device__ __forceinline__ cdouble* as_const(const double* p) {
   const uint64_t v = (uint64_t)p;
@@ -40,19 +55,34 @@ __device__ __forceinline__ cdouble* as_const(const double* p) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return (cdouble*)(((uint64_t)hi << 32) | lo);
 }
-// wave-uniform element (scalar load)
-__device__ __forceinline__ double uld(cdouble* p, int i) { return p[__builtin_amdgcn_readfirstlane(i)]; }
 
 // minimum over the wave's active lanes (DPP reduction, no LDS round trips)
 __device__ __forceinline__ int wave_min(int v) {
   return __builtin_amdgcn_readfirstlane(__ockl_wfred_min_i32(v));
 }
 
-// v + v of lane t ^ 32 and v + v of lane t ^ 16, with the gfx950 lane-swap
-// instructions (v_permlane32_swap exchanges the upper half of its first
-// operand with the lower half of its second; v_permlane16_swap the odd rows of
-// the first with the even rows of the second): swapping v with itself leaves
-// the lane's own value in one result and the partner's in the other.
+// Lane exchanges of doubles.  dpp<CTRL, BANKS>: the DPP control applied to v
+// in the banks (groups of four lanes of a row of 16) that BANKS selects, old
+// elsewhere.
+template <int CTRL, int BANKS>
+__device__ __forceinline__ double dpp(double old, double v) {
+  const uint64_t u = __double_as_longlong(v), o = __double_as_longlong(old);
+  const unsigned lo = __builtin_amdgcn_update_dpp((unsigned)o, (unsigned)u, CTRL, 0xf, BANKS, false);
+  const unsigned hi = __builtin_amdgcn_update_dpp((unsigned)(o >> 32), (unsigned)(u >> 32), CTRL, 0xf, BANKS, false);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+constexpr int kDppXor2 = 0x4e;     // quad_perm [2, 3, 0, 1]
+constexpr int kDppRor4 = 0x124;    // row_ror: lane i of a row takes lane i - 4 (mod 16)
+constexpr int kDppRor8 = 0x128;
+constexpr int kDppRor12 = 0x12c;
+// v of lane src (any lane of the wave)
+__device__ __forceinline__ double lane_get(double v, int src) {
+  const uint64_t u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_ds_bpermute(4 * src, (unsigned)u);
+  const unsigned hi = __builtin_amdgcn_ds_bpermute(4 * src, (unsigned)(u >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+// v + v of lane t ^ 32 and v + v of lane t ^ 16 (gfx950 lane swaps)
 __device__ __forceinline__ double add_xor32(double v) {
   const uint64_t u = __double_as_longlong(v);
   const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
@@ -62,187 +92,17 @@ __device__ __forceinline__ double add_xor32(double v) {
   const double y = __longlong_as_double((long long)(((uint64_t)b[1] << 32) | a[1]));
   return x + y;
 }
-// Transposing form: lanes t < 32 get A(t) + A(t + 32), lanes t >= 32 get
-// B(t - 32) + B(t) (both lanes of a pair add in the same order).
-__device__ __forceinline__ double fold32(double A, double B) {
-  const uint64_t ua = __double_as_longlong(A), ub = __double_as_longlong(B);
-  const auto a = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
-  const auto b = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-  const double x = __longlong_as_double((long long)(((uint64_t)b[0] << 32) | a[0]));
-  const double y = __longlong_as_double((long long)(((uint64_t)b[1] << 32) | a[1]));
-  return x + y;
-}
-__device__ __forceinline__ double add_xor16(double v) {
-  const uint64_t u = __double_as_longlong(v);
-  const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
-  const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  const double x = __longlong_as_double((long long)(((uint64_t)b[0] << 32) | a[0]));
-  const double y = __longlong_as_double((long long)(((uint64_t)b[1] << 32) | a[1]));
-  return x + y;
-}
 
 __device__ __forceinline__ int64_t moff(int L, int m) {
   return (m == 0) ? 0 : (int64_t)(L + 1) + 2 * ((int64_t)(m - 1) * (L + 1) - (int64_t)(m - 1) * m / 2);
 }
-__device__ __forceinline__ int64_t tri(int L, int m) {
-  return (int64_t)m * (L + 1) - (int64_t)m * (m - 1) / 2;
-}
 
-// ------------------------------------------------------- per-wave stepper
-// A wave owns R groups of 64 ring pairs: pair of group j on lane t is
-// base + 64 j + t (j = 0 most polar).  Per group the wave keeps the lanes'
-// recurrence state and two wave-uniform numbers: lw (first l any lane of
-// groups j..R-1 evaluates; lw[R-1] is where the wave starts stepping) and nx
-// (next l where some lane of the group starts).  Between start events all
-// groups step in lockstep; a lane before its start carries zero state.
-template <int R>
-struct Grp {
-  double z[R], a0[R], a1[R];
-  double2 st[R];  // the lane's start values (mu_{ls-1}, mu_ls), loaded up front
-  int ls[R];
-  int lw[R];
-  int nx[R];
-};
-
-template <int R>
-__device__ __forceinline__ void grp_init(Grp<R>& G, const LegArgs& a, int m, int base, int lane) {
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const int p = base + 64 * j + lane;
-    const bool valid = p < a.npairs;
-    G.z[j] = a.zpair[valid ? p : a.npairs - 1];
-    G.ls[j] = valid ? a.ls[(size_t)m * a.npairs + p] : INT_MAX;
-    G.st[j] = valid ? a.ms[(size_t)m * a.npairs + p] : make_double2(0.0, 0.0);
-    G.a0[j] = 0.0;
-    G.a1[j] = 0.0;
-    const int w = wave_min(G.ls[j]);
-    G.nx[j] = w;
-    G.lw[j] = (j == 0) ? w : min(w, G.lw[j - 1]);
-  }
-}
-
-// One step of group j at l with start injection (event step).
-template <int R>
-__device__ __forceinline__ double grp_event_step(Grp<R>& G, int j, const LegArgs& a, int m, int base,
-                                                 int lane, int l, double gl) {
-  double c = fma(gl * G.z[j], G.a1[j], -G.a0[j]);
-  double pv = G.a1[j];
-  if (l == G.nx[j]) {
-    if (G.ls[j] == l) {
-      c = G.st[j].y;
-      pv = G.st[j].x;
-    }
-    G.nx[j] = wave_min(G.ls[j] > l ? G.ls[j] : INT_MAX);
-  }
-  G.a0[j] = pv;
-  G.a1[j] = c;
-  return c;
-}
-
-// ------------------------------------------------------------- synthesis
-// Accumulators X (parity of the next step) and Y (the other parity): every
-// step adds into X and then swaps X and Y, so consecutive steps need no
-// parity test (the swap is free inside unrolled pairs).  At the end X holds
-// the sum over l with l - m of the parity of L + 1 - m.
-template <int NM, int R>
-struct SynAcc {
-  double X[R][NM][2], Y[R][NM][2];  // [group][map][cos, sin]
-};
-
-template <int NM, int R>
-__device__ __forceinline__ void syn_swap(SynAcc<NM, R>& A) {
-#pragma unroll
-  for (int j = 0; j < R; ++j)
-#pragma unroll
-    for (int k = 0; k < NM; ++k)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const double t = A.X[j][k][c];
-        A.X[j][k][c] = A.Y[j][k][c];
-        A.Y[j][k][c] = t;
-      }
-}
-
-// one step of every group into X (no swap)
-template <int NM, int R, bool HAS_S>
-__device__ __forceinline__ void syn_acc(SynAcc<NM, R>& A, Grp<R>& G, double gl, const double* uc,
-                                        const double* us) {
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const double c = fma(gl * G.z[j], G.a1[j], -G.a0[j]);
-    G.a0[j] = G.a1[j];
-    G.a1[j] = c;
-#pragma unroll
-    for (int k = 0; k < NM; ++k) {
-      A.X[j][k][0] = fma(c, uc[k], A.X[j][k][0]);
-      if (HAS_S) A.X[j][k][1] = fma(c, us[k], A.X[j][k][1]);
-    }
-  }
-}
-
-// One chunk of B steps from l (B even, so the even / odd accumulators keep
-// their roles).  EV: some lane may start inside the chunk; every step then
-// checks for start events (wave-uniform test per group, start values and
-// the next event only at an event).
-template <int NM, int R, bool HAS_S, bool EV>
-__device__ __forceinline__ void syn_chunk(SynAcc<NM, R>& A, Grp<R>& G, const LegArgs& a, int m, int base,
-                                          int lane, cdouble* gb, cdouble* const* ub, int nsl, int l) {
-  constexpr int B = (NM == 1) ? 8 : ((NM == 2) ? 4 : 2);
-  l = __builtin_amdgcn_readfirstlane(l);
-  cdouble* gp = gb + l;
-  double gv[B], uc[B][NM], us[B][NM];
-#pragma unroll
-  for (int i = 0; i < B; ++i) gv[i] = gp[i];
-#pragma unroll
-  for (int k = 0; k < NM; ++k) {
-    cdouble* up = ub[k] + l;
-#pragma unroll
-    for (int i = 0; i < B; ++i) {
-      uc[i][k] = up[i];
-      us[i][k] = HAS_S ? up[i + nsl] : 0.0;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < B; ++i) {
-    if (EV) {
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        const double c = grp_event_step<R>(G, j, a, m, base, lane, l + i, gv[i]);
-#pragma unroll
-        for (int k = 0; k < NM; ++k) {
-          A.X[j][k][0] = fma(c, uc[i][k], A.X[j][k][0]);
-          if (HAS_S) A.X[j][k][1] = fma(c, us[i][k], A.X[j][k][1]);
-        }
-      }
-    } else {
-      syn_acc<NM, R, HAS_S>(A, G, gv[i], uc[i], us[i]);
-    }
-    syn_swap<NM, R>(A);
-  }
-}
-
-// one event-checked step at l (the last steps of a wave, fewer than a chunk)
-template <int NM, int R, bool HAS_S>
-__device__ __forceinline__ void syn_step(SynAcc<NM, R>& A, Grp<R>& G, const LegArgs& a, int m, int base,
-                                         int lane, cdouble* gb, cdouble* const* ub, int nsl, int l) {
-  const double gl = uld(gb, l);
-  double uc[NM], us[NM];
-#pragma unroll
-  for (int k = 0; k < NM; ++k) {
-    uc[k] = uld(ub[k], l);
-    us[k] = HAS_S ? uld(ub[k], l + nsl) : 0.0;
-  }
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const double c = grp_event_step<R>(G, j, a, m, base, lane, l, gl);
-#pragma unroll
-    for (int k = 0; k < NM; ++k) {
-      A.X[j][k][0] = fma(c, uc[k], A.X[j][k][0]);
-      if (HAS_S) A.X[j][k][1] = fma(c, us[k], A.X[j][k][1]);
-    }
-  }
-  syn_swap<NM, R>(A);
+// LDS traffic of one wave stays in order: only the compiler must not move
+// accesses of the wave-private tile across this point.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // map slots of a launch (see LegArgs::mlist)
@@ -257,60 +117,18 @@ __device__ __forceinline__ bool leg_any(const LegArgs& a, int s0, int n, int ns)
   for (int k = 0; k < n && s0 + k < ns; ++k) any = any || !a.skip.off(leg_map(a, s0 + k));
   return any;
 }
-
-template <int NM, int R, bool HAS_S>
-__device__ __forceinline__ void synth_wave(const LegArgs& a, int m, int base, int lane, int nmaps, int map0,
-                                           const double* __restrict__ uhat, int64_t ustride,
-                                           double2* __restrict__ phase, int64_t pstride) {
-  const int L = a.lmax;
-  cdouble* gb = as_const(a.g + tri(L, m) - m);
-  const int nsl = L - m + 1;
-  cdouble* ub[NM];
-#pragma unroll
-  for (int k = 0; k < NM; ++k)
-    ub[k] = as_const(uhat + (int64_t)leg_map(a, min(map0 + k, nmaps - 1)) * ustride + moff(L, m) - m);
-  Grp<R> G;
-  grp_init<R>(G, a, m, base, lane);
-  SynAcc<NM, R> A;
-#pragma unroll
-  for (int j = 0; j < R; ++j)
-#pragma unroll
-    for (int k = 0; k < NM; ++k) A.X[j][k][0] = A.X[j][k][1] = A.Y[j][k][0] = A.Y[j][k][1] = 0.0;
-  // all R groups step from the first start of any of them (groups that have
-  // not started carry zero state and add zeros), in chunks of B steps; a
-  // chunk takes the event-checked path only if a start falls inside it
-  constexpr int B = (NM == 1) ? 8 : ((NM == 2) ? 4 : 2);
-  int l = G.lw[R - 1];
-  for (; l + B <= L + 1; l += B) {
-    int ne = G.nx[0];
-#pragma unroll
-    for (int j = 1; j < R; ++j) ne = min(ne, G.nx[j]);
-    if (ne >= l + B)
-      syn_chunk<NM, R, HAS_S, false>(A, G, a, m, base, lane, gb, ub, nsl, l);
-    else
-      syn_chunk<NM, R, HAS_S, true>(A, G, a, m, base, lane, gb, ub, nsl, l);
-  }
-  for (; l <= L; ++l) syn_step<NM, R, HAS_S>(A, G, a, m, base, lane, gb, ub, nsl, l);
-  // X holds parity (L + 1 - m) & 1 (the loop always ends at l = L + 1, or
-  // never ran, in which case X = Y = 0)
-  const bool x_is_odd = ((L + 1 - m) & 1) != 0;
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const int p = base + 64 * j + lane;
-    const int rs = a.nring - 1 - p;
-#pragma unroll
-    for (int k = 0; k < NM; ++k) {
-      const double ec = x_is_odd ? A.Y[j][k][0] : A.X[j][k][0];
-      const double es = x_is_odd ? A.Y[j][k][1] : A.X[j][k][1];
-      const double oc = x_is_odd ? A.X[j][k][0] : A.Y[j][k][0];
-      const double os = x_is_odd ? A.X[j][k][1] : A.Y[j][k][1];
-      if (p < a.npairs && map0 + k < nmaps) {
-        double2* ph = phase + (int64_t)leg_map(a, map0 + k) * pstride;
-        ph[(int64_t)p * (L + 1) + m] = make_double2(ec + oc, es + os);
-        if (rs != p) ph[(int64_t)rs * (L + 1) + m] = make_double2(ec - oc, es - os);
-      }
-    }
-  }
+// Ring pairs p0 .. of a tile: pair p0 + i in slot i, valid below limit.  full:
+// all 64 are valid and none is the equator ring, its own pair.
+struct TilePairs {
+  int p0, limit;
+  bool full;
+};
+__device__ __forceinline__ TilePairs tile_pairs(const LegArgs& a, int tile, bool polar) {
+  TilePairs t;
+  t.p0 = polar ? tile * 64 : (tile - a.pol_tiles) * 64 + a.pol_pairs;
+  t.limit = polar ? a.pol_pairs : a.npairs;
+  t.full = t.p0 + 64 <= t.limit && 2 * (t.p0 + 63) + 1 < a.nring;
+  return t;
 }
 
 // XCD-aware order: the 8 XCDs take blocks round-robin; consecutive blocks on
@@ -324,554 +142,704 @@ __device__ __forceinline__ void block_coords(int ntiles, int& mb, int& tile) {
   mb = (q / ntiles) * 8 + xcd;
 }
 
-template <int NM, int R>
-__global__ __launch_bounds__(256) void k_leg_synth(LegArgs a, int nmaps, const double* __restrict__ uhat,
-                                                   int64_t ustride, double2* __restrict__ phase,
-                                                   int64_t pstride, int ntiles) {
-  int mb, tile;
-  block_coords(ntiles, mb, tile);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m = mb * 4 + wave;
-  if (m > a.lmax) return;
-  const int lane = threadIdx.x & 63;
-  const int base = tile * 64 * R;
-  const int map0 = blockIdx.y * NM;
-  const int ns = leg_nslots(a, nmaps);
-  if (!leg_any(a, map0, NM, ns)) return;
-  if (m == 0)
-    synth_wave<NM, R, false>(a, m, base, lane, ns, map0, uhat, ustride, phase, pstride);
-  else
-    synth_wave<NM, R, true>(a, m, base, lane, ns, map0, uhat, ustride, phase, pstride);
+// ----------------------------------------------------------- recurrence
+// State of one lane's ring pair: (q, d) before step k, k a multiple of 8.
+struct RecState {
+  double y, q, d;
+  int ks;     // the lane's start
+  int nx;     // next start in the wave (uniform)
+  int first;  // first start in the wave (uniform)
+};
+__device__ __forceinline__ void rec_init(RecState& r, const LegArgs& a, int m, int slot, bool in) {
+  r.y = in ? a.ys[slot] : 0.0;
+  r.ks = in ? a.ks[(size_t)m * a.nslots + slot] : INT_MAX;
+  r.q = r.d = 0.0;
+  r.nx = r.first = wave_min(r.ks);
 }
 
-// ------------------------------------------------------ synthesis, MFMA
-// For many maps the l-contraction F_par[p][col] = sum_{l of parity par}
-// lambda_lm(p) u[l][col] is a dense product: rows = ring pairs, K = values of
-// l of one parity (l - m even: E, odd: O), N = 16 columns = 8 maps x (cos,
-// sin).  Operand layouts of v_mfma_f64_16x16x4 on gfx950 (measured): A lane t
-// = A[t % 16][t / 16], B lane t = B[t / 16][t % 16], D lane t register r =
-// D[t / 16 + 4 r][t % 16].
-// One wave owns (m, 64 ring pairs, 8 maps); lane t runs the recurrence of
-// pair t.  Each block of 8 steps [lb, lb + 8) (lb - m even) goes through a
-// wave-private LDS tile lam[8][64] so that row block rb (pairs 16 rb ..
-// 16 rb + 15) can be handed to the MFMA as A (lane (i, k) takes lam[2k][16 rb
-// + i] for E, lam[2k + 1][...] for O); B is u at l = lb + 2k (+1) for the 16
-// columns.  8 MFMAs per block, start indices injected at wave-uniform event
-// blocks as in the vector kernels.
+// Coefficients of N steps from k0 (scalar registers)
+template <int N>
+struct RecCoef {
+  double b[N], g[N];
+};
+template <int N>
+__device__ __forceinline__ RecCoef<N> rec_coef(cdouble* b, cdouble* gi, int k0) {
+  RecCoef<N> c;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    c.b[i] = b[k0 + i];
+    c.g[i] = gi[k0 + i];
+  }
+  return c;
+}
+
+// Eight steps of the signed q_k, k = k0 .. k0 + 7, with the coefficients from
+// C.b[O] on, each pair (even, odd k) handed to put(i / 2, q_i, q_{i+1}).  Lanes
+// whose start is k0 join first.
+template <bool POLAR, int O, int N, class Put>
+__device__ __forceinline__ void rec8(RecState& r, const RecCoef<N>& C, const LegArgs& a, int m, int slot, int k0,
+                                     Put&& put) {
+  if (r.nx == k0) {
+    if (r.ks == k0) {
+      const double2 v = a.st[(size_t)m * a.nslots + slot];
+      asm volatile("" ::"v"(v.x), "v"(v.y));  // waited for here, not where the paths meet (prefetches stay in flight)
+      r.q = v.x;
+      r.d = v.y;
+    }
+    r.nx = wave_min(r.ks > k0 ? r.ks : INT_MAX);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    const double qe = r.q;
+    r.d = fma(r.y + C.b[O + i], qe, r.d);
+    if (POLAR) {
+      const double qo = fma(C.g[O + i], r.d, qe);
+      put(i / 2, qe, qo);
+      r.d = fma(r.y + C.b[O + i + 1], qo, r.d);
+      r.q = fma(C.g[O + i + 1], r.d, qo);
+    } else {
+      const double qo = fma(-C.g[O + i], r.d, -qe);  // the recurrence runs on -qo
+      put(i / 2, qe, qo);
+      r.d = fma(-(r.y + C.b[O + i + 1]), qo, r.d);
+      r.q = fma(C.g[O + i + 1], r.d, -qo);
+    }
+  }
+}
+
+// Tile groups: the polar tiles in groups of T, then the others, so that a wave
+// runs one form (chosen once) and its tiles share the coefficients.
+struct TileRange {
+  int t0, tend;
+  bool polar;
+};
+template <int T>
+__device__ __forceinline__ TileRange tile_range(const LegArgs& a, int tg) {
+  const int np = (a.pol_tiles + T - 1) / T;
+  if (tg < np) return {tg * T, a.pol_tiles, true};
+  return {a.pol_tiles + (tg - np) * T, a.nslots / 64, false};
+}
+
+// Wave-private LDS tile of q: row k / 2 holds the pairs (q_k, q_{k+1}) of 64
+// ring pairs as double2.  The row lengths (in double2) are the ones whose A
+// operand reads are free of bank conflicts (measured, cycles per instruction:
+// 16-byte reads 4.6 at 64 for the synthesis' rows of 16 lanes and at 68 for
+// the adjoint's four rows at a time, 8 to 16 at other lengths; 8-byte reads of
+// eight rows 4.1 at 65).  LDS writes run at 76 bytes per cycle in any shape,
+// which with one map per wave is as tight a bound as the FP64 pipe.
+constexpr int kQRowSyn = 64, kQRowAdj4 = 68, kQRowAdj16 = 65;
+
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ void lds_wave_sync() {
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS traffic done
-  __builtin_amdgcn_wave_barrier();
-}
-
-__global__ __launch_bounds__(256) void k_leg_synth_mfma(LegArgs a, int nmaps, const double* __restrict__ uhat,
-                                                        int64_t ustride, double2* __restrict__ phase,
-                                                        int64_t pstride, int ntiles) {
-  __shared__ double lamsh[4][8 * 64];
-  int mb, tile;
-  block_coords(ntiles, mb, tile);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m = mb * 4 + wave;
+// ------------------------------------------------------------- synthesis
+// F[pair][col] = sum_k q_k[pair] B[k][col] on the matrix cores: rows = ring
+// pairs, K = k, columns = maps x (E, O) x (cos, sin) with B_E = eps_{l+1} u_l
+// + eps_{l+2} u_{l+2} (l = m + 2k) and B_O = u_{l+1}, formed as they are loaded.
+// C16 groups of four maps take v_mfma_f64_16x16x4 (16 columns), C4 single maps
+// v_mfma_f64_4x4x4 (four blocks of four rows share one map's four columns):
+// both run at the same FP64 rate (77 TFLOP/s measured) and read the same A
+// operand (lane t: row t % 16, k t / 16), so any map count runs without empty
+// columns.  Matrix and vector FP64 instructions share the issue pipe (measured:
+// they add), which is why the recurrence's three operations per two l matter.
+// One wave owns (m, T tiles of 64 ring pairs, 4 C16 + C4 maps); a block of 8
+// steps goes through the wave's LDS tile into the A operands.
+template <int C16, int C4, int T, bool POLAR>
+__device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int t0, int tend, int map0, int ns,
+                                         const double* __restrict__ u, int64_t ustride,
+                                         double2* __restrict__ phase, int64_t pstride, double2* qsh) {
+  constexpr int NG = C16 + C4, NMW = 4 * C16 + C4;
   const int L = a.lmax;
-  if (m > L) return;
-  const int mg = blockIdx.y;
-  const int ns = leg_nslots(a, nmaps);
-  if (!leg_any(a, mg * 8, 8, ns)) return;
-  double* lam = lamsh[wave];
+  const bool mok = mw <= L;  // a block's last waves may lie past L: they only join its stores
+  const int m = min(mw, L);
+  double2* qt = qsh + wave * (4 * kQRowSyn);
   const int lane = threadIdx.x & 63;
   const int i16 = lane & 15, kq = lane >> 4;
-  const int p = tile * 64 + lane;
-  const bool valid = p < a.npairs;
-  const double z = valid ? a.zpair[p] : 0.0;
-  const int ls = valid ? a.ls[(size_t)m * a.npairs + p] : INT_MAX;
-  const double2 st = valid ? a.ms[(size_t)m * a.npairs + p] : make_double2(0.0, 0.0);
-  // B column of this lane: map mg * 8 + j / 2, part j & 1 (cos, sin)
-  const int j = i16;
-  const int slot = mg * 8 + (j >> 1), cs = j & 1;
-  const bool sok = slot < ns;
-  const int map = sok ? leg_map(a, slot) : 0;
-  const double* __restrict__ ub =
-      (sok && !(m == 0 && cs == 1)) ? uhat + (int64_t)map * ustride + moff(L, m) + cs * (L - m + 1) - m : nullptr;
-  cdouble* gb = as_const(a.g + tri(L, m) - m);  // 8 zeros follow the table
-  // B loads are unconditional (clamped index, then masked) so that the
-  // in-order vector-memory counter lets the next block's loads stay in flight
-  const double* __restrict__ ubase = ub ? ub : uhat + m;
-  const double bmask = ub ? 1.0 : 0.0;
-  auto loadB = [&](int l) {
-    const double v = ubase[l <= L ? l : L];
-    return v * (l <= L ? bmask : 0.0);  // the value is always used: the load stays unconditional
-  };
-  const int lfirst = wave_min(ls);
-  v4d DE[4], DO[4];
+  const int par = (lane >> 1) & 1, cs = lane & 1;
+  const int n = L - m;  // largest l - m
+  const int K = n / 2 + 1;
+  // column g of this lane: map slot
+  int cslot[NG];
 #pragma unroll
-  for (int rb = 0; rb < 4; ++rb) {
-    DE[rb] = v4d{0.0, 0.0, 0.0, 0.0};
-    DO[rb] = v4d{0.0, 0.0, 0.0, 0.0};
+  for (int g = 0; g < NG; ++g) cslot[g] = g < C16 ? map0 + 4 * g + ((lane >> 2) & 3) : map0 + 4 * C16 + (g - C16);
+  RecState r[T];
+  int kst = INT_MAX;
+  cdouble* cb = as_const((POLAR ? a.bp : a.be) + krow(L, m));
+  cdouble* cg = as_const(a.gi + krow(L, m));
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    rec_init(r[t], a, m, (t0 + t) * 64 + lane, t0 + t < tend && mok);
+    kst = min(kst, r[t].first);
   }
-  if (lfirst <= L) {
-    int lb = lfirst - ((lfirst - m) & 1);
-    int nx = lfirst;  // next l at which some lane starts
-    double a0 = 0.0, a1 = 0.0;
-    double bE = loadB(lb + 2 * kq);
-    double bO = loadB(lb + 2 * kq + 1);
-    for (; lb <= L; lb += 8) {
-      lb = __builtin_amdgcn_readfirstlane(lb);
-      const double nE = loadB(lb + 8 + 2 * kq);
-      const double nO = loadB(lb + 9 + 2 * kq);
-      double gv[8];
-      cdouble* gp = gb + lb;
+  v4d D16[T][4][C16 > 0 ? C16 : 1];
+  double D4[T][4][C4 > 0 ? C4 : 1];
 #pragma unroll
-      for (int s2 = 0; s2 < 8; ++s2) gv[s2] = gp[s2];
-      if (nx >= lb + 8) {
+  for (int t = 0; t < T; ++t)
 #pragma unroll
-        for (int s2 = 0; s2 < 8; ++s2) {
-          const double cc = fma(gv[s2] * z, a1, -a0);
-          a0 = a1;
-          a1 = cc;
-          lam[s2 * 64 + lane] = cc;
+    for (int rb = 0; rb < 4; ++rb) {
+#pragma unroll
+      for (int g = 0; g < C16; ++g) D16[t][rb][g] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < C4; ++c) D4[t][rb][c] = 0.0;
+    }
+  // This lane's k in a block are k0 + 2 kq and k0 + 2 kq + 1: l - m = x, x + 2
+  // (and x + 4 for the second's eps_{l+2} term), x = 2 (k0 + 2 kq) + par.
+  // Pointers run with k0: u of the lane's part, and (eps_{l+1}, eps_{l+2},
+  // eps_{l+3}, eps_{l+4}) of E columns or the fixed (1, 0, 1, 0) of O columns.
+  const int k1 = min(kst, K);
+  const double* up[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g)
+    up[g] = u + (int64_t)leg_map(a, min(cslot[g], ns - 1)) * ustride + moff(L, m) + (m > 0 && cs ? n + 1 : 0) +
+            2 * (k1 + 2 * kq) + par;
+  const double* ep = par ? a.ep : a.ep + 4 + erow(L, m) + 1 + 2 * (k1 + 2 * kq);
+  const int64_t estep = par ? 0 : 16;
+  double un[NG][3], en[4];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) en[i] = ep[i];
+    ep += estep;
+    if (2 * (k0 + 7) + 3 <= n) {
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) un[g][i] = up[g][2 * i];
+    } else {
+      const int x = 2 * (k0 + 2 * kq) + par;
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          const double v = up[g][min(2 * i, n - x)];  // clamped to l = L
+          un[g][i] = x + 2 * i <= n ? v : 0.0;
         }
-      } else {
+    }
 #pragma unroll
-        for (int s2 = 0; s2 < 8; ++s2) {
-          double cc = fma(gv[s2] * z, a1, -a0);
-          double pv = a1;
-          if (ls == lb + s2) {
-            cc = st.y;
-            pv = st.x;
-          }
-          a0 = pv;
-          a1 = cc;
-          lam[s2 * 64 + lane] = cc;
-        }
-        nx = wave_min(ls >= lb + 8 ? ls : INT_MAX);
-      }
-      lds_wave_sync();
+    for (int g = 0; g < NG; ++g) up[g] += 16;
+  };
+  RecCoef<8> C{};
+  if (kst < K) {
+    load(kst);
+    C = rec_coef<8>(cb, cg, kst);
+  }
+  const bool two = C16 < 2 || map0 + 4 < ns;  // the second group of four has maps
+  for (int k0 = kst; k0 < K; k0 += 8) {
+    k0 = __builtin_amdgcn_readfirstlane(k0);
+    double B0[NG], B1[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      B0[g] = fma(en[1], un[g][1], en[0] * un[g][0]);
+      B1[g] = fma(en[3], un[g][2], en[2] * un[g][1]);
+    }
+    load(k0 + 8);  // past K: in bounds, unused
+    RecCoef<8> Cn;
+    if (T > 1) Cn = rec_coef<8>(cb, cg, k0 + 8);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      if (T > 1 && r[t].first > k0) continue;
+      rec8<POLAR, 0>(r[t], C, a, m, (t0 + t) * 64 + lane, k0,
+                     [&](int i, double qe, double qo) { qt[i * kQRowSyn + lane] = make_double2(qe, qo); });
+      if (T == 1) C = rec_coef<8>(cb, cg, k0 + 8);  // the next block's, during the products
+      wave_fence();
+      double2 A[4];
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) A[rb] = qt[kq * kQRowSyn + 16 * rb + i16];
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb) {
-        const double aE = lam[(2 * kq) * 64 + 16 * rb + i16];
-        const double aO = lam[(2 * kq + 1) * 64 + 16 * rb + i16];
-        DE[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aE, bE, DE[rb], 0, 0, 0);
-        DO[rb] = __builtin_amdgcn_mfma_f64_16x16x4f64(aO, bO, DO[rb], 0, 0, 0);
+#pragma unroll
+        for (int g = 0; g < C16; ++g)
+          if (g == 0 || two)
+            D16[t][rb][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[rb].x, B0[g], D16[t][rb][g], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < C4; ++c)
+          D4[t][rb][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[rb].x, B0[C16 + c], D4[t][rb][c], 0, 0, 0);
       }
-      // the next block's LDS writes follow these reads in this wave's program
-      // order, which the LDS preserves; only keep the compiler from hoisting them
-      __builtin_amdgcn_wave_barrier();
-      bE = nE;
-      bO = nO;
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) {
+#pragma unroll
+        for (int g = 0; g < C16; ++g)
+          if (g == 0 || two)
+            D16[t][rb][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[rb].y, B1[g], D16[t][rb][g], 0, 0, 0);
+#pragma unroll
+        for (int c = 0; c < C4; ++c)
+          D4[t][rb][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[rb].y, B1[C16 + c], D4[t][rb][c], 0, 0, 0);
+      }
+      wave_fence();
     }
+    if (T > 1) C = Cn;
   }
-  // D[rb][row = kq + 4 r][col = j]: ring pair tile*64 + 16 rb + kq + 4 r
-  if (!sok) return;
-  double* ph = reinterpret_cast<double*>(phase + (int64_t)map * pstride);
+  // Lanes of E columns store the north ring, lanes of O columns the south one
+  // (the column t ^ 2 holds the other parity of the same part): c_m (D + z O)
+  // and c_m (E - z D).
+  const double cm = m == 0 ? (cs ? 0.0 : 1.0) : 1.4142135623730951;
+  const int64_t rstep = 2 * (int64_t)(L + 1);
 #pragma unroll
-  for (int rb = 0; rb < 4; ++rb)
+  for (int t = 0; t < T; ++t) {
+    if (t0 + t >= tend) break;
+    const TilePairs tp = tile_pairs(a, t0 + t, POLAR);
+    const double* zt = a.zs + (t0 + t) * 64;
+    if constexpr (C16 == 0) {
+      // one to three maps: straight to the phase array
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int pp = tile * 64 + 16 * rb + kq + 4 * r;
-      if (pp >= a.npairs) continue;
-      const int rs = a.nring - 1 - pp;
-      ph[2 * ((int64_t)pp * (L + 1) + m) + cs] = DE[rb][r] + DO[rb][r];
-      if (rs != pp) ph[2 * ((int64_t)rs * (L + 1) + m) + cs] = DE[rb][r] - DO[rb][r];
-    }
-}
-
-// --------------------------------------------------------------- adjoint
-// Same wave decomposition.  Per l every lane sums its groups' products into
-// P[s]; each chunk of CH steps is reduced over the wave's 64 lanes through a
-// wave-private LDS block (no block barrier) in a fixed order and written as
-// the wave's partial v^ (one partial per ring tile of 64 R pairs).
-constexpr int kRedStride = 33;  // row stride (doubles) of the reduction block
-template <int NM>
-struct AdjCfg {
-  static constexpr int CH = (8 / NM) < 1 ? 1 : (8 / NM);
-  static constexpr int NOUT = CH * NM * 2;
-};
-
-// One chunk of CH steps [lc, lc + CH) for all R groups (lc - m even: even
-// steps use E, odd steps O).  Groups that have not started yet carry zero
-// state and contribute zeros.  FAST: no start event inside the chunk and all
-// CH steps <= L, so there are no per-step checks and P is initialised by the
-// first group's products.  Otherwise every step checks for start events and
-// the band-limit, and P must be zeroed by the caller.
-template <int NM, int R, bool FAST, bool SQ, bool HAS_S>
-__device__ __forceinline__ void adj_chunk(Grp<R>& G, const double (&E)[R][NM][2], const double (&O)[R][NM][2],
-                                          const double (&gv)[AdjCfg<NM>::CH], const LegArgs& a, int m,
-                                          int base, int lane, int lc, int L,
-                                          double (&P)[AdjCfg<NM>::CH][NM][2]) {
-  constexpr int CH = AdjCfg<NM>::CH;
+      for (int rb = 0; rb < 4; ++rb) {
+        // D: block (t / 4) % 4, row t / 16 of it, column t % 4
+        const int i = 16 * rb + 4 * ((lane >> 2) & 3) + kq;
+        const double cz = cm * zt[i];
+        const double wd = par ? -cz : cm, wo = par ? cm : cz;
+        const int p = tp.p0 + i, ring = par ? a.nring - 1 - p : p;
+        const bool ok = mok && (tp.full || (p < tp.limit && !(par && ring == p)));
 #pragma unroll
-  for (int s = 0; s < CH; ++s) {
-    const int l = lc + s;
-    if (!FAST && l > L) break;
-    const bool odd = (s & 1) != 0;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      double c;
-      if (FAST) {
-        c = fma(gv[s] * G.z[j], G.a1[j], -G.a0[j]);
-        G.a0[j] = G.a1[j];
-        G.a1[j] = c;
-      } else {
-        c = grp_event_step<R>(G, j, a, m, base, lane, l, gv[s]);
+        for (int c = 0; c < C4; ++c) {
+          const double D = D4[t][rb][c], o = dpp<kDppXor2, 0xf>(0.0, D);
+          double* ob = reinterpret_cast<double*>(phase + (int64_t)leg_map(a, min(cslot[c], ns - 1)) * pstride);
+          if (ok && cslot[c] < ns) ob[(int64_t)ring * rstep + 2 * m + cs] = fma(wo, o, wd * D);
+        }
       }
-      const double w = SQ ? c * c : c;
+    } else {
+      // Four or more maps write most of the phase array's bytes per unit of
+      // work: the block's four m of a ring are put together in LDS and leave as
+      // 64 contiguous bytes instead of four 16-byte pieces (Nside 256 / L 512,
+      // 42 maps: see the figures at launch_leg_synth).
+      double* xs = reinterpret_cast<double*>(qsh);  // [row 16][N, S][map][wave][cos, sin]
+      static_assert(16 * 2 * NMW * 4 <= 4 * 4 * kQRowSyn, "a row block of every map fits the tiles' LDS");
 #pragma unroll
-      for (int k = 0; k < NM; ++k) {
-        const double hc = (SQ || !odd) ? E[j][k][0] : O[j][k][0];
-        const double hs = (SQ || !odd) ? E[j][k][1] : O[j][k][1];
-        if (FAST && j == 0) {
-          P[s][k][0] = w * hc;
-          P[s][k][1] = HAS_S ? w * hs : 0.0;
-        } else {
-          P[s][k][0] = fma(w, hc, P[s][k][0]);
-          if (HAS_S) P[s][k][1] = fma(w, hs, P[s][k][1]);
+      for (int rb = 0; rb < 4; ++rb) {
+        __syncthreads();
+        auto put = [&](int row, int ms, double D) {
+          const double cz = cm * zt[16 * rb + row];
+          const double o = dpp<kDppXor2, 0xf>(0.0, D);
+          xs[(((row * 2 + par) * NMW + ms) * 4 + wave) * 2 + cs] = fma(par ? cm : cz, o, (par ? -cz : cm) * D);
+        };
+#pragma unroll
+        for (int q = 0; q < 4; ++q)  // D: row kq + 4 q, column t % 16
+#pragma unroll
+          for (int g = 0; g < C16; ++g) put(kq + 4 * q, 4 * g + ((lane >> 2) & 3), D16[t][rb][g][q]);
+#pragma unroll
+        for (int c = 0; c < C4; ++c)  // D: block (t / 4) % 4, row t / 16 of it, column t % 4
+          put(4 * ((lane >> 2) & 3) + kq, 4 * C16 + c, D4[t][rb][c]);
+        __syncthreads();
+        const int mo = mw - wave + (threadIdx.x & 3);
+        for (int e = threadIdx.x >> 2; e < 32 * NMW; e += 64) {
+          const int ms = e % NMW, side = (e / NMW) & 1, row = e / (2 * NMW);
+          const int p = tp.p0 + 16 * rb + row, ring = side ? a.nring - 1 - p : p;
+          if (mo > L || map0 + ms >= ns || p >= tp.limit || (side && ring == p)) continue;
+          phase[(int64_t)leg_map(a, map0 + ms) * pstride + (int64_t)ring * (L + 1) + mo] =
+              qsh[e * 4 + (threadIdx.x & 3)];
         }
       }
     }
   }
 }
 
-template <int NM, int R, bool SQ, bool HAS_S>
-__device__ __forceinline__ void adjoint_wave(const LegArgs& a, int m, int tile, int lane, int nmaps, int map0,
-                                             const double2* __restrict__ phase, int64_t pstride,
-                                             double* __restrict__ vpart, int64_t vstride, int64_t tstride,
-                                             double* __restrict__ wb) {
-  constexpr int CH = AdjCfg<NM>::CH;
-  constexpr int NOUT = AdjCfg<NM>::NOUT;
-  static_assert(NOUT == 16, "wave reduction assumes 16 outputs per chunk");
-  static_assert(CH % 2 == 0, "chunks keep the parity of their first step");
-  const int L = a.lmax;
-  const int base = tile * 64 * R;
-  cdouble* gb = as_const(a.g + tri(L, m) - m);
-  Grp<R> G;
-  grp_init<R>(G, a, m, base, lane);
-  double E[R][NM][2], O[R][NM][2];
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const int p = base + 64 * j + lane;
-    const bool valid = p < a.npairs;
-    const int pc = valid ? p : a.npairs - 1;
-    const int rs = a.nring - 1 - pc;
-#pragma unroll
-    for (int k = 0; k < NM; ++k) {
-      const double2* ph = phase + (int64_t)leg_map(a, min(map0 + k, nmaps - 1)) * pstride;
-      const double2 hn = valid ? ph[(int64_t)pc * (L + 1) + m] : make_double2(0.0, 0.0);
-      const double2 hs = (valid && rs != pc) ? ph[(int64_t)rs * (L + 1) + m] : make_double2(0.0, 0.0);
-      if (valid && rs == pc) {
-        // equator ring: its own pair, lambda(z) H for both parities
-        E[j][k][0] = hn.x; E[j][k][1] = hn.y;
-        O[j][k][0] = SQ ? 0.0 : hn.x; O[j][k][1] = SQ ? 0.0 : hn.y;
-      } else {
-        E[j][k][0] = hn.x + hs.x; E[j][k][1] = hn.y + hs.y;
-        O[j][k][0] = hn.x - hs.x; O[j][k][1] = hn.y - hs.y;
-      }
-    }
-  }
-  const int nsl = L - m + 1;
-  double* const vbase = vpart + (int64_t)tile * tstride + moff(L, m);
-  // first evaluated l of any group, moved down to the parity of m (the step
-  // before a start produces zeros)
-  int l0 = G.lw[R - 1];
-  if (l0 < m) l0 = m;
-  if (l0 > L + 1) l0 = L + 1;
-  l0 -= (l0 - m) & 1;
-  // zero-fill this tile's output below the first evaluated l
-  for (int i = lane; i < (l0 - m) * NM * 2; i += 64) {
-    const int nl = l0 - m;
-    const int ll = i % nl, rest = i / nl, cs = rest & 1, k = rest >> 1;
-    if ((cs == 1 && !HAS_S) || map0 + k >= nmaps) continue;
-    vbase[(int64_t)leg_map(a, map0 + k) * vstride + cs * nsl + ll] = 0.0;
-  }
-  for (int lc = l0; lc <= L; lc += CH) {
-    const int lend = lc + CH - 1;
-    int ne = G.nx[0];
-#pragma unroll
-    for (int j = 1; j < R; ++j) ne = min(ne, G.nx[j]);
-    const bool fast = ne > lend && lend <= L;
-    // g of m is followed by g of m + 1 (and the table by 8 zeros), so the CH
-    // values from lc are always in bounds; those past L go unused
-    double gv[CH];
-    cdouble* gp = gb + __builtin_amdgcn_readfirstlane(lc);
-#pragma unroll
-    for (int s = 0; s < CH; ++s) gv[s] = gp[s];
-    double P[CH][NM][2];
-    if (fast) {
-      adj_chunk<NM, R, true, SQ, HAS_S>(G, E, O, gv, a, m, base, lane, lc, L, P);
-    } else {
-#pragma unroll
-      for (int s = 0; s < CH; ++s)
-#pragma unroll
-        for (int k = 0; k < NM; ++k) P[s][k][0] = P[s][k][1] = 0.0;
-      adj_chunk<NM, R, false, SQ, HAS_S>(G, E, O, gv, a, m, base, lane, lc, L, P);
-    }
-    // wave-private reduction of the 16 outputs u = (s NM + k) 2 + cs.  A
-    // lane-swap step first sums lanes t and t + 32 (outputs u < 8 stay in the
-    // lower half, u + 8 in the upper), so the LDS block wb[16][kRedStride]
-    // holds 32 partials per output; four lanes then sum 8 columns each (the
-    // column groups of lanes t and t ^ 16 are 16 apart: no bank conflicts)
-    // and two more swap steps finish.
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int v = u + 8;
-      const double h = fold32(P[u / (NM * 2)][(u >> 1) % NM][u & 1], P[v / (NM * 2)][(v >> 1) % NM][v & 1]);
-      wb[(u + 8 * (lane >> 5)) * kRedStride + (lane & 31)] = h;
-    }
-    __builtin_amdgcn_wave_barrier();
-    const int o = lane & 15, sub = lane >> 4;
-    const double* wr = wb + o * kRedStride + 8 * (((sub & 1) << 1) | (sub >> 1));
-    double acc = wr[0];
-#pragma unroll
-    for (int i = 1; i < 8; ++i) acc += wr[i];
-    acc = add_xor16(acc);
-    acc = add_xor32(acc);
-    __builtin_amdgcn_wave_barrier();
-    if (sub == 0) {
-      const int s = o / (NM * 2), k = (o >> 1) % NM, cs = o & 1;
-      const int l = lc + s;
-      if (l <= L && map0 + k < nmaps && (HAS_S || cs == 0))
-        vbase[(int64_t)leg_map(a, map0 + k) * vstride + cs * nsl + (l - m)] = acc;
-    }
-  }
-}
-
-template <int NM, int R, bool SQ>
-__global__ __launch_bounds__(256) void k_leg_adjoint(LegArgs a, int nmaps, const double2* __restrict__ phase,
-                                                     int64_t pstride, double* __restrict__ vpart,
-                                                     int64_t vstride, int64_t tstride, int ntiles) {
-  __shared__ double wbuf[4][AdjCfg<NM>::NOUT * kRedStride];
-  int mb, tile;
-  block_coords(ntiles, mb, tile);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int m = mb * 4 + wave;
-  if (m > a.lmax) return;
-  const int lane = threadIdx.x & 63;
-  const int map0 = blockIdx.y * NM;
-  const int ns = leg_nslots(a, nmaps);
-  if (!leg_any(a, map0, NM, ns)) return;
-  if (m == 0)
-    adjoint_wave<NM, R, SQ, false>(a, m, tile, lane, ns, map0, phase, pstride, vpart, vstride, tstride, wbuf[wave]);
-  else
-    adjoint_wave<NM, R, SQ, true>(a, m, tile, lane, ns, map0, phase, pstride, vpart, vstride, tstride, wbuf[wave]);
-}
-
-// -------------------------------------------------------- adjoint, MFMA
-// v_par[l][col] = sum_p lambda_lm(p) H_par(p)[col] as a dense product: rows =
-// 16 values of l of one parity, K = ring pairs, N = 16 columns (8 maps x cos,
-// sin).  One wave owns (m, T tiles of 64 ring pairs, 8 maps); lane t runs the
-// recurrences of pair t of each tile and, tile after tile, writes each chunk
-// of 32 steps [lb, lb + 32) (lb - m even) to wave-private LDS tiles lamE /
-// lamO [64 pairs][16 steps of one parity]; K-block kb (pairs 4 kb .. 4 kb + 3)
-// then feeds the MFMA with A lane (i, k) = lam_par[4 kb + k][i] and B lane
-// (j, k) = H_par(4 kb + k)[j] (held in registers: T tiles x 16 K-blocks x
-// E/O).  The T tiles accumulate into the same 16 x 16 results, the wave's
-// partial v for 32 values of l: one partial per T tiles, T times less
-// partial-sum traffic to and from HBM than one per tile.
-template <int T>
-__global__ __launch_bounds__(256) void k_leg_adjoint_mfma(LegArgs a, int nmaps, const double2* __restrict__ phase,
-                                                          int64_t pstride, double* __restrict__ vpart,
-                                                          int64_t vstride, int64_t tstride, int ntg) {
-  // pair-major tiles per parity, lamE[pair][i] = lambda at l = lb + 2 i (O:
-  // + 1), rows of 17 doubles: a lane group's A reads (16 consecutive i) and
-  // the per-step writes (consecutive pairs, stride 17) are both conflict-free
-  constexpr int RS = 17;
-  __shared__ double lamsh[4][2 * 64 * RS];
+template <int C16, int C4, int T>
+__global__ __launch_bounds__(256) void k_leg_syn(LegArgs a, int nmaps, const double* __restrict__ u,
+                                                 int64_t ustride, double2* __restrict__ phase,
+                                                 int64_t pstride, int ntg) {
+  constexpr int NMW = 4 * C16 + C4;
+  __shared__ double2 qsh[4 * 4 * kQRowSyn];
   int mb, tg;
   block_coords(ntg, mb, tg);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = mb * 4 + wave;
-  const int L = a.lmax;
-  if (m > L) return;
-  const int mg = blockIdx.y;
+  if (mb * 4 > a.lmax) return;  // whole block
+  const int map0 = blockIdx.y * NMW;
   const int ns = leg_nslots(a, nmaps);
-  if (!leg_any(a, mg * 8, 8, ns)) return;
-  double* lamE = lamsh[wave];
-  double* lamO = lamE + 64 * RS;
-  const int lane = threadIdx.x & 63;
-  const int i16 = lane & 15, kq = lane >> 4;
-  // this lane's column: map mg * 8 + j / 2, part j & 1
-  const int j = i16;
-  const int slot = mg * 8 + (j >> 1), cs = j & 1;
-  const bool sok = slot < ns;
-  const int map = sok ? leg_map(a, slot) : 0;
-  const bool colok = sok && !(m == 0 && cs == 1);
-  double z[T], a0[T], a1[T];
-  double2 st[T];
-  int ls[T], nx[T];
-  // B operands: H_E, H_O of pair (tg T + t) 64 + 4 kb + kq in column j
-  double HE[T][16], HO[T][16];
-  int lfirst = INT_MAX;
+  if (!leg_any(a, map0, NMW, ns)) return;
+  const TileRange tr = tile_range<T>(a, tg);
+  if (tr.polar)
+    syn_wave<C16, C4, T, true>(a, m, wave, tr.t0, tr.tend, map0, ns, u, ustride, phase, pstride, qsh);
+  else
+    syn_wave<C16, C4, T, false>(a, m, wave, tr.t0, tr.tend, map0, ns, u, ustride, phase, pstride, qsh);
+}
+
+// --------------------------------------------------------------- adjoint
+// W[k][col] = sum_p q_k[p] H[p][col] on the matrix cores (rows = k, K = ring
+// pairs), with H_E = H_N + H_S and H_O = z (H_N - H_S) held in registers for
+// the wave's T tiles of 64 ring pairs, then v_{m+2k} = eps_{l+1} W^E_k + eps_l
+// W^E_{k-1} and v_{m+2k+1} = W^O_k: one partial v per T tiles (fixed order, no
+// atomics).  T sets the partial sums' traffic (one (L+1)^2 vector per map and T
+// tiles, written here and read by the tile sum).
+
+// Zero partial below the first evaluated k and the row pointers of a column.
+struct AdjOut {
+  double* vb;  // index l - m of the lane's part
+  bool ok;
+};
+__device__ __forceinline__ AdjOut adj_out(const LegArgs& a, double* vpart, int64_t vstride, int64_t tstride, int tg,
+                                          int m, int slot, int ns, int cs) {
+  AdjOut o;
+  const int L = a.lmax;
+  o.ok = slot < ns && !(m == 0 && cs);
+  const int mp = leg_map(a, min(slot, ns - 1));
+  o.vb = vpart + (int64_t)tg * tstride + (int64_t)mp * vstride + moff(L, m) + (cs && m > 0 ? L - m + 1 : 0);
+  return o;
+}
+// H of N ring pairs i0 + 16 (j / IN) + j % IN of a tile in a lane's column (ph:
+// the map's phase array at (ring 0, m, part); par: 0 E, 1 O; in: the tile exists)
+template <int N, int IN>
+__device__ __forceinline__ void adj_h(const LegArgs& a, const double* ph, int tile, bool polar, bool in, int i0, int par,
+                                      double (&H)[N]) {
+  const TilePairs tp = tile_pairs(a, tile, polar);
+  const int64_t rstep = 2 * (int64_t)(a.lmax + 1);
+  const double* z = a.zs + tile * 64 + i0;
+  const double sg = par ? -1.0 : 1.0;
+  if (in && tp.full) {
+    const double* pn = ph + (int64_t)(tp.p0 + i0) * rstep;
+    const double* ps = ph + (int64_t)(a.nring - 1 - tp.p0 - i0) * rstep;
+    double hn[N], hs[N], zv[N];
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const int tile = tg * T + t;
-    const int p = tile * 64 + lane;
-    const bool valid = p < a.npairs;
-    z[t] = valid ? a.zpair[p] : 0.0;
-    ls[t] = valid ? a.ls[(size_t)m * a.npairs + p] : INT_MAX;
-    st[t] = valid ? a.ms[(size_t)m * a.npairs + p] : make_double2(0.0, 0.0);
-    a0[t] = a1[t] = 0.0;
-    nx[t] = wave_min(ls[t]);
-    lfirst = min(lfirst, nx[t]);
-    const double* ph = reinterpret_cast<const double*>(phase + (int64_t)(colok ? map : 0) * pstride);
-#pragma unroll
-    for (int kb = 0; kb < 16; ++kb) {
-      const int pp = tile * 64 + 4 * kb + kq;
-      double hn = 0.0, hs = 0.0;
-      const bool ok = colok && pp < a.npairs;
-      const int rs = a.nring - 1 - pp;
-      if (ok) {
-        hn = ph[2 * ((int64_t)pp * (L + 1) + m) + cs];
-        if (rs != pp) hs = ph[2 * ((int64_t)rs * (L + 1) + m) + cs];
-      }
-      // the equator ring is its own pair: lambda(z) H for both parities
-      HE[t][kb] = (ok && rs == pp) ? hn : hn + hs;
-      HO[t][kb] = (ok && rs == pp) ? hn : hn - hs;
-    }
-  }
-  const int nsl = L - m + 1;
-  double* const vb = vpart + (int64_t)tg * tstride + (int64_t)(colok ? map : 0) * vstride + moff(L, m) + cs * nsl - m;
-  const int l0 = lfirst <= L ? lfirst - ((lfirst - m) & 1) : L + 1;
-  // zero partial below the first evaluated l
-  if (colok)
-    for (int l = m + kq; l < l0; l += 4) vb[l] = 0.0;
-  cdouble* gb = as_const(a.g + tri(L, m) - m);  // 8 zeros follow the table
-  for (int lb = l0; lb <= L; lb += 32) {
-    lb = __builtin_amdgcn_readfirstlane(lb);
-    // two independent accumulator pairs (even / odd K-blocks)
-    v4d DE2[2], DO2[2];
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
-      DE2[v] = v4d{0.0, 0.0, 0.0, 0.0};
-      DO2[v] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < N; ++j) {
+      hn[j] = *pn;
+      hs[j] = *ps;
+      zv[j] = z[16 * (j / IN) + j % IN];
+      const int64_t step = (j % IN == IN - 1 ? 17 - IN : 1) * rstep;
+      pn += step;
+      ps -= step;
     }
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const bool fast = nx[t] >= lb + 32;
+    for (int j = 0; j < N; ++j) H[j] = fma(sg, hs[j], hn[j]) * (par ? zv[j] : 1.0);
+  } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        // groups of 8 steps that start past L are not loaded (their rows are
-        // never stored)
-        double gv[8];
-        cdouble* gp = gb + lb + 8 * q;
-        const bool in = lb + 8 * q <= L;
-#pragma unroll
-        for (int s2 = 0; s2 < 8; ++s2) gv[s2] = in ? gp[s2] : 0.0;
-        if (fast) {
-#pragma unroll
-          for (int s2 = 0; s2 < 8; ++s2) {
-            const double cc = fma(gv[s2] * z[t], a1[t], -a0[t]);
-            a0[t] = a1[t];
-            a1[t] = cc;
-            ((s2 & 1) ? lamO : lamE)[lane * RS + 4 * q + (s2 >> 1)] = cc;
-          }
-        } else {
-#pragma unroll
-          for (int s2 = 0; s2 < 8; ++s2) {
-            double cc = fma(gv[s2] * z[t], a1[t], -a0[t]);
-            double pv = a1[t];
-            if (ls[t] == lb + 8 * q + s2) {
-              cc = st[t].y;
-              pv = st[t].x;
-            }
-            a0[t] = pv;
-            a1[t] = cc;
-            ((s2 & 1) ? lamO : lamE)[lane * RS + 4 * q + (s2 >> 1)] = cc;
-          }
-        }
-      }
-      if (!fast) nx[t] = wave_min(ls[t] >= lb + 32 ? ls[t] : INT_MAX);
-      lds_wave_sync();
-#pragma unroll
-      for (int kb = 0; kb < 16; ++kb) {
-        const double aE = lamE[(4 * kb + kq) * RS + i16];
-        const double aO = lamO[(4 * kb + kq) * RS + i16];
-        DE2[kb & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(aE, HE[t][kb], DE2[kb & 1], 0, 0, 0);
-        DO2[kb & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(aO, HO[t][kb], DO2[kb & 1], 0, 0, 0);
-      }
-      // the next tile's (or chunk's) steps overwrite lam only after these reads
-      lds_wave_sync();
-    }
-    const v4d DE = DE2[0] + DE2[1];
-    const v4d DO = DO2[0] + DO2[1];
-    // D[row = kq + 4 r][col = j]: l = lb + 2 row (E), lb + 2 row + 1 (O)
-    if (colok) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int lE = lb + 2 * (kq + 4 * r);
-        if (lE <= L) vb[lE] = DE[r];
-        if (lE + 1 <= L) vb[lE + 1] = DO[r];
+    for (int j = 0; j < N; ++j) {
+      const int i = 16 * (j / IN) + j % IN;
+      const int p = tp.p0 + i0 + i, rs = a.nring - 1 - p;
+      H[j] = 0.0;
+      if (in && p < tp.limit) {
+        const double hn = ph[(int64_t)p * rstep];
+        const double hs = rs != p ? ph[(int64_t)rs * rstep] : 0.0;  // the equator ring is its own pair
+        H[j] = fma(sg, hs, hn) * (par ? z[i] : 1.0);
       }
     }
   }
 }
 
-// -------------------------------------------------------- hat scaling
-// out[map][i] = c_m f_lm (or f_lm^2) * sum_t in[t][map][i]
-__global__ void k_hat_scale(const double* __restrict__ f, int L, int nmaps,
-                            const double* __restrict__ in, int64_t istride, int ntiles,
-                            int64_t tstride, double* __restrict__ out, int64_t ostride, int square) {
-  const int m = blockIdx.y;
-  const int map = blockIdx.z;
-  const int nsl = L - m + 1;
-  const int np = (m == 0) ? 1 : 2;
-  const int64_t mo = moff(L, m);
-  const double cm = (m == 0 || square) ? 1.0 : 1.4142135623730951;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nsl * np; i += gridDim.x * blockDim.x) {
-    const int ll = i % nsl;
-    const double fv = f[tri(L, m) + ll];
-    const double sc = square ? fv * fv : cm * fv;
-    double acc = 0.0;
-    for (int t = 0; t < ntiles; ++t) acc += in[(int64_t)t * tstride + (int64_t)map * istride + mo + i];
-    out[(int64_t)map * ostride + mo + i] = sc * acc;
+// One to three maps: v_mfma_f64_4x4x4 with its four blocks on different ring
+// pairs, so a map's H takes 8 registers per tile.  Lane t =
+// (j = t % 4: column (E cos, E sin, O cos, O sin), b = (t / 4) % 4, i = t / 16);
+// operand k index t / 16: pair 16 s + b + 4 (t / 16) of H register s; A rows:
+// k = k0 + 8 x + 2 (t % 4) + {0, 1}.  The blocks are summed once per 16 steps.
+template <int NM, int T, bool POLAR>
+__device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t0, int tend, int map0, int ns,
+                                          const double2* __restrict__ phase, int64_t pstride,
+                                          double* __restrict__ vpart, int64_t vstride, int64_t tstride, double2* qt) {
+  const int L = a.lmax;
+  const int lane = threadIdx.x & 63;
+  const int b = (lane >> 2) & 3, b0 = b & 1, b1 = b >> 1, hi = lane >> 4;
+  const int par = (lane >> 1) & 1, cs = lane & 1;
+  const int n = L - m, K = n / 2 + 1;
+  RecState r[T];
+  double H[T][NM][4];
+  AdjOut out[NM];
+  int kst = INT_MAX;
+#pragma unroll
+  for (int c = 0; c < NM; ++c) out[c] = adj_out(a, vpart, vstride, tstride, tg, m, map0 + c, ns, cs);
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int s0 = (t0 + t) * 64;
+    const bool in = t0 + t < tend;
+    rec_init(r[t], a, m, s0 + lane, in);
+    kst = min(kst, r[t].first);
+#pragma unroll
+    for (int c = 0; c < NM; ++c) {
+      const double* ph =
+          reinterpret_cast<const double*>(phase + (int64_t)leg_map(a, min(map0 + c, ns - 1)) * pstride) + 2 * m + cs;
+      adj_h<4, 1>(a, ph, t0 + t, POLAR, in, b + 4 * hi, par, H[t][c]);
+    }
+  }
+  // zero partial below the first evaluated k (all of it if no lane starts)
+  const int zend = min(2 * min(kst, K), n + 1);
+#pragma unroll
+  for (int c = 0; c < NM; ++c)
+    if (out[c].ok && par == 0)
+      for (int x = lane >> 2; x < zend; x += 16) out[c].vb[x] = 0.0;
+  cdouble* cb = as_const((POLAR ? a.bp : a.be) + krow(L, m));
+  cdouble* cg = as_const(a.gi + krow(L, m));
+  const double* er = a.ep + 4 + erow(L, m);
+  const double cm = m == 0 ? 1.0 : 1.4142135623730951;
+  const int kl = 8 * b1 + 2 * (lane >> 4) + b0;  // this lane's k - k0 after the block sums
+  // lane of W_{k-1}: the lane of k - 1, whose carry for k = k0 is the last block's k0 + 15
+  const int kp = (kl + 15) & 15;
+  const int psrc = (lane & 3) + 4 * (2 * (kp >> 3) + (kp & 1)) + 16 * ((kp & 7) >> 1);
+  double Wp[NM];
+#pragma unroll
+  for (int c = 0; c < NM; ++c) Wp[c] = 0.0;
+  for (int k0 = kst; k0 < K; k0 += 16) {
+    k0 = __builtin_amdgcn_readfirstlane(k0);
+    const RecCoef<16> C = rec_coef<16>(cb, cg, k0);
+    const double ea = par ? 1.0 : er[2 * (k0 + kl) + 1];
+    const double eb = par ? 0.0 : er[2 * (k0 + kl)];
+    double D[4][NM];
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+#pragma unroll
+      for (int c = 0; c < NM; ++c) D[x][c] = 0.0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      if (r[t].first >= k0 + 16) continue;
+      const int slot = (t0 + t) * 64 + lane;
+      rec8<POLAR, 0>(r[t], C, a, m, slot, k0,
+                     [&](int i, double qe, double qo) { qt[i * kQRowAdj4 + lane] = make_double2(qe, qo); });
+      rec8<POLAR, 8>(r[t], C, a, m, slot, k0 + 8,
+                     [&](int i, double qe, double qo) { qt[(4 + i) * kQRowAdj4 + lane] = make_double2(qe, qo); });
+      wave_fence();
+      double2 A[2][4];
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) A[x][s] = qt[(4 * x + (lane & 3)) * kQRowAdj4 + 16 * s + b + 4 * hi];
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int c = 0; c < NM; ++c) {
+            D[2 * x][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[x][s].x, H[t][c][s], D[2 * x][c], 0, 0, 0);
+            D[2 * x + 1][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[x][s].y, H[t][c][s], D[2 * x + 1][c], 0, 0, 0);
+          }
+      wave_fence();
+    }
+#pragma unroll
+    for (int c = 0; c < NM; ++c) {
+      // sum over the blocks, lane block b keeping D[b] (x = b1, odd k = b0)
+      const double r0 = (b1 ? D[2][c] : D[0][c]) + dpp<kDppRor8, 0xf>(0.0, b1 ? D[0][c] : D[2][c]);
+      const double r1 = (b1 ? D[3][c] : D[1][c]) + dpp<kDppRor8, 0xf>(0.0, b1 ? D[1][c] : D[3][c]);
+      const double y = b0 ? r0 : r1;
+      const double W = (b0 ? r1 : r0) + dpp<kDppRor12, 0x5>(dpp<kDppRor4, 0xa>(0.0, y), y);
+      const double Wm = lane_get(kl == 15 ? Wp[c] : W, psrc);
+      Wp[c] = W;
+      const int x = 2 * (k0 + kl) + par;
+      if (out[c].ok && x <= n) out[c].vb[x] = cm * fma(eb, Wm, ea * W);
+    }
+  }
+}
+
+template <int NM, int T>
+__global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0, const double2* __restrict__ phase,
+                                                  int64_t pstride, double* __restrict__ vpart, int64_t vstride,
+                                                  int64_t tstride, int ntg) {
+  __shared__ double2 qsh[4][8 * kQRowAdj4];
+  int mb, tg;
+  block_coords(ntg, mb, tg);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = mb * 4 + wave;
+  if (m > a.lmax) return;
+  const int ns = leg_nslots(a, nmaps);
+  if (!leg_any(a, map0, NM, ns)) return;
+  const TileRange tr = tile_range<T>(a, tg);
+  if (tr.polar)
+    adj4_wave<NM, T, true>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+  else
+    adj4_wave<NM, T, false>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+}
+
+// Groups of four maps: v_mfma_f64_16x16x4, column j = t % 16 = 4 map + 2 (E, O)
+// + (cos, sin); H takes 32 registers per tile.  K-block 4 s + b holds the ring
+// pairs that block b of k_leg_adj4 takes from H register s, and the four
+// accumulators b are added as its blocks are: a map's result does not depend
+// on how many maps run beside it.
+template <int T, bool POLAR>
+__device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int t0, int tend, int map0, int ns,
+                                           const double2* __restrict__ phase, int64_t pstride,
+                                           double* __restrict__ vpart, int64_t vstride, int64_t tstride, double2* qt) {
+  const int L = a.lmax;
+  const double* qd = reinterpret_cast<const double*>(qt);
+  const int lane = threadIdx.x & 63;
+  const int i16 = lane & 15, kq = lane >> 4;
+  const int par = (lane >> 1) & 1, cs = lane & 1;
+  const int n = L - m, K = n / 2 + 1;
+  const int slot = map0 + ((lane >> 2) & 3);
+  const AdjOut out = adj_out(a, vpart, vstride, tstride, tg, m, slot, ns, cs);
+  RecState r[T];
+  double H[T][16];
+  int kst = INT_MAX;
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int s0 = (t0 + t) * 64;
+    const bool in = t0 + t < tend;
+    rec_init(r[t], a, m, s0 + lane, in);
+    kst = min(kst, r[t].first);
+    const double* ph =
+        reinterpret_cast<const double*>(phase + (int64_t)leg_map(a, min(slot, ns - 1)) * pstride) + 2 * m + cs;
+    adj_h<16, 4>(a, ph, t0 + t, POLAR, in, 4 * kq, par, H[t]);
+  }
+  const int zend = min(2 * min(kst, K), n + 1);
+  if (out.ok && par == 0)
+    for (int x = kq; x < zend; x += 4) out.vb[x] = 0.0;
+  cdouble* cb = as_const((POLAR ? a.bp : a.be) + krow(L, m));
+  cdouble* cg = as_const(a.gi + krow(L, m));
+  const double* er = a.ep + 4 + erow(L, m);
+  const double cm = m == 0 ? 1.0 : 1.4142135623730951;
+  double Wp = 0.0;  // D[3] of the last block: its row 15 sits in lanes 48..63
+  for (int k0 = kst; k0 < K; k0 += 16) {
+    k0 = __builtin_amdgcn_readfirstlane(k0);
+    const RecCoef<16> C = rec_coef<16>(cb, cg, k0);
+    v4d D[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) D[b] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      if (r[t].first >= k0 + 16) continue;
+      const int sl = (t0 + t) * 64 + lane;
+      rec8<POLAR, 0>(r[t], C, a, m, sl, k0,
+                     [&](int i, double qe, double qo) { qt[i * kQRowAdj16 + lane] = make_double2(qe, qo); });
+      rec8<POLAR, 8>(r[t], C, a, m, sl, k0 + 8,
+                     [&](int i, double qe, double qo) { qt[(4 + i) * kQRowAdj16 + lane] = make_double2(qe, qo); });
+      wave_fence();
+      double A[16];
+#pragma unroll
+      for (int kb = 0; kb < 16; ++kb) A[kb] = qd[(i16 >> 1) * (2 * kQRowAdj16) + 2 * (16 * (kb >> 2) + (kb & 3) + 4 * kq) + (i16 & 1)];
+#pragma unroll
+      for (int kb = 0; kb < 16; ++kb)
+        D[kb & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[kb], H[t][kb], D[kb & 3], 0, 0, 0);
+      wave_fence();
+    }
+    // D: row (k - k0) = kq + 4 q, column t % 16
+    const v4d W = (D[0] + D[2]) + (D[1] + D[3]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      // W_{k-1}: the lane group below, or row 4 q - 1 from the last group
+      const double prev = q == 0 ? Wp : W[q > 0 ? q - 1 : 0];
+      const double Wm = lane_get(kq == 3 ? prev : W[q], (lane + 48) & 63);
+      const int x = 2 * (k0 + kq + 4 * q);
+      const double ea = par ? 1.0 : er[x + 1], eb = par ? 0.0 : er[x];
+      if (out.ok && x + par <= n) out.vb[x + par] = cm * fma(eb, Wm, ea * W[q]);
+    }
+    Wp = W[3];
+  }
+}
+
+template <int T>
+__global__ __launch_bounds__(256, 2) void k_leg_adj16(LegArgs a, int nmaps, const double2* __restrict__ phase,
+                                                      int64_t pstride, double* __restrict__ vpart, int64_t vstride,
+                                                      int64_t tstride, int ntg) {
+  __shared__ double2 qsh[4][8 * kQRowAdj16];
+  int mb, tg;
+  block_coords(ntg, mb, tg);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = mb * 4 + wave;
+  if (m > a.lmax) return;
+  const int map0 = blockIdx.y * 4;
+  const int ns = leg_nslots(a, nmaps);
+  if (!leg_any(a, map0, 4, ns)) return;
+  const TileRange tr = tile_range<T>(a, tg);
+  if (tr.polar)
+    adj16_wave<T, true>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+  else
+    adj16_wave<T, false>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+}
+
+// Squared functions (M_diag setup, Sect. 5): v_lm = sum_r lambda_lm^2 G_m(r) of
+// one map, one wave per (m, 64 ring pairs).  Each four steps (eight l, 16
+// outputs) are reduced over the lanes through a wave-private LDS block in a
+// fixed order: four lanes sum 16 columns each, then two lane swaps finish.
+constexpr int kRedRow = 65;
+__device__ __forceinline__ double add_xor16(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
+  const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  const double x = __longlong_as_double((long long)(((uint64_t)b[0] << 32) | a[0]));
+  const double y = __longlong_as_double((long long)(((uint64_t)b[1] << 32) | a[1]));
+  return x + y;
+}
+__global__ __launch_bounds__(256) void k_leg_adj_sq(LegArgs a, const double2* __restrict__ phase,
+                                                    double* __restrict__ vpart, int64_t tstride, int ntg) {
+  __shared__ double red[4][16 * kRedRow];
+  int mb, tile;
+  block_coords(ntg, mb, tile);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = mb * 4 + wave;
+  const int L = a.lmax;
+  if (m > L) return;
+  double* wb = red[wave];
+  const int lane = threadIdx.x & 63;
+  const int n = L - m, K = n / 2 + 1, slot = tile * 64 + lane;
+  RecState r;
+  rec_init(r, a, m, slot, true);
+  const double* ph = reinterpret_cast<const double*>(phase) + 2 * m;
+  double G[2][1];
+  adj_h<1, 1>(a, ph, tile, tile < a.pol_tiles, true, lane, 0, G[0]);
+  adj_h<1, 1>(a, ph + 1, tile, tile < a.pol_tiles, true, lane, 0, G[1]);
+  const double z = a.zs[slot];
+  double* vb = vpart + (int64_t)tile * tstride + moff(L, m);
+  const int np = m == 0 ? 1 : 2;
+  const int zend = min(2 * min(r.first, K), n + 1);
+  for (int x = lane; x < zend * np; x += 64) vb[x < zend ? x : n + 1 + x - zend] = 0.0;
+  const bool polar = tile < a.pol_tiles;
+  cdouble* cb = as_const((polar ? a.bp : a.be) + krow(L, m));
+  cdouble* cg = as_const(a.gi + krow(L, m));
+  cdouble* er = as_const(a.ep + 4 + erow(L, m));
+  double qm = 0.0;  // q_{k-1}
+  for (int k0 = r.first; k0 < K; k0 += 8) {
+    k0 = __builtin_amdgcn_readfirstlane(k0);
+    const RecCoef<8> C = rec_coef<8>(cb, cg, k0);
+    double q[8];
+    auto put = [&](int i, double qe, double qo) {
+      q[2 * i] = qe;
+      q[2 * i + 1] = qo;
+    };
+    if (polar)
+      rec8<true, 0>(r, C, a, m, slot, k0, put);
+    else
+      rec8<false, 0>(r, C, a, m, slot, k0, put);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int x = 2 * (k0 + 4 * h + i);
+        const double le = fma(er[x], qm, er[x + 1] * q[4 * h + i]);
+        const double lo = z * q[4 * h + i];
+        qm = q[4 * h + i];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          wb[(4 * i + c) * kRedRow + lane] = le * le * G[c][0];
+          wb[(4 * i + 2 + c) * kRedRow + lane] = lo * lo * G[c][0];
+        }
+      }
+      wave_fence();
+      const int o = lane & 15, sub = lane >> 4;
+      double acc = wb[o * kRedRow + 16 * sub];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) acc += wb[o * kRedRow + 16 * sub + i];
+      acc = add_xor16(acc);
+      acc = add_xor32(acc);
+      wave_fence();
+      const int x = 2 * (k0 + 4 * h) + (o >> 1), c = o & 1;
+      if (sub == 0 && x <= n && c < np) vb[c * (n + 1) + x] = acc;
+    }
   }
 }
 
 }  // namespace
 
 // ------------------------------------------------------------ launchers
-// Default kernel choice (measured on MI355X, HEALPix Nside 64..1024):
-// matrix-core kernels from 4 maps on; vector ring-pair groups per lane R as
-// large as still leaves >= 4096 waves, up to 2 for synthesis (Nside 1024 /
-// L 2000 / 1 map: 0.68 ms vs 0.75 ms at R = 1 and R = 4) and 4 for the adjoint
-// (0.94 ms vs 1.28 ms at R = 2); two 64-pair tiles per matrix-core adjoint
-// wave under the same wave count rule.
-static int largest_r(int npairs, int L, int rmax, long want) {
-  for (int R : {4, 2, 1}) {
-    if (R > rmax) continue;
-    const long tiles = (npairs + 64L * R - 1) / (64L * R);
-    if ((long)(L + 1) * tiles >= want) return R;
+// Kernel choice: tiles of 64 ring pairs per wave.  More tiles share the operand
+// loads of the synthesis and divide the adjoint's partial sums, fewer leave
+// more waves in flight.  Measured (ms, T = 1 / 2 / 4; adjoint with its tile sum):
+//                          synthesis               adjoint
+//   Nside 256 / L 512 x1   0.030 / 0.043 / 0.058   0.047 / 0.051 / 0.065   ( 4104 waves at T = 1)
+//   Nside 512 / L 1024 x1  0.134 / 0.101 / 0.112   0.187 / 0.162 / 0.160   (16400)
+//   Nside 1024 / L 2000 x1 0.84  / 0.56  / 0.52    1.09  / 0.82  / 0.76    (64032)
+//   Nside 1024 / L 2000 x4 1.27  / 1.15            3.63  / 2.64  / 2.29
+//   Nside 256 / L 512 x42  0.346 / 0.366           1.04  / 0.89  / 0.86
+// so the rules take the largest T that leaves 8192 waves (synthesis) or 4096
+// (adjoint).  The autotuner replaces them per shape.
+static int largest_t(long tiles, int L, int tmax, long groups, long want) {
+  for (int T : {4, 2}) {
+    if (T > tmax || T >= 2 * tiles) continue;
+    if ((long)(L + 1) * ((tiles + T - 1) / T) * groups >= want) return T;
   }
   return 1;
 }
 
-// Maps per wave of the vector synthesis: all of them up to 8, else the
-// group size in {8, 6, 4} that leaves the fewest empty slots.
-static int syn_nm(int nmaps) {
-  if (nmaps <= 8) return nmaps;
-  int best = 8, waste = 1 << 30;
-  for (int c : {8, 6, 4}) {
-    const int w = ((nmaps + c - 1) / c) * c - nmaps;
-    if (w < waste) {
-      waste = w;
-      best = c;
-    }
-  }
-  return best;
-}
-
-static int syn_rmax(int nmaps) { return std::max(1, 4 / syn_nm(nmaps)); }
+// Largest T the synthesis is built for (the sums of T tiles sit in registers;
+// from five maps on two tiles leave too few waves and gain nothing).
+static int syn_tmax(int nmaps) { return nmaps == 1 ? 4 : nmaps <= 4 ? 2 : 1; }
+constexpr int kAdjTmax = 4;
 
 static LegChoice default_choice(int npairs, int L, int nmaps) {
   LegChoice c;
-  c.syn_mfma = c.adj_mfma = nmaps >= 4;
-  c.syn_r = largest_r(npairs, L, std::min(2, syn_rmax(nmaps)), 4096);
-  // the adjoint's per-chunk lane reduction wants more waves in flight: four
-  // pairs per lane only from 8192 waves (Nside 512 / L 1024, one map: two
-  // pairs per lane 0.169 ms, four 0.185 ms; Nside 1024 / L 2000: four 0.97,
-  // two 1.03 ms)
-  c.adj_r = largest_r(npairs, L, 4, 8192);
-  const long nt = (npairs + 63) / 64;
-  c.adj_t = (long)(L + 1) * ((nt + 1) / 2) * ((nmaps + 7) / 8) >= 4096 ? 2 : 1;
+  const long tiles = (npairs + 63) / 64;
+  c.syn_t = largest_t(tiles, L, syn_tmax(nmaps), 1, 8192);
+  c.adj_t = largest_t(tiles, L, kAdjTmax, std::max(1, nmaps / 4), 4096);
   return c;
 }
 
@@ -881,12 +849,9 @@ static int env_int(const char* name) {
 }
 
 static void apply_env(LegChoice& c, int nmaps) {
-  if (const int v = env_int("CRS_LEG_MFMA_MIN")) c.syn_mfma = c.adj_mfma = nmaps >= std::max(1, v);
-  if (const int v = env_int("CRS_LEG_RS"))
-    if (v == 1 || v == 2 || v == 4) c.syn_r = std::min(v, syn_rmax(nmaps));
-  if (const int v = env_int("CRS_LEG_RA"))
-    if (v == 1 || v == 2 || v == 4) c.adj_r = v;
-  if (const int v = env_int("CRS_LEG_TA")) c.adj_t = v == 2 ? 2 : 1;
+  auto pick = [](int v, int most) { return v >= 4 && most >= 4 ? 4 : v >= 2 && most >= 2 ? 2 : 1; };
+  if (const int v = env_int("CRS_LEG_TS")) c.syn_t = pick(v, syn_tmax(nmaps));
+  if (const int v = env_int("CRS_LEG_TA")) c.adj_t = pick(v, kAdjTmax);
 }
 
 static std::mutex g_tune_mu;
@@ -903,83 +868,86 @@ LegChoice leg_choice(int npairs, int L, int nmaps) {
   return c;
 }
 
-void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const double* uhat, int64_t ustride,
+// blocks of a launch over ntg tile groups: four consecutive m each, m-blocks
+// rounded up to the XCD order of block_coords
+static unsigned leg_blocks(int L, int ntg) { return (unsigned)(((L + 1 + 3) / 4 + 7) / 8 * 8 * ntg); }
+
+// tile groups of T (tile_range)
+static int tile_groups(int pol_tiles, int nslots, int T) {
+  return (pol_tiles + T - 1) / T + (nslots / 64 - pol_tiles + T - 1) / T;
+}
+
+void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const double* u, int64_t ustride,
                       double2* phase, int64_t pstride, hipStream_t s) {
-  const int L = a.lmax;
-  if (c.syn_mfma) {
-    const int ntiles = (a.npairs + 63) / 64;
-    const int nmb = (L + 1 + 3) / 4;
-    const int nmb8 = (nmb + 7) / 8 * 8;
-    dim3 grid(nmb8 * ntiles, (nmaps + 7) / 8);
-    hipLaunchKernelGGL(k_leg_synth_mfma, grid, dim3(256), 0, s, a, nmaps, uhat, ustride, phase, pstride, ntiles);
-    CRS_HIP(hipGetLastError());
-    return;
+#define CRS_SYN(G16, G4, TT)                                                                          \
+  do {                                                                                                \
+    const int ntg = tile_groups(a.pol_tiles, a.nslots, TT), per = 4 * G16 + G4;                       \
+    hipLaunchKernelGGL((k_leg_syn<G16, G4, TT>), dim3(leg_blocks(a.lmax, ntg), (nmaps + per - 1) / per), \
+                       dim3(256), 0, s, a, nmaps, u, ustride, phase, pstride, ntg);                   \
+  } while (0)
+  // up to eight maps: one wave carries exactly nmaps; more: eight per wave, the
+  // last group's second half skipped when it is empty
+  switch (std::min(nmaps, 9)) {
+    case 1: if (c.syn_t == 4) CRS_SYN(0, 1, 4); else if (c.syn_t == 2) CRS_SYN(0, 1, 2); else CRS_SYN(0, 1, 1); break;
+    case 2: if (c.syn_t == 2) CRS_SYN(0, 2, 2); else CRS_SYN(0, 2, 1); break;
+    case 3: if (c.syn_t == 2) CRS_SYN(0, 3, 2); else CRS_SYN(0, 3, 1); break;
+    case 4: if (c.syn_t == 2) CRS_SYN(1, 0, 2); else CRS_SYN(1, 0, 1); break;
+    case 5: CRS_SYN(1, 1, 1); break;
+    case 6: CRS_SYN(1, 2, 1); break;
+    default: CRS_SYN(2, 0, 1); break;
   }
-  const int nm = syn_nm(nmaps);
-  const int R = std::min(c.syn_r, syn_rmax(nmaps));
-  const int ntiles = (a.npairs + 64 * R - 1) / (64 * R);
-  const int nmb = (L + 1 + 3) / 4;
-  const int nmb8 = (nmb + 7) / 8 * 8;
-  dim3 grid(nmb8 * ntiles, (nmaps + nm - 1) / nm);
-  dim3 block(256);
-#define CRS_SYN(N, RR) \
-  if (nm == N && R == RR) { hipLaunchKernelGGL((k_leg_synth<N, RR>), grid, block, 0, s, a, nmaps, uhat, ustride, phase, pstride, ntiles); CRS_HIP(hipGetLastError()); return; }
-  CRS_SYN(1, 1) CRS_SYN(1, 2) CRS_SYN(1, 4)
-  CRS_SYN(2, 1) CRS_SYN(2, 2)
-  CRS_SYN(3, 1) CRS_SYN(4, 1) CRS_SYN(5, 1) CRS_SYN(6, 1) CRS_SYN(7, 1) CRS_SYN(8, 1)
 #undef CRS_SYN
-  throw Error{CRS_EINVAL, "no synthesis kernel variant"};
+  CRS_HIP(hipGetLastError());
 }
 
-// Vector adjoint: R is chosen first and the maps per wave follow (R * NM <= 8).
-static int adj_nm(int nmaps, int R) {
-  const int cap = 8 / R;
-  const int nm = nmaps >= 4 ? 4 : (nmaps >= 2 ? 2 : 1);
-  return std::min(nm, cap);
-}
-
-int leg_adjoint_tiles(const LegChoice& c, int npairs, bool square) {
-  if (c.adj_mfma && !square) return ((npairs + 63) / 64 + c.adj_t - 1) / c.adj_t;
-  return (npairs + 64 * c.adj_r - 1) / (64 * c.adj_r);
+int leg_adjoint_tiles(const LegChoice& c, crs_grid g, bool square) {
+  return tile_groups(g->pol_tiles, g->nslots, square ? 1 : c.adj_t);
 }
 
 void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const double2* phase, int64_t pstride,
                         double* vpart, int64_t vstride, int64_t tstride, bool square,
                         hipStream_t s) {
-  const int L = a.lmax;
-  const int ntg = leg_adjoint_tiles(c, a.npairs, square);
-  const int nmb = (L + 1 + 3) / 4;
-  const int nmb8 = (nmb + 7) / 8 * 8;
-  if (c.adj_mfma && !square) {
-    dim3 grid(nmb8 * ntg, (nmaps + 7) / 8);
-    if (c.adj_t == 2)
-      hipLaunchKernelGGL(k_leg_adjoint_mfma<2>, grid, dim3(256), 0, s, a, nmaps, phase, pstride, vpart, vstride,
-                         tstride, ntg);
-    else
-      hipLaunchKernelGGL(k_leg_adjoint_mfma<1>, grid, dim3(256), 0, s, a, nmaps, phase, pstride, vpart, vstride,
-                         tstride, ntg);
+  const int ntg = tile_groups(a.pol_tiles, a.nslots, square ? 1 : c.adj_t);
+  const unsigned nb = leg_blocks(a.lmax, ntg);
+  if (square) {
+    CRS_CHECK(nmaps == 1, CRS_EINVAL, "the squared adjoint takes one map");
+    hipLaunchKernelGGL(k_leg_adj_sq, dim3(nb), dim3(256), 0, s, a, phase, vpart, tstride, ntg);
     CRS_HIP(hipGetLastError());
     return;
   }
-  const int R = c.adj_r;
-  const int nm = adj_nm(nmaps, R);
-  dim3 grid(nmb8 * ntg, (nmaps + nm - 1) / nm);
-#define CRS_ADJ(N, RR)                                                                            \
-  if (nm == N && R == RR) {                                                                       \
-    if (square)                                                                                   \
-      hipLaunchKernelGGL((k_leg_adjoint<N, RR, true>), grid, dim3(256), 0, s, a, nmaps, phase,    \
-                         pstride, vpart, vstride, tstride, ntg);                                  \
-    else                                                                                          \
-      hipLaunchKernelGGL((k_leg_adjoint<N, RR, false>), grid, dim3(256), 0, s, a, nmaps, phase,   \
-                         pstride, vpart, vstride, tstride, ntg);                                  \
-    CRS_HIP(hipGetLastError());                                                                   \
-    return;                                                                                       \
+  // groups of four maps on the 16-column kernel; a remainder of one or two
+  // maps takes the per-map kernel where that saves columns worth a launch (up
+  // to ten maps), otherwise the last group runs partly empty.  Lists of active
+  // maps are formed on the device: their remainder is not known here.
+  int g16 = nmaps <= 3 ? 0 : nmaps / 4, rest = nmaps - 4 * g16;
+  if (g16 > 0 && rest > 0 && (rest == 3 || nmaps > 10 || a.mlist)) {
+    ++g16;
+    rest = 0;
   }
-  CRS_ADJ(1, 1) CRS_ADJ(1, 2) CRS_ADJ(1, 4)
-  CRS_ADJ(2, 1) CRS_ADJ(2, 2) CRS_ADJ(2, 4)
-  CRS_ADJ(4, 1) CRS_ADJ(4, 2)
-#undef CRS_ADJ
-  throw Error{CRS_EINVAL, "no adjoint kernel variant"};
+#define CRS_ADJ16(TT)                                                                                 \
+  hipLaunchKernelGGL((k_leg_adj16<TT>), dim3(nb, g16), dim3(256), 0, s, a, nmaps, phase, pstride,     \
+                     vpart, vstride, tstride, ntg)
+#define CRS_ADJ4(N, TT)                                                                               \
+  hipLaunchKernelGGL((k_leg_adj4<N, TT>), dim3(nb), dim3(256), 0, s, a, nmaps, 4 * g16, phase,        \
+                     pstride, vpart, vstride, tstride, ntg)
+#define CRS_ADJ4T(N)                                                                                  \
+  do {                                                                                                \
+    if (c.adj_t == 4) CRS_ADJ4(N, 4);                                                                 \
+    else if (c.adj_t == 2) CRS_ADJ4(N, 2);                                                            \
+    else CRS_ADJ4(N, 1);                                                                              \
+  } while (0)
+  if (g16 > 0) {
+    if (c.adj_t == 4) CRS_ADJ16(4);
+    else if (c.adj_t == 2) CRS_ADJ16(2);
+    else CRS_ADJ16(1);
+  }
+  if (rest == 1) CRS_ADJ4T(1);
+  else if (rest == 2) CRS_ADJ4T(2);
+  else if (rest == 3) CRS_ADJ4T(3);
+#undef CRS_ADJ16
+#undef CRS_ADJ4
+#undef CRS_ADJ4T
+  CRS_HIP(hipGetLastError());
 }
 
 // ------------------------------------------------------------ autotuner
@@ -1007,60 +975,41 @@ LegChoice leg_autotune(const LegArgs& a0, int nmaps, double* uhat, double2* phas
   const int L = a.lmax;
   const int64_t nalm = (int64_t)(L + 1) * (L + 1);
   const int64_t pst = (int64_t)a.nring * (L + 1);
-  const LegChoice base = default_choice(a.npairs, L, nmaps);
-  // the largest tile count of any candidate (one 64-pair tile per wave)
+  LegChoice best = default_choice(a.npairs, L, nmaps);
+  const int tiles = a.nslots / 64;
+  // the largest partial-sum count of any candidate (one tile per wave)
   DevBuf<double> vpart;
-  vpart.alloc((size_t)((a.npairs + 63) / 64) * nmaps * nalm);
+  vpart.alloc((size_t)tiles * nmaps * nalm);
   CRS_HIP(hipMemsetAsync(uhat, 0, (size_t)nmaps * nalm * sizeof(double), s));
   CRS_HIP(hipMemsetAsync(phase, 0, (size_t)nmaps * pst * sizeof(double2), s));
   const int reps = 3;
-  LegChoice best = base;
   float tbest = 1e30f;
-  auto try_syn = [&](LegChoice c) {
-    const float t = time_launches([&] { launch_leg_synth(c, a, nmaps, uhat, nalm, phase, pst, s); }, reps, s);
-    if (t < tbest) {
-      tbest = t;
-      best.syn_mfma = c.syn_mfma;
-      best.syn_r = c.syn_r;
+  for (int t : {1, 2, 4}) {
+    if (t > syn_tmax(nmaps) || t >= 2 * tiles) continue;
+    LegChoice c = best;
+    c.syn_t = t;
+    const float ms = time_launches([&] { launch_leg_synth(c, a, nmaps, uhat, nalm, phase, pst, s); }, reps, s);
+    if (ms < tbest) {
+      tbest = ms;
+      best.syn_t = t;
     }
-  };
-  for (int r : {1, 2, 4}) {
-    if (r > syn_rmax(nmaps)) continue;
-    LegChoice c = base;
-    c.syn_mfma = 0;
-    c.syn_r = r;
-    try_syn(c);
   }
-  if (nmaps >= 2) {
-    LegChoice c = base;
-    c.syn_mfma = 1;
-    try_syn(c);
-  }
+  // the adjoint's candidates are timed with the sum over their partials
   tbest = 1e30f;
-  auto try_adj = [&](LegChoice c) {
-    const float t = time_launches([&] {
+  for (int t : {1, 2, 4}) {
+    if (t > kAdjTmax || t >= 2 * tiles) continue;
+    LegChoice c = best;
+    c.adj_t = t;
+    const int nt = tile_groups(a.pol_tiles, a.nslots, t);
+    const float ms = time_launches([&] {
       launch_leg_adjoint(c, a, nmaps, phase, pst, vpart.p, nalm, (int64_t)nmaps * nalm, false, s);
+      launch_tile_sum(nalm, nmaps, vpart.p, nalm, nt, (int64_t)nmaps * nalm, uhat, nalm, s);
     }, reps, s);
-    if (t < tbest) {
-      tbest = t;
-      best.adj_mfma = c.adj_mfma;
-      best.adj_r = c.adj_r;
-      best.adj_t = c.adj_t;
+    if (ms < tbest) {
+      tbest = ms;
+      best.adj_t = t;
     }
-  };
-  for (int r : {1, 2, 4}) {
-    LegChoice c = base;
-    c.adj_mfma = 0;
-    c.adj_r = r;
-    try_adj(c);
   }
-  if (nmaps >= 2)
-    for (int t : {1, 2}) {
-      LegChoice c = base;
-      c.adj_mfma = 1;
-      c.adj_t = t;
-      try_adj(c);
-    }
   CRS_HIP(hipStreamSynchronize(s));
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1072,33 +1021,23 @@ LegChoice leg_autotune(const LegArgs& a0, int nmaps, double* uhat, double2* phas
 }
 
 namespace {
-__global__ void k_tile_sum(const double* __restrict__ hs, int64_t nalm, const double* __restrict__ in,
-                           int64_t istride, int ntiles, int64_t tstride, double* __restrict__ out,
-                           int64_t ostride) {
+__global__ void k_tile_sum(int64_t nalm, const double* __restrict__ in, int64_t istride, int ntiles, int64_t tstride,
+                           double* __restrict__ out, int64_t ostride) {
   const int map = blockIdx.y;
   const double* __restrict__ src = in + (int64_t)map * istride;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nalm; i += (int64_t)gridDim.x * blockDim.x) {
     double acc = 0.0;
     for (int t = 0; t < ntiles; ++t) acc += src[(int64_t)t * tstride + i];
-    out[(int64_t)map * ostride + i] = hs[i] * acc;
+    out[(int64_t)map * ostride + i] = acc;
   }
 }
 }  // namespace
 
-void launch_tile_sum(const double* hs, int64_t nalm, int nmaps, const double* in, int64_t istride,
-                     int ntiles, int64_t tstride, double* out, int64_t ostride, hipStream_t s) {
+void launch_tile_sum(int64_t nalm, int nmaps, const double* in, int64_t istride, int ntiles, int64_t tstride,
+                     double* out, int64_t ostride, hipStream_t s) {
   const int64_t nb = std::min<int64_t>((nalm + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_tile_sum, dim3((unsigned)nb, nmaps), dim3(256), 0, s, hs, nalm, in, istride, ntiles, tstride,
+  hipLaunchKernelGGL(k_tile_sum, dim3((unsigned)nb, nmaps), dim3(256), 0, s, nalm, in, istride, ntiles, tstride,
                      out, ostride);
-  CRS_HIP(hipGetLastError());
-}
-
-void launch_hat_scale(const double* f, int lmax, int nmaps, const double* in, int64_t istride,
-                      int ntiles, int64_t tstride, double* out, int64_t ostride, bool square,
-                      hipStream_t s) {
-  dim3 grid((2 * (lmax + 1) + 255) / 256, lmax + 1, nmaps);
-  hipLaunchKernelGGL(k_hat_scale, grid, dim3(256), 0, s, f, lmax, nmaps, in, istride, ntiles,
-                     tstride, out, ostride, square ? 1 : 0);
   CRS_HIP(hipGetLastError());
 }
 

@@ -185,7 +185,7 @@ void apply_j(const MaskLevel& lv, int L, const ShtPlan& p, MaskRun& r, double* m
   synth_ws(lv.grid, L, nm, r.sc.hat.p, map, r, skip, s);
   map_op(MOP_MASK, r, map, nullptr, nullptr, lv.ind.p, nullptr, 0.0, lv.grid->npix, skip, s);
   const int nt = adjoint_ws(lv.grid, L, nm, map, r, skip, s);
-  launch_from_parts(out, (const int64_t*)nullptr, L, 0, lv.w, p.hs.p, r.sc.parts.p, nt, (int64_t)nm * nalm_of(L),
+  launch_from_parts(out, (const int64_t*)nullptr, L, 0, lv.w, r.sc.parts.p, nt, (int64_t)nm * nalm_of(L),
                     (const double*)nullptr, 0, (const double*)nullptr, 0, (int64_t)0, (const double*)nullptr, 0,
                     r.mc.p, nm, skip, s);
 }
@@ -213,28 +213,27 @@ void vcycle(const MaskMG& mg, MaskRun& r, int h, MapSkip skip, hipStream_t s) {
   // u = Y_h^T x                                               (L_h, N_h)
   int nt = adjoint_ws(lv.grid, Lh, nm, r.x[h].p, r, skip, s);
   launch_from_parts(r.u[h].p, (const int64_t*)nullptr, Lh, 0, 1.0,
-                     ph.hs.p, r.sc.parts.p, nt, (int64_t)nm * nalm_of(Lh), (const double*)nullptr, 0,
+                     r.sc.parts.p, nt, (int64_t)nm * nalm_of(Lh), (const double*)nullptr, 0,
                      (const double*)nullptr, 0, (int64_t)0, (const double*)nullptr, 0, r.mc.p, nm, skip, s);
   // exact J: jv = J D_h u = W_h Y_h^T (mask_h) Y_h D_h u       (L_h, N_h)
   if (mg.exact_j) {
-    launch_hat_from(r.sc.hat.p, Lh, ph.hs.p, (const double*)r.u[h].p, Lh, (const int64_t*)nullptr, nalm_of(Lh),
+    launch_hat_from(r.sc.hat.p, Lh, (const double*)r.u[h].p, Lh, (const int64_t*)nullptr, nalm_of(Lh),
                     (const double*)nullptr, 0, (int64_t)0, lv.D.p, Lh + 1, r.mc.p, nm, skip, s);
     apply_j(lv, Lh, ph, r, r.y[h].p, r.jv[h].p, skip, s);
   }
   // r~ = W_h Y_h^T b - D_h u (J D_h u with exact J), at L_H  (L_H, N_h)
   nt = adjoint_ws(lv.grid, LH, nm, r.b[h].p, r, skip, s);
   if (mg.exact_j) {
-    launch_from_parts(r.rt[h].p, (const int64_t*)nullptr, LH, 0, lv.w, pH.hs.p, r.sc.parts.p, nt,
+    launch_from_parts(r.rt[h].p, (const int64_t*)nullptr, LH, 0, lv.w, r.sc.parts.p, nt,
                       (int64_t)nm * nalm_of(LH), (const double*)nullptr, 0, r.jv[h].p, Lh, nalm_of(Lh),
                       mg.ones.p, 0, r.mc.p, nm, skip, s);
   } else {
     launch_from_parts(r.rt[h].p, (const int64_t*)nullptr, LH, 0,
-                       lv.w, pH.hs.p, r.sc.parts.p, nt, (int64_t)nm * nalm_of(LH), (const double*)nullptr, 0, r.u[h].p, Lh,
+                       lv.w, r.sc.parts.p, nt, (int64_t)nm * nalm_of(LH), (const double*)nullptr, 0, r.u[h].p, Lh,
                        nalm_of(Lh), lv.D.p, Lh + 1, r.mc.p, nm, skip, s);
   }
   // r_H = (mask_H) Y_H R_H r~                                (L_H, N_H)
-  launch_hat_from(r.sc.hat.p, LH, get_plan(cv.grid, LH, s).hs.p,
-                     (const double*)r.rt[h].p, LH, (const int64_t*)nullptr, nalm_of(LH), (const double*)nullptr, 0,
+  launch_hat_from(r.sc.hat.p, LH, (const double*)r.rt[h].p, LH, (const int64_t*)nullptr, nalm_of(LH), (const double*)nullptr, 0,
                      (int64_t)0, lv.rH.p, 0, r.mc.p, nm, skip, s);
   CRS_HIP(hipGetLastError());
   synth_ws(cv.grid, LH, nm, r.sc.hat.p, r.b[h + 1].p, r, skip, s);
@@ -243,10 +242,10 @@ void vcycle(const MaskMG& mg, MaskRun& r, int h, MapSkip skip, hipStream_t s) {
   // c~ = R_H Y_H^T c_H                                       (L_H, N_H)
   nt = adjoint_ws(cv.grid, LH, nm, r.x[h + 1].p, r, skip, s);
   launch_from_parts(r.ct[h].p, (const int64_t*)nullptr, LH, 0,
-                     1.0, get_plan(cv.grid, LH, s).hs.p, r.sc.parts.p, nt, (int64_t)nm * nalm_of(LH), lv.rH.p, 0,
+                     1.0, r.sc.parts.p, nt, (int64_t)nm * nalm_of(LH), lv.rH.p, 0,
                      (const double*)nullptr, 0, (int64_t)0, (const double*)nullptr, 0, r.mc.p, nm, skip, s);
   // x += (mask_h) W_h Y_h c~                                 (L_H, N_h)
-  launch_hat_from(r.sc.hat.p, LH, pH.hs.p, (const double*)r.ct[h].p,
+  launch_hat_from(r.sc.hat.p, LH, (const double*)r.ct[h].p,
                      LH, (const int64_t*)nullptr, nalm_of(LH), (const double*)nullptr, 0, (int64_t)0,
                      (const double*)nullptr, 0, r.mc.p, nm, skip, s);
   CRS_HIP(hipGetLastError());
@@ -255,13 +254,13 @@ void vcycle(const MaskMG& mg, MaskRun& r, int h, MapSkip skip, hipStream_t s) {
   // x += M_h (b - (mask_h) Y_h D_h (u + c~))                 (L_h, N_h)
   // (exact J: u + J c~, J c~ = W_h Y_h^T (mask_h) Y_h c~ at L_h)
   if (mg.exact_j) {
-    launch_hat_from(r.sc.hat.p, Lh, ph.hs.p, (const double*)r.ct[h].p, LH, (const int64_t*)nullptr, nalm_of(LH),
+    launch_hat_from(r.sc.hat.p, Lh, (const double*)r.ct[h].p, LH, (const int64_t*)nullptr, nalm_of(LH),
                     (const double*)nullptr, 0, (int64_t)0, (const double*)nullptr, 0, r.mc.p, nm, skip, s);
     apply_j(lv, Lh, ph, r, r.y[h].p, r.jv[h].p, skip, s);
-    launch_hat_from(r.sc.hat.p, Lh, ph.hs.p, (const double*)r.u[h].p, Lh, (const int64_t*)nullptr, nalm_of(Lh),
+    launch_hat_from(r.sc.hat.p, Lh, (const double*)r.u[h].p, Lh, (const int64_t*)nullptr, nalm_of(Lh),
                     (const double*)r.jv[h].p, Lh, nalm_of(Lh), lv.D.p, Lh + 1, r.mc.p, nm, skip, s);
   } else {
-    launch_hat_from(r.sc.hat.p, Lh, ph.hs.p, (const double*)r.u[h].p,
+    launch_hat_from(r.sc.hat.p, Lh, (const double*)r.u[h].p,
                        Lh, (const int64_t*)nullptr, nalm_of(Lh), (const double*)r.ct[h].p, LH, nalm_of(LH), lv.D.p,
                        Lh + 1, r.mc.p, nm, skip, s);
   }
@@ -528,7 +527,7 @@ void exec_mask(Exec& e, const double* r, double* z, bool accumulate, hipStream_t
     const int L0 = mg.L0;
     const ShtPlan& p0 = get_plan(l0.grid, L0, s);
     // b_0 = (mask) Y R r_k
-    launch_hat_from(run.sc.hat.p, L0, p0.hs.p, r, L0,
+    launch_hat_from(run.sc.hat.p, L0, r, L0,
                        run.off_top.p, (int64_t)0, (const double*)nullptr, 0, (int64_t)0, mg.rtop.p, 0, run.mc.p, run.nm, skip, s);
     CRS_HIP(hipGetLastError());
     synth_ws(l0.grid, L0, run.nm, run.sc.hat.p, run.b[0].p, run, skip, s);
@@ -537,7 +536,7 @@ void exec_mask(Exec& e, const double* r, double* z, bool accumulate, hipStream_t
     // z_k (+)= R Y^T x_0
     const int nt = adjoint_ws(l0.grid, L0, run.nm, run.x[0].p, run, skip, s);
     launch_from_parts(z, run.off_top.p, L0, accumulate ? 1 : 0,
-                       1.0, p0.hs.p, run.sc.parts.p, nt, (int64_t)run.nm * nalm_of(L0), mg.rtop.p, 0,
+                       1.0, run.sc.parts.p, nt, (int64_t)run.nm * nalm_of(L0), mg.rtop.p, 0,
                        (const double*)nullptr, 0, (int64_t)0, (const double*)nullptr, 0, run.mc.p, run.nm, skip, s);
     CRS_HIP(hipGetLastError());
   }

@@ -33,7 +33,7 @@ void VarMixRunDel::operator()(VarMixRun* p) const { delete p; }
 
 namespace {
 
-// hat[j][i] = hs_i^2 b_{nu,l} sum_t parts_nu[t][map(j)][i_nu] at band-limit Lk:
+// hat[j][i] = b_{nu,l} sum_t parts_nu[t][map(j)][i_nu] at band-limit Lk:
 // the synthesis input of Q~ applied to B_nu v_nu (v_nu the plain band
 // adjoint), repacked from the band's layout at L_nu (zero above L_nu).
 __global__ void k_band_hat(double* __restrict__ hat, int Lk, const SysDev* __restrict__ sys,
@@ -60,9 +60,7 @@ __global__ void k_band_hat(double* __restrict__ hat, int Lk, const SysDev* __res
       const int64_t ib = moff_h(Lb, m) + (int64_t)part * (Lb - m + 1) + ll;
       double sv = 0.0;
       for (int t = 0; t < nt; ++t) sv += v[(int64_t)t * tstride + ib];
-      const double cm = (m == 0) ? 1.0 : 1.4142135623730951;
-      const double hs = cm * P.ftab[tri_h(P.Lf, m) + ll];
-      val = hs * hs * beamtab[(int64_t)l * nb + nu] * sv;
+      val = beamtab[(int64_t)l * nb + nu] * sv;
     }
     o[i] = val;
   }
@@ -115,14 +113,13 @@ void exec_varmix_fwd(Exec& e, const double* x, hipStream_t s, const double* act)
   for (size_t v = 0; v < m->varmix.size(); ++v) {
     const VarMix& vm = m->varmix[v];
     const int Lk = m->lk[vm.k];
-    const double* hs = get_plan(vm.grid, Lk, s).hs.p;
     // y = Y^T W Q Y x_k
-    launch_hat_from(r.sc.hat.p, Lk, hs, x, Lk, r.xoff[v].p, 0, nullptr, 0, 0, nullptr, 0, nullptr, r.nm, skip, s);
+    launch_hat_from(r.sc.hat.p, Lk, x, Lk, r.xoff[v].p, 0, nullptr, 0, 0, nullptr, 0, nullptr, r.nm, skip, s);
     scratch_synth(r.sc, vm.grid, Lk, r.nm, r.sc.hat.p, r.map.p, skip, s);
     launch_map_op(MOP_MASK, r.map.p, nullptr, nullptr, vm.qw.p, nullptr, 0.0, vm.grid->npix, r.nm, skip, s);
     const int nt = scratch_adjoint(r.sc, vm.grid, Lk, r.nm, r.map.p, skip, s);
     const int64_t nalm = (int64_t)(Lk + 1) * (Lk + 1);
-    launch_from_parts(r.ybuf.p + r.hyoff[v], nullptr, Lk, 0, 1.0, hs, r.sc.parts.p, nt, (int64_t)r.nm * nalm,
+    launch_from_parts(r.ybuf.p + r.hyoff[v], nullptr, Lk, 0, 1.0, r.sc.parts.p, nt, (int64_t)r.nm * nalm,
                       nullptr, 0, nullptr, 0, 0, nullptr, 0, nullptr, r.nm, skip, s);
   }
 }
@@ -139,7 +136,6 @@ void exec_varmix_back(Exec& e, double* out, hipStream_t s, const double* act) {
   for (size_t v = 0; v < m->varmix.size(); ++v) {
     const VarMix& vm = m->varmix[v];
     const int Lk = m->lk[vm.k];
-    const double* hs = get_plan(vm.grid, Lk, s).hs.p;
     const int64_t nalm = (int64_t)(Lk + 1) * (Lk + 1);
     // out_k += Y^T W Q Y (B_nu v_nu)
     dim3 gr((unsigned)std::min<int64_t>((nalm + 255) / 256, 2048), r.nm);
@@ -149,7 +145,7 @@ void exec_varmix_back(Exec& e, double* out, hipStream_t s, const double* act) {
     scratch_synth(r.sc, vm.grid, Lk, r.nm, r.sc.hat.p, r.map.p, skip, s);
     launch_map_op(MOP_MASK, r.map.p, nullptr, nullptr, vm.qw.p, nullptr, 0.0, vm.grid->npix, r.nm, skip, s);
     const int nt = scratch_adjoint(r.sc, vm.grid, Lk, r.nm, r.map.p, skip, s);
-    launch_from_parts(out, r.xoff[v].p, Lk, 1, 1.0, hs, r.sc.parts.p, nt, (int64_t)r.nm * nalm, nullptr, 0,
+    launch_from_parts(out, r.xoff[v].p, Lk, 1, 1.0, r.sc.parts.p, nt, (int64_t)r.nm * nalm, nullptr, 0,
                       nullptr, 0, 0, nullptr, 0, nullptr, r.nm, skip, s);
   }
 }

@@ -89,7 +89,6 @@ struct ProbDev {
   const double* dInv;    // [Lf+1][nc]: C^-1
   const double* dSqrt;   // [Lf+1][nc]: C^-1/2
   const double* dPi;     // [Lf+1][nc][nc]: U^+_pr (U^+_pr)^T
-  const double* ftab;    // f_lm triangle at Lf
   const double* Dinv;    // [(Lc+1)^2][nc][nc] M_diag blocks (NULL without)
   const double* const* vptr;  // per band: partial sums of its group (this Exec)
   const int* binfo;           // per band: {L, group maps, map base, tiles, map stride, dropped from M_PI}
@@ -130,13 +129,13 @@ struct ExecGroup {
 
 // ------------------------------------------- harmonic / map batch operations
 // (harmonic.hip).  nm vectors or maps per launch, map j skipped when skip.off(j).
-// out_hat[j] = hs f_j[l] (in1_j + in2_j) repacked to LO (in1_j at in1 + off1[j]
+// out[j] = f_j[l] (in1_j + in2_j) repacked to LO (in1_j at in1 + off1[j]
 // or + j st1; in2 optional at in2 + j st2; f_j = F + mc[j] fst, optional)
-void launch_hat_from(double* out, int LO, const double* hs, const double* in1, int L1, const int64_t* off1,
+void launch_hat_from(double* out, int LO, const double* in1, int L1, const int64_t* off1,
                      int64_t st1, const double* in2, int L2, int64_t st2, const double* F, int fst, const int* mc,
                      int nm, MapSkip skip, hipStream_t s);
-// out_j (at out + offo[j] or + j nalm(LO)) (+)= alpha f_j[l] hs sum_t parts[t][j] - g_j[l] sub_j
-void launch_from_parts(double* out, const int64_t* offo, int LO, int acc, double alpha, const double* hs,
+// out_j (at out + offo[j] or + j nalm(LO)) (+)= alpha f_j[l] sum_t parts[t][j] - g_j[l] sub_j
+void launch_from_parts(double* out, const int64_t* offo, int LO, int acc, double alpha,
                        const double* parts, int ntiles, int64_t tstride, const double* F, int fst, const double* sub,
                        int Ls, int64_t sst, const double* Gs, int gst, const int* mc, int nm, MapSkip skip,
                        hipStream_t s);
@@ -152,7 +151,7 @@ struct ShtScratch {
   std::map<std::pair<crs_grid, int>, std::pair<int, LegChoice>> choice;
   void reserve(crs_grid g, int L, int nm, hipStream_t s);
 };
-// map[j] = Y hat[j] (hat: nm x nalm(L) hat vectors; map stride npix)
+// map[j] = Y hat[j] (hat: nm x nalm(L); map stride npix)
 void scratch_synth(ShtScratch& w, crs_grid g, int L, int nm, const double* hat, double* map, MapSkip skip,
                    hipStream_t s);
 // Y^T map to per-tile partial sums in w.parts ([tile][j][nalm(L)]); returns the tile count
@@ -340,7 +339,6 @@ struct crs_model_s {
   crs::DevBuf<double> cA, cP;        // [Lmax+1][nb][nc]
   crs::DevBuf<double> dInv, dSqrt;   // [Lmax+1][nc] diagonal prior terms
   crs::DevBuf<double> dPi;           // [Lmax+1][nc][nc]
-  crs::DevBuf<double> ftab;          // f_lm triangle at Lmax
   crs::DevBuf<double> beamtab;       // [Lmax+1][nb] b_{nu,l} (0 above L_nu)
   crs::DevBuf<double> gwork;         // [x; lambda] stacked for the mixing gradient
   crs::DevBuf<double> Dinv;          // [(Lc+1)^2][nc][nc]

@@ -117,24 +117,6 @@ void small_pinv(const std::vector<double>& A, int m, int n, std::vector<double>&
   }
 }
 
-void build_ftab(crs_model m, hipStream_t s) {
-  const int L = m->Lmax;
-  int64_t ntri = (int64_t)(L + 1) * (L + 2) / 2;
-  std::vector<double> ft(ntri, 0.0);
-  for (int mm = 0; mm <= L; ++mm) {
-    int64_t o = tri_h(L, mm) - mm;
-    ft[o + mm] = 1.0;
-    if (mm + 1 <= L) ft[o + mm + 1] = 1.0;
-    for (int l = mm + 2; l <= L; ++l) {
-      double dl = l, dm = mm;
-      double a = std::sqrt((4.0 * dl * dl - 1.0) / ((dl - dm) * (dl + dm)));
-      double b = std::sqrt(((dl - 1.0 - dm) * (dl - 1.0 + dm)) / (4.0 * (dl - 1.0) * (dl - 1.0) - 1.0));
-      ft[o + l] = a * b * ft[o + l - 2];
-    }
-  }
-  m->ftab.upload(ft, s);
-}
-
 // U_l^+ and the derived device tables (cP, dPi); alpha must be set.
 void build_pinv_tables(crs_model m, hipStream_t s) {
   const int nb = m->nbands, nc = m->ncomp, L = m->Lmax;
@@ -225,7 +207,7 @@ void build_diag(crs_model m, hipStream_t s) {
     Band& b = m->bands[nu];
     ShtPlan& p = get_plan(b.grid, b.lmax, s);
     const LegChoice lc = leg_choice(p.npairs, b.lmax, 1);
-    const int ntiles = leg_adjoint_tiles(lc, p.npairs, true);
+    const int ntiles = leg_adjoint_tiles(lc, b.grid, true);
     const int64_t nalm = (int64_t)(b.lmax + 1) * (b.lmax + 1);
     const int64_t pst = (int64_t)b.grid->nring * (b.lmax + 1);
     DevBuf<double2> ph;
@@ -235,7 +217,7 @@ void build_diag(crs_model m, hipStream_t s) {
     out.alloc((size_t)nalm);
     launch_ring(b.grid, b.lmax, RING_DIAG, 1, ph.p, pst, b.tau.p, nullptr, b.grid->npix, nullptr, 1, s);
     launch_leg_adjoint(lc, leg_args(b.grid, p), 1, ph.p, pst, vp.p, nalm, nalm, true, s);
-    launch_hat_scale(p.f.p, b.lmax, 1, vp.p, nalm, ntiles, nalm, out.p, nalm, true, s);
+    launch_tile_sum(nalm, 1, vp.p, nalm, ntiles, nalm, out.p, nalm, s);
     dg[nu].resize(nalm);
     CRS_HIP(hipMemcpyAsync(dg[nu].data(), out.p, nalm * sizeof(double), hipMemcpyDeviceToHost, s));
     CRS_HIP(hipStreamSynchronize(s));
@@ -439,7 +421,6 @@ int crs_model_create(const crs_model_desc* d, crs_stream st, crs_model* out) {
     }
     m->d_lk.upload(m->lk, s);
     m->d_coff.upload(m->coff, s);
-    build_ftab(m.get(), s);
     build_mix_tables(m.get(), s);
     build_pinv_tables(m.get(), s);
     if (d->flags & CRS_MODEL_DIAG) {

@@ -370,3 +370,45 @@ def test_reserve_then_transforms_allocate_nothing():
     assert torch.cuda.mem_get_info()[0] == free0
     assert _rel(out_map[:2].cpu().numpy(), ref_map) < 1e-13
     assert _rel(out_alm[:2].cpu().numpy(), ref_alm) < 1e-13
+
+
+TILES = [
+    # (spec, lmax, nmaps, tiles per wave synthesis / adjoint): every map count
+    # that picks another kernel, tile groups of one and of several tiles with
+    # a ragged last one, grids with and without padded polar slots, the last
+    # block of steps cut at every length (odd and even lmax)
+    (("healpix", 37), 91, 1, 4, 4),
+    (("healpix", 64), 130, 2, 2, 4),
+    (("healpix", 100), 205, 3, 2, 4),    # 200 pairs: four tiles, the last of 8 pairs
+    (("healpix", 70), 72, 4, 2, 2),
+    (("healpix", 33), 64, 5, 1, 2),
+    (("gl", 131, 262), 130, 6, 1, 4),    # equator ring, 66 pairs
+    (("gl", 70, 141), 69, 7, 1, 2),
+    (("healpix", 21), 31, 8, 1, 4),
+    (("healpix", 34), 47, 11, 1, 1),
+    (("healpix", 2), 1, 6, 1, 1),
+]
+
+
+@pytest.mark.parametrize("spec,lmax,nmaps,ts,ta", TILES)
+def test_legendre_tiles_match_oracle(spec, lmax, nmaps, ts, ta, monkeypatch):
+    torch, crsolve = _setup()
+    monkeypatch.setenv("CRS_LEG_TS", str(ts))
+    monkeypatch.setenv("CRS_LEG_TA", str(ta))
+    print(f"case tiles {spec} lmax={lmax} nmaps={nmaps} {ts} {ta}", flush=True)
+    g = crsolve.Grid.from_spec(spec)
+    og = geometry.make_grid(spec)
+    rng = np.random.default_rng(51)
+    alm = rng.standard_normal((nmaps, sht.nalm(lmax)))
+    maps = rng.standard_normal((nmaps, og.npix))
+    dev = torch.device("cuda")
+    got_map = crsolve.sht_synth(g, lmax, torch.tensor(alm, device=dev))
+    got_alm = crsolve.sht_adjoint(g, lmax, torch.tensor(maps, device=dev))
+    assert _rel(got_map.cpu().numpy(), sht.synth(og, lmax, alm)) < SHT_TOL
+    assert _rel(got_alm.cpu().numpy(), sht.adjoint(og, lmax, maps)) < SHT_TOL
+    # a map's result does not depend on the maps beside it (the Legendre sums
+    # run in one order; the ring stage of a map is its own)
+    one_map = crsolve.sht_synth(g, lmax, torch.tensor(alm[-1:], device=dev))
+    one_alm = crsolve.sht_adjoint(g, lmax, torch.tensor(maps[-1:], device=dev))
+    assert torch.equal(one_map[0], got_map[-1])
+    assert torch.equal(one_alm[0], got_alm[-1])
