@@ -174,24 +174,12 @@ LegArgs leg_args(crs_grid g, ShtPlan& p) {
 
 RingArgs ring_args(crs_grid g, int lmax) {
   RingArgs r;
-  r.nphi = g->d_nphi.p;
-  r.offset = g->d_offset.p;
-  r.phinum = g->d_phinum.p;
-  r.phiden = g->d_phiden.p;
-  r.nfac = g->d_nfac.p;
-  r.fac = g->d_fac.p;
-  r.facm = g->d_facm.p;
-  r.fftn = g->d_fftn.p;
-  r.twoff = g->d_twoff.p;
+  r.info = nullptr;
   r.tw = g->d_tw.p;
-  r.bfoff = g->d_bfoff.p;
   r.bf = g->d_bf.p;
   r.tw2 = g->d_tw2.p;
-  r.nring = g->nring;
   r.lmax = lmax;
-  r.maxn = g->ring_maxn;
-  r.xcap = 1;
-  r.any_blue = 0;
+  r.xcap = r.wcap = r.pcap = 0;
   r.skip = MapSkip{};
   return r;
 }

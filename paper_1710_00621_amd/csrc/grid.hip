@@ -44,18 +44,28 @@ std::vector<int> factorize(int n) {
   std::vector<int> f;
   int e = 0;
   while (n % 2 == 0) { ++e; n /= 2; }
-  int n8 = e / 3, rest = e % 3;
-  if (rest == 1 && n8 > 0) { --n8; rest = 4; }
-  for (int i = 0; i < n8; ++i) f.push_back(8);
-  if (rest == 4) { f.push_back(4); f.push_back(4); }
-  if (rest == 2) f.push_back(4);
-  if (rest == 1) f.push_back(2);
   for (int p = 3; p * p <= n; p += 2)
     while (n % p == 0) { f.push_back(p); n /= p; }
   if (n > 1) f.push_back(n);
+  std::sort(f.begin(), f.end(), std::greater<int>());
+  for (int s = 0; pow2_radix(e, s) > 0; ++s) f.push_back(pow2_radix(e, s));
   if (f.empty()) f.push_back(1);
   return f;
 }
+
+// Largest prime factor of an FFT length n0 that the ring kernel computes
+// directly (p - 1 FMAs per point); a length with a larger one goes through
+// Bluestein's convolution of 2 n0 .. 4 n0 points.  The direct sums are long
+// serial loops, which short rings (few blocks, a short FFT) cannot hide: ring
+// stage in us with the line at 7 / 19 / 31 / 61 / 97 for every length,
+//   Nside 64, 20 maps (n0 <= 128):    20.9  20.4  21.5  25.7  25.2
+//   33 x 65 GL, 1 map (n0 = 65):       9.2  10.2  10.3  10.7  10.3
+//   Nside 256, 1 map (n0 <= 512):     15.9  17.2  17.0  19.8  23.8
+//   Nside 256, 42 maps (n0 <= 512):    218   218   218   231   239
+//   Nside 1024, 6 maps (n0 <= 2048):   554   544   530   530   532
+//   Nside 1024, 4 maps, adjoint:       355   344   348   339   345
+//   512 x 1026 GL, 40 maps (n0 = 513 = 19 3^3): 306 through Bluestein, 152 directly
+int prime_max(int n0) { return n0 <= 128 ? 7 : n0 <= 512 ? 19 : n0 <= 1024 ? 31 : 61; }
 
 // In-place radix-2 complex FFT (forward, exp(-2 pi i jk / n)), n a power of two.
 void host_fft_pow2(std::vector<double2>& x) {
@@ -194,52 +204,53 @@ void grid_finalize(crs_grid g, hipStream_t s) {
   // half-length complex transform (two real samples per complex word); a
   // length whose largest prime factor exceeds 7 goes through Bluestein's
   // chirp convolution with a power-of-two FFT.
-  std::vector<int> nfac(nr), fac((size_t)nr * kMaxFactors, 1), fftn(nr);
-  std::vector<unsigned> facm((size_t)nr * kMaxFactors, 0u);
-  std::vector<int64_t> twoff(nr), bfoff(nr, -1);
+  std::vector<RingInfo> info(nr);
   std::map<int, int64_t> tw_of, bf_of;
   std::vector<double2> tw, bf;
   g->ring_classes.clear();
   std::map<int, int> class_of;
-  bool any_blue = false;
+  bool any_pow2 = false;
   for (int r = 0; r < nr; ++r) {
     const int n = g->nphi[r];
+    RingInfo& ri = info[r];
+    ri = RingInfo{};
+    ri.ring = r;
+    ri.nphi = n;
+    ri.num = g->phi0_num[r];
+    ri.offset = g->offset[r];
+    ri.bfoff = -1;
     const bool half = (n % 2) == 0;
     const int n0 = half ? n / 2 : n;
     auto f0 = factorize(n0);
-    // radices are 2, 4, 8 and primes, so a prime factor above 7 is one > 8
-    bool blue = false;
-    for (int v : f0) blue = blue || v > 8;
+    const int pmax = f0[0];  // the largest odd prime, if there is one
+    bool blue = (pmax & 1) && pmax > prime_max(n0);
+    CRS_CHECK(n0 <= 4096 || !(pmax & 1) || pmax <= 7, CRS_EUNSUPPORTED,
+              "ring FFT above 8192 points (an odd ring longer than 4096 pixels with a prime factor above 7)");
     int nf = n0;
     if (blue) {
       nf = 1;
       while (nf < 2 * n0 - 1) nf *= 2;
-      any_blue = true;
       auto it = bf_of.find(n0);
       if (it == bf_of.end()) {
         bf_of[n0] = (int64_t)bf.size();
-        bfoff[r] = (int64_t)bf.size();
+        ri.bfoff = (int64_t)bf.size();
         auto spec = bluestein_filter(n0, nf);
         bf.insert(bf.end(), spec.begin(), spec.end());
       } else {
-        bfoff[r] = it->second;
+        ri.bfoff = it->second;
       }
     }
-    CRS_CHECK(nf <= kBlueMax, CRS_EUNSUPPORTED,
-              "ring FFT above 8192 points (an odd ring longer than 4096 pixels with a prime factor above 7)");
     auto ff = factorize(nf);
-    CRS_CHECK((int)ff.size() <= kMaxFactors, CRS_EUNSUPPORTED, "too many FFT factors");
-    nfac[r] = (int)ff.size();
-    {
-      unsigned ns = 1;
-      for (size_t i = 0; i < ff.size(); ++i) {
-        fac[(size_t)r * kMaxFactors + i] = ff[i];
-        facm[(size_t)r * kMaxFactors + i] = ns <= 1 ? 0u : (unsigned)(0xFFFFFFFFull / ns + 1);
-        ns *= (unsigned)ff[i];
-      }
+    CRS_CHECK((int)ff.size() <= kRingStages, CRS_EUNSUPPORTED, "too many FFT factors");
+    ri.nfac = (int)ff.size();
+    ri.fftn = nf;
+    unsigned ns = 1;
+    for (size_t i = 0; i < ff.size(); ++i) {
+      ri.fac[i] = ff[i];
+      ri.facm[i] = ns <= 1 ? 0u : (unsigned)(0xFFFFFFFFull / ns + 1);
+      ns *= (unsigned)ff[i];
     }
-    fftn[r] = nf;
-    g->ring_maxn = std::max(g->ring_maxn, n);
+    any_pow2 = any_pow2 || (nf & (nf - 1)) == 0;
     auto it = tw_of.find(n);
     if (it == tw_of.end()) {
       int64_t o = (int64_t)tw.size();
@@ -249,18 +260,17 @@ void grid_finalize(crs_grid g, hipStream_t s) {
         host_sincospi((double)t / (double)n, &sv, &cv);
         tw.push_back(make_double2(cv, -sv));
       }
-      twoff[r] = o;
+      ri.twoff = o;
     } else {
-      twoff[r] = it->second;
+      ri.twoff = it->second;
     }
     int tier = 0;
     while (ring_tier_maxfft(tier) < nf) ++tier;
-    // classes by (tier, Bluestein, odd radix) from the 512-thread tier up: a
+    // classes by (tier, Bluestein, odd radix) from the 256-thread tier up: a
     // class without odd radices runs a kernel built for power-of-two FFTs
-    // only (72 instead of 115 registers: more blocks per CU), and Bluestein's
-    // longer buffers do not set the LDS size of the direct rings.  The
-    // smaller tiers stay whole (their kernels differ by a few registers,
-    // less than an extra launch costs).
+    // only (107 to 115 instead of 127 registers), and Bluestein's longer
+    // buffers do not set the LDS size of the direct rings.  The smaller tiers
+    // stay whole (the difference is less than an extra launch costs).
     bool odd = false;
     for (int v : ff) odd = odd || (v % 2) != 0;
     const int key = tier >= 2 ? tier * 4 + (blue ? 2 : 0) + (odd ? 1 : 0) : tier * 4;
@@ -275,18 +285,27 @@ void grid_finalize(crs_grid g, hipStream_t s) {
     rc.rings.push_back(r);
     rc.blue = rc.blue || blue;
     rc.odd = rc.odd || odd;
-    rc.xcap = std::max(rc.xcap, std::max(nf, n0));
-    rc.maxn = std::max(rc.maxn, n);
+    rc.xcap = std::max(rc.xcap, nf + nf / 16);
+    rc.wcap = std::max(rc.wcap, 64 + (nf + 63) / 64);
+    int pw = 0;
+    for (int v : ff) pw += v > 7 && (v & 1) ? v : 0;
+    rc.pcap = std::max(rc.pcap, pw);
     const int nt = ring_tier_threads(tier);
-    if (n <= nt) rc.gcap = std::max(rc.gcap, n + n * (nt / n));
+    if (n <= ring_short(nt)) rc.gcap = std::max(rc.gcap, n + n * (ring_short(nt) / n));
   }
   // largest tier first
   std::stable_sort(g->ring_classes.begin(), g->ring_classes.end(),
                    [](const RingClass& x, const RingClass& y) { return x.tier > y.tier; });
   g->d_ring_class.clear();
+  std::vector<std::vector<RingInfo>> hold;  // uploaded from: alive until the sync below
+  auto records = [&](const std::vector<int>& rings) -> const std::vector<RingInfo>& {
+    hold.emplace_back();
+    for (int r : rings) hold.back().push_back(info[r]);
+    return hold.back();
+  };
   for (auto& rc : g->ring_classes) {
     g->d_ring_class.emplace_back();
-    g->d_ring_class.back().upload(rc.rings, s);
+    g->d_ring_class.back().upload(records(rc.rings), s);
   }
   // Launches with few maps merge the classes that would have too few blocks
   // to fill the GPU on their own into one launch (run by the kernel of their
@@ -309,7 +328,8 @@ void grid_finalize(crs_grid g, hipStream_t s) {
     acc.blue = acc.blue || rc.blue;
     acc.odd = acc.odd || rc.odd;
     acc.xcap = std::max(acc.xcap, rc.xcap);
-    acc.maxn = std::max(acc.maxn, rc.maxn);
+    acc.wcap = std::max(acc.wcap, rc.wcap);
+    acc.pcap = std::max(acc.pcap, rc.pcap);
     acc.rings.insert(acc.rings.end(), rc.rings.begin(), rc.rings.end());
     RingClass m = acc;
     std::sort(m.rings.begin(), m.rings.end());
@@ -318,24 +338,23 @@ void grid_finalize(crs_grid g, hipStream_t s) {
     m.gcap = 0;
     for (int r : m.rings) {
       const int n = g->nphi[r];
-      if (n <= nt) m.gcap = std::max(m.gcap, n + n * (nt / n));
+      if (n <= ring_short(nt)) m.gcap = std::max(m.gcap, n + n * (ring_short(nt) / n));
     }
     g->ring_prefix.push_back(m);
     g->d_ring_prefix.emplace_back();
-    g->d_ring_prefix.back().upload(m.rings, s);
+    g->d_ring_prefix.back().upload(records(m.rings), s);
   }
-  if (any_blue) {
-    std::vector<double2> t2(kBlueMax);
+  std::vector<double2> t2;
+  if (any_pow2) {
+    t2.resize(kBlueMax);
     for (int t = 0; t < kBlueMax; ++t) {
       double sv, cv;
       host_sincospi(2.0 * t / kBlueMax, &sv, &cv);
       t2[t] = make_double2(cv, -sv);
     }
     g->d_tw2.upload(t2, s);
-    g->d_bf.upload(bf, s);
   }
-  g->d_fftn.upload(fftn, s);
-  g->d_bfoff.upload(bfoff, s);
+  if (!bf.empty()) g->d_bf.upload(bf, s);
   slot_layout(g);
   std::vector<double> zs(g->nslots, 0.0), ss(g->nslots, 1.0), ys(g->nslots, 0.0);
   for (int p = 0; p < (nr + 1) / 2; ++p) {
@@ -347,14 +366,6 @@ void grid_finalize(crs_grid g, hipStream_t s) {
     // functions are those at the pixel centres the grid reports
     ys[i] = polar ? -(1.0 - g->z[p]) * (1.0 + g->z[p]) : -g->z[p] * g->z[p];
   }
-  g->d_nphi.upload(g->nphi, s);
-  g->d_offset.upload(g->offset, s);
-  g->d_phinum.upload(g->phi0_num, s);
-  g->d_phiden.upload(g->phi0_den, s);
-  g->d_nfac.upload(nfac, s);
-  g->d_fac.upload(fac, s);
-  g->d_facm.upload(facm, s);
-  g->d_twoff.upload(twoff, s);
   g->d_tw.upload(tw, s);
   g->d_zs.upload(zs, s);
   g->d_ss.upload(ss, s);

@@ -95,7 +95,6 @@ struct DevBuf {
 };
 
 constexpr int kMaxRing = 8192;   // pixels per ring (the FFT stays LDS resident)
-constexpr int kMaxFactors = 16;  // radices per ring length
 constexpr int kBlueMax = 8192;   // longest Bluestein convolution (power of two)
 constexpr size_t kMaxLds = 160 * 1024;  // LDS bytes one workgroup may use (gfx950)
 
@@ -128,19 +127,49 @@ __host__ __device__ inline int64_t erow(int L, int m) { return (int64_t)m * (L +
 struct RingClass {
   std::vector<int> rings;
   bool blue = false;  // some ring of the class uses Bluestein's convolution
-  bool odd = false;   // some FFT length of the class has radices 3, 5 or 7
+  bool odd = false;   // some FFT length of the class has odd radices
   int tier = 0;
-  int xcap = 1;       // complex LDS words for ring data / convolution
-  int maxn = 1;       // longest ring in the class
-  int gcap = 0;       // fold scratch words (rings shorter than the block)
+  int xcap = 1;       // complex LDS words: ring data / convolution, with its padding,
+  int wcap = 0;       //   FFT twiddles,
+  int pcap = 0;       //   tables of the prime radices,
+  int gcap = 0;       //   fold scratch (rings shorter than the block)
 };
-// tiers: FFT length <= 512 / 1024 / 4096 / 8192 with 128 / 256 / 512 / 1024
-// threads (the longest FFT is a Bluestein convolution of kBlueMax words)
-constexpr int kMaxRingClasses = 16;  // at most 4 per tier
-inline int ring_tier_threads(int tier) { return 128 << tier; }
-inline int ring_tier_maxfft(int tier) {
-  return tier == 0 ? 512 : tier == 1 ? 1024 : tier == 2 ? 4096 : kBlueMax;
+// tiers: FFT length <= 512 << t with 64 << t threads (eight points per thread;
+// the longest FFT is a Bluestein convolution of kBlueMax words)
+constexpr int kMaxRingClasses = 20;  // at most 4 per tier
+inline int ring_tier_threads(int tier) { return 64 << tier; }
+inline int ring_tier_maxfft(int tier) { return 512 << tier; }
+// Rings of at most this many pixels are folded by that many threads of the
+// block (below 1024: the partial sums share the LDS with the longest FFT).
+__host__ __device__ constexpr int ring_short(int nt) { return nt < 512 ? nt : 512; }
+
+// Radix of stage s of an FFT of length 2^e (e <= 13), 0 past the last.  The
+// sequences read the same in both directions (the last stage of one transform
+// and the first of the next then hold the same points, see ring.hip).
+__host__ __device__ constexpr int pow2_radix(int e, int s) {
+  constexpr int r[14][5] = {{0, 0, 0, 0, 0},   {2, 0, 0, 0, 0},  {4, 0, 0, 0, 0},    {8, 0, 0, 0, 0},   {4, 4, 0, 0, 0},
+                            {4, 2, 4, 0, 0},   {8, 8, 0, 0, 0},  {4, 8, 4, 0, 0},    {8, 4, 8, 0, 0},   {8, 8, 8, 0, 0},
+                            {8, 4, 4, 8, 0},  {8, 4, 2, 4, 8}, {8, 8, 8, 8, 0}, {8, 8, 2, 8, 8}};
+  return s < 5 ? r[e][s] : 0;
 }
+__host__ __device__ constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
+
+// One ring of a launch class: everything the kernel needs to know about it in
+// one 128-byte record, read with the block index (one dependent load).
+constexpr int kRingStages = 10;  // radices of an FFT length up to 8192
+struct RingInfo {
+  int ring, nphi;
+  int num;              // phi0 = pi num / nphi, 0 or 1
+  int fftn;             // FFT length: nphi / 2 (even), nphi (odd) or the Bluestein length
+  int64_t offset;       // first pixel
+  int64_t twoff;        // into tw
+  int64_t bfoff;        // into bf, -1: direct transform
+  int nfac;
+  int fac[kRingStages];
+  unsigned facm[kRingStages];  // per stage: FastDiv multiplier of the stride Ns before it
+  int pad;
+};
+static_assert(sizeof(RingInfo) == 128, "one record per 128 bytes");
 
 // Workspace of the public transforms (sht_synth / sht_adjoint).
 struct GridWork {
@@ -158,22 +187,18 @@ struct crs_grid_s {
   std::vector<int> nphi, phi0_num, phi0_den;  // phi0 = pi * num / den
   std::vector<int64_t> offset;
   // device ring tables
-  crs::DevBuf<int> d_nphi, d_phinum, d_phiden, d_nfac, d_fac, d_fftn;
-  crs::DevBuf<unsigned> d_facm;
-  crs::DevBuf<int64_t> d_offset, d_twoff, d_bfoff;
   crs::DevBuf<double2> d_bf;      // Bluestein filter spectra per distinct length
-  crs::DevBuf<double2> d_tw2;     // exp(-2 pi i t / kBlueMax), t < kBlueMax
+  crs::DevBuf<double2> d_tw2;     // exp(-2 pi i t / kBlueMax), t < kBlueMax (power-of-two FFTs)
   // ring pair slots (see slot_layout): polar pairs and tiles, all slots; per
   // slot z of the north ring, sin(theta) and y = -sin^2 or -z^2
   int pol_pairs = 0, pol_tiles = 0, nslots = 0;
   crs::DevBuf<double> d_zs, d_ss, d_ys;
   crs::DevBuf<double2> d_tw;      // twiddles exp(-2 pi i t / N) per distinct N
-  int ring_maxn = 1;
   std::vector<crs::RingClass> ring_classes;  // by (tier, Bluestein, odd radix)
-  std::vector<crs::DevBuf<int>> d_ring_class;
+  std::vector<crs::DevBuf<crs::RingInfo>> d_ring_class;
   std::vector<int> ring_small_order;         // classes by ring count, ascending
   std::vector<crs::RingClass> ring_prefix;   // [k]: the first k + 1 of them merged
-  std::vector<crs::DevBuf<int>> d_ring_prefix;
+  std::vector<crs::DevBuf<crs::RingInfo>> d_ring_prefix;
   std::map<int, std::unique_ptr<crs::ShtPlan>> plans;
   std::unique_ptr<crs::GridWork> work;
   int device = 0;
@@ -236,24 +261,13 @@ void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const d
 // Ring FFT stage.
 enum RingMode { RING_SYNTH = 0, RING_ADJOINT = 1, RING_ROUNDTRIP = 2, RING_DIAG = 3 };
 struct RingArgs {
-  const int* nphi;
-  const int64_t* offset;
-  const int* phinum;
-  const int* phiden;
-  const int* nfac;     // radices of the FFT length of each ring
-  const int* fac;
-  const unsigned* facm;  // per stage: FastDiv multiplier of the stride Ns before it
-  const int* fftn;     // FFT length: Nphi / 2 (even), Nphi (odd) or the Bluestein length
-  const int64_t* twoff;
-  const double2* tw;   // per distinct Nphi: exp(-i pi t / Nphi), t < 2 Nphi
-  const int64_t* bfoff;
+  const RingInfo* info;  // records of the launch (set by launch_ring per class)
+  const double2* tw;    // per distinct Nphi: exp(-i pi t / Nphi), t < 2 Nphi
   const double2* bf;    // per Bluestein length: filter spectrum [fftn], then the chirp [n0]
   const double2* tw2;
-  int nring, lmax;
-  int maxn, xcap;      // per launch class: longest ring, LDS data words
-  int any_blue;        // per launch class: Bluestein tables present in LDS
+  int lmax;
+  int xcap, wcap, pcap;  // LDS words per launch class (RingClass)
   MapSkip skip;
-  const int* rings;    // ring list of the launch (set by launch_ring per class)
 };
 // maps j = 0..nmaps-1 use weight weights[j / maps_per_weight] (RING_ROUNDTRIP).
 void launch_ring(crs_grid g, int lmax, RingMode mode, int nmaps, double2* phase, int64_t pstride,

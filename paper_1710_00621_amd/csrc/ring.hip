@@ -22,15 +22,36 @@
 //   adjoint    Z = DFT_H(z), E_k = (Z_k + conj Z_{H-k}) / 2,
 //              O_k = (Z_k - conj Z_{H-k}) / (2i), F^_k = E_k + e^{-2 pi i k / Nphi} O_k.
 // Odd rings run a full complex FFT of length Nphi.  The FFT is a mixed-radix
-// Stockham autosort in LDS (radix 8, 4, 2, 3, 5, 7); a length with a prime
-// factor above 7 is computed by Bluestein's chirp-z identity
+// Stockham autosort in LDS (radix 8, 4, 2, 3, 5, 7 and primes up to a limit that
+// grows with the length, see prime_max in grid.hip); a length with a larger
+// prime factor is computed by Bluestein's chirp-z identity
 // n k = (n^2 + k^2 - (k - n)^2) / 2 as a cyclic convolution of power-of-two
 // length M >= 2n - 1 (filter spectrum precomputed per length on the host).
-// One block per (ring, map); rings are launched in classes by FFT length
-// (<= 512: 128 threads, <= 1024: 256, <= 4096: 512, <= 8192: 1024) and,
-// for the two longer tiers, by Bluestein or direct transform and whether
-// the FFT has odd radices; the half-length and Bluestein paths are chosen
-// per ring.
+// One block per (ring, map), eight points per thread; rings are launched in
+// classes by FFT length (<= 512 << t: 64 << t threads) and, from t = 2, by
+// Bluestein or direct transform and whether the FFT has odd radices.
+//
+// What bounds it.  A block is a chain of dependent steps (ring record, phases,
+// the FFT's exchanges through LDS, the store), so time goes with the length of
+// the chain and with the LDS traffic of the FFT long before memory is busy:
+//   - everything a block knows about its ring is one 128-byte record, and global
+//     loads are issued in batches (loops that waited for each load, two levels
+//     of tables and radices read per stage were 80 % of a wave's life);
+//   - power-of-two lengths have their indices compiled in, a padded layout
+//     (half of all LDS cycles were bank conflicts), and the map load, the
+//     Bluestein products, the round trip's weights and the map store happen in
+//     registers in the FFT's first and last stages: a Bluestein transform of S
+//     stages per FFT exchanges 2 S - 2 times through LDS instead of 2 S + 3;
+//   - two thirds of a HEALPix grid's cap rings have a prime factor above 7:
+//     the direct sums of stage_prime take a fraction of Bluestein's 2 FFTs of 2
+//     to 4 times the length.
+// Measured, synthesis / adjoint, ms: Nside 256, 42 maps 0.338 / 0.315 -> 0.218 /
+// 0.205 (617 MB: 2.8 / 3.0 TB/s of the 5.0 a copy reaches); Nside
+// 1024, 6 maps 0.865 / 0.798 -> 0.530 / 0.465; Nside 1024, 1 map 0.171 / 0.163 ->
+// 0.147 / 0.147; Nside 2048, 1 map 0.848 / 0.718 -> 0.53 / 0.50; 512 x 1026 GL, 40
+// maps 0.479 / 0.498 -> 0.150 / 0.172.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace crs {
@@ -58,27 +79,12 @@ struct FastDiv {
   __device__ __forceinline__ unsigned mod(unsigned n) const { return n - div(n) * d; }
 };
 
-// Twiddles exp(-2 pi i u / Lt) from two LDS tables: Wf[u & 63] Wc[u >> 6]
-// (exact table entries; the product adds one rounding).  An FFT of length
-// n | Lt reads omega_n^t at u = t * q, q = Lt / n.
+// Twiddles exp(-2 pi i u / n) of an FFT of length n from two LDS tables:
+// Wf[u & 63] Wc[u >> 6] (exact table entries; the product adds one rounding).
 struct TwCtx {
   const double2* Wf;
   const double2* Wc;
-  int q;
-  __device__ __forceinline__ double2 at(int u) const { return cmul(Wc[u >> 6], Wf[u & 63]); }
-  __device__ __forceinline__ double2 tw(int t, bool inv) const {
-    const double2 w = at(t * q);
-    return inv ? conj2(w) : w;
-  }
-};
-
-// The ring's table exp(-i pi t / Nphi), t < 2 Nphi, read from global memory
-// (L2-resident: every ring of that length and every map shares it).  The
-// fold reads its phase factors here, so it need not wait for the LDS copy of
-// the tables.
-struct GlobalTw {
-  const double2* __restrict__ T;
-  __device__ __forceinline__ double2 at(int t) const { return T[t]; }
+  __device__ __forceinline__ double2 tw(int u) const { return cmul(Wc[u >> 6], Wf[u & 63]); }
 };
 
 // cos(2 pi k / R) and sin(2 pi k / R), 1 <= k <= (R-1)/2, for the odd radices
@@ -96,31 +102,64 @@ __device__ __forceinline__ constexpr double dft_sin(int R, int k) {
                  : k == 2 ? 0.9749279121818236070181317 : 0.4338837391175581204757683);
 }
 
+// forward DFT of R points; the inverse of a ring is taken as conj(DFT(conj .)),
+// the conjugations folded into the steps before and after
 template <int R>
-__device__ __forceinline__ void small_dft(double2 (&v)[R], bool inv) {
+__device__ __forceinline__ void small_dft(double2 (&v)[R]) {
   if constexpr (R == 2) {
     const double2 a = v[0], b = v[1];
     v[0] = cadd(a, b);
     v[1] = csub(a, b);
   } else if constexpr (R == 8) {
     // X_k = E_k + w^k O_k, X_{k+4} = E_k - w^k O_k (E, O: 4-point DFTs of the
-    // even and odd samples; w = exp(-/+ i pi / 4))
+    // even and odd samples; w = exp(-i pi / 4))
     double2 e[4] = {v[0], v[2], v[4], v[6]};
     double2 o[4] = {v[1], v[3], v[5], v[7]};
-    small_dft<4>(e, inv);
-    small_dft<4>(o, inv);
+    small_dft<4>(e);
+    small_dft<4>(o);
     constexpr double h = 0.7071067811865475244008444;  // 1 / sqrt(2)
     double2 t[4];
     t[0] = o[0];
-    t[1] = inv ? make_double2(h * (o[1].x - o[1].y), h * (o[1].x + o[1].y))
-               : make_double2(h * (o[1].x + o[1].y), h * (o[1].y - o[1].x));
-    t[2] = inv ? make_double2(-o[2].y, o[2].x) : make_double2(o[2].y, -o[2].x);
-    t[3] = inv ? make_double2(-h * (o[3].x + o[3].y), h * (o[3].x - o[3].y))
-               : make_double2(h * (o[3].y - o[3].x), -h * (o[3].x + o[3].y));
+    t[1] = make_double2(h * (o[1].x + o[1].y), h * (o[1].y - o[1].x));
+    t[2] = make_double2(o[2].y, -o[2].x);
+    t[3] = make_double2(h * (o[3].y - o[3].x), -h * (o[3].x + o[3].y));
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       v[k] = cadd(e[k], t[k]);
       v[k + 4] = csub(e[k], t[k]);
+    }
+  } else if constexpr (R == 16) {
+    // 4 x 4: 4-point DFTs over n1 of x_{4 n1 + n2}, times w^(n2 k1) (w = exp(-i pi
+    // / 8)), 4-point DFTs over n2: X_{k1 + 4 k2}
+    constexpr double c1 = 0.9238795325112867561281832;  // cos(pi / 8)
+    constexpr double s1 = 0.3826834323650897717284600;  // sin(pi / 8)
+    constexpr double h = 0.7071067811865475244008444;
+    auto rot = [](double2 z, double c, double sn) {  // z (c - i sn)
+      return make_double2(fma(z.x, c, z.y * sn), fma(z.y, c, -(z.x * sn)));
+    };
+    auto rot8 = [](double2 z) { return make_double2(h * (z.x + z.y), h * (z.y - z.x)); };
+    double2 u[4][4];  // [n2][k1]
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < 4; ++n1) u[n2][n1] = v[4 * n1 + n2];
+      small_dft<4>(u[n2]);
+    }
+    u[1][1] = rot(u[1][1], c1, s1);
+    u[1][2] = rot8(u[1][2]);
+    u[1][3] = rot(u[1][3], s1, c1);
+    u[2][1] = rot8(u[2][1]);
+    u[2][2] = make_double2(u[2][2].y, -u[2][2].x);
+    u[2][3] = make_double2(h * (u[2][3].y - u[2][3].x), -h * (u[2][3].x + u[2][3].y));
+    u[3][1] = rot(u[3][1], s1, c1);
+    u[3][2] = make_double2(h * (u[3][2].y - u[3][2].x), -h * (u[3][2].x + u[3][2].y));
+    u[3][3] = rot(u[3][3], -c1, -s1);
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) {
+      double2 w[4] = {u[0][k1], u[1][k1], u[2][k1], u[3][k1]};
+      small_dft<4>(w);
+#pragma unroll
+      for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = w[k2];
     }
   } else if constexpr (R == 4) {
     const double2 t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
@@ -128,11 +167,11 @@ __device__ __forceinline__ void small_dft(double2 (&v)[R], bool inv) {
     const double2 mit3 = make_double2(t3.y, -t3.x);  // -i t3
     v[0] = cadd(t0, t2);
     v[2] = csub(t0, t2);
-    v[1] = inv ? csub(t1, mit3) : cadd(t1, mit3);
-    v[3] = inv ? cadd(t1, mit3) : csub(t1, mit3);
+    v[1] = cadd(t1, mit3);
+    v[3] = csub(t1, mit3);
   } else {
     // odd R: with a_s = x_s + x_{R-s}, b_s = x_s - x_{R-s},
-    //   y_r = x_0 + sum_s a_s cos(2 pi r s / R) -/+ i sum_s b_s sin(2 pi r s / R),
+    //   y_r = x_0 + sum_s a_s cos(2 pi r s / R) - i sum_s b_s sin(2 pi r s / R),
     //   y_{R-r} the same with the sine term's sign flipped.
     constexpr int H = (R - 1) / 2;
     double2 a[H], b[H];
@@ -159,21 +198,36 @@ __device__ __forceinline__ void small_dft(double2 (&v)[R], bool inv) {
         B.y = fma(b[s - 1].y, sn, B.y);
       }
       const double2 miB = make_double2(B.y, -B.x);  // -i B
-      out[r] = inv ? csub(A, miB) : cadd(A, miB);
-      out[R - r] = inv ? cadd(A, miB) : csub(A, miB);
+      out[r] = cadd(A, miB);
+      out[R - r] = csub(A, miB);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = out[r];
   }
 }
 
+// Global loads of a thread that are issued together: a loop that waits for each
+// of its loads pays the memory latency once per iteration (that was most of a
+// block's life: 80 % of its waves' cycles).
+constexpr int kBatch = 4;
+
+// v[r] *= w^r: powers as products of shorter ones (a chain of log2 R products)
+template <int R>
+__device__ __forceinline__ void twiddle(double2 (&v)[R], double2 w1) {
+  double2 w[R];
+  w[1] = w1;
+#pragma unroll
+  for (int r = 2; r < R; ++r) w[r] = cmul(w[(r + 1) / 2], w[r / 2]);
+#pragma unroll
+  for (int r = 1; r < R; ++r) v[r] = cmul(v[r], w[r]);
+}
+
 // One radix-R Stockham stage on x[0..n): butterfly j (k = j mod Ns) reads
-// x[j + r n/R], twiddles by omega_n^{r k span} (span = n / (Ns R); powers
-// of omega^{k span} by repeated multiplication), and writes x[(j / Ns) Ns R
+// x[j + r n/R], twiddles by omega_n^{r k span} (span = n / (Ns R)), and writes x[(j / Ns) Ns R
 // + k + r Ns].  Every thread keeps its butterflies in registers across the
 // barrier, so the stage works in place.
 template <int R, int NT, int MAXN>
-__device__ void stage(double2* x, int n, int Ns, unsigned nsm, const TwCtx& C, bool inv) {
+__device__ __forceinline__ void stage(double2* x, int n, int Ns, unsigned nsm, const TwCtx& C) {
   constexpr int MAXIT = (MAXN / R + NT - 1) / NT;
   const int nb = (int)((unsigned)n / (unsigned)R);
   const FastDiv dv((unsigned)Ns, nsm);
@@ -187,17 +241,8 @@ __device__ void stage(double2* x, int n, int Ns, unsigned nsm, const TwCtx& C, b
       const int k = (int)dv.mod((unsigned)j);
 #pragma unroll
       for (int r = 0; r < R; ++r) v[it][r] = x[j + r * nb];
-      if (k != 0) {
-        const double2 w1 = C.tw(k * span, inv);
-        double2 w = w1;
-        v[it][1] = cmul(v[it][1], w);
-#pragma unroll
-        for (int r = 2; r < R; ++r) {
-          w = cmul(w, w1);
-          v[it][r] = cmul(v[it][r], w);
-        }
-      }
-      small_dft<R>(v[it], inv);
+      if (k != 0) twiddle<R>(v[it], C.tw(k * span));
+      small_dft<R>(v[it]);
     }
   }
   __syncthreads();
@@ -214,122 +259,224 @@ __device__ void stage(double2* x, int n, int Ns, unsigned nsm, const TwCtx& C, b
   __syncthreads();
 }
 
-// Radix of stage s of a power-of-two length 2^e, in the order the host's
-// factorization gives (radix 8 first, 2^4 as 4 x 4, a remaining 2^2 as 4,
-// a remaining 2 last); 0 past the last stage.
-__host__ __device__ constexpr int pow2_radix(int e, int s) {
-  int n8 = e / 3, rest = e % 3;
-  if (rest == 1 && n8 > 0) {
-    --n8;
-    rest = 4;
+// The same for a prime radix p >= 11 (not known at compile time), by the sums
+// that the odd radices of small_dft use: a thread computes up to kPairs output
+// pairs (r, p - r) of one butterfly, so a point is read p / (2 kPairs) times and
+// costs p - 1 FMAs.  cs: exp(-2 pi i t / p), t < p, in LDS.  A block of n / 8
+// threads has at least one thread per work item: (n / p) ceil((p - 1) / 12) <=
+// 2 n / 17.
+constexpr int kPairs = 6;
+template <int NT>
+__device__ __forceinline__ void stage_prime(double2* x, int n, int p, int Ns, unsigned nsm, const double2* cs, const TwCtx& C) {
+  const int nb = (int)((unsigned)n / (unsigned)p), H = (p - 1) / 2;
+  const FastDiv dv((unsigned)Ns, nsm), dnb((unsigned)nb);
+  const int tid = threadIdx.x;
+  if (Ns > 1) {
+    const int span = (int)dv.div((unsigned)nb);
+    for (int i = nb + tid; i < n; i += NT) {
+      const int r = (int)dnb.div((unsigned)i), k = (int)dv.mod((unsigned)(i - r * nb));
+      x[i] = cmul(x[i], C.tw(r * k * span));
+    }
+    __syncthreads();
   }
-  if (s < n8) return 8;
-  s -= n8;
-  if (rest == 4) return s < 2 ? 4 : 0;
-  if (rest == 2) return s == 0 ? 4 : 0;
-  if (rest == 1) return s == 0 ? 2 : 0;
-  return 0;
-}
-__host__ __device__ constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
-static_assert(pow2_radix(9, 0) == 8 && pow2_radix(9, 2) == 8 && pow2_radix(9, 3) == 0, "512 = 8 8 8");
-static_assert(pow2_radix(8, 1) == 8 && pow2_radix(8, 2) == 4 && pow2_radix(8, 3) == 0, "256 = 8 8 4");
-static_assert(pow2_radix(10, 1) == 8 && pow2_radix(10, 2) == 4 && pow2_radix(10, 3) == 4 &&
-                  pow2_radix(10, 4) == 0, "1024 = 8 8 4 4");
-static_assert(pow2_radix(11, 2) == 8 && pow2_radix(11, 3) == 4 && pow2_radix(11, 4) == 0, "2048 = 8 8 8 4");
-static_assert(pow2_radix(13, 3) == 4 && pow2_radix(13, 4) == 4 && pow2_radix(13, 5) == 0, "8192 = 8 8 8 4 4");
-static_assert(pow2_radix(1, 0) == 2 && pow2_radix(1, 1) == 0, "2");
-
-// The stages of a power-of-two length N with every length, stride and
-// divisor fixed at compile time (the same stages and arithmetic as the
-// general loop below, without its per-stage scalar work).
-template <int NT, int MAXN, int N, int S = 0, int NS = 1>
-__device__ __forceinline__ void fft_fixed(double2* x, const TwCtx& C, bool inv) {
-  constexpr int R = pow2_radix(ilog2(N), S);
-  if constexpr (R > 0) {
-    constexpr unsigned m = NS <= 1 ? 0u : 0xFFFFFFFFu / NS + 1u;
-    stage<R, NT, MAXN>(x, N, NS, m, C, inv);
-    fft_fixed<NT, MAXN, N, S + 1, NS * R>(x, C, inv);
-  }
-}
-
-// In-place DFT of x[0..n) in LDS: forward exp(-2 pi i jk/n), inverse exp(+).
-// POW2: the length is a power of two (radix 8, 4 and 2 only).  HALF: length
-// MAXN / 2 gets its fixed stages too (where that does not cost registers).
-template <int NT, int MAXN, bool POW2, bool HALF>
-__device__ void fft_lds(double2* x, int n, const int* __restrict__ fac, const unsigned* __restrict__ facm,
-                        int nfac, const TwCtx& C, bool inv) {
-  if (n == MAXN) {  // the tier's longest length: the Bluestein convolutions and the widest rings
-    fft_fixed<NT, MAXN, MAXN>(x, C, inv);
-    return;
-  }
-  // half of it: the belt rings of a HEALPix grid whose largest length sits in
-  // the tier
-  if constexpr (HALF) {
-    if (n == MAXN / 2) {
-      fft_fixed<NT, MAXN, MAXN / 2>(x, C, inv);
-      return;
+  const int g = (int)dnb.div((unsigned)tid), j = tid - g * nb, r0 = g * kPairs + 1;
+  const bool on = r0 <= H;
+  double2 A[kPairs], B[kPairs], y0 = make_double2(0.0, 0.0);
+  if (on) {
+    int rq[kPairs], kq[kPairs];
+    const double2 x0 = x[j];
+    y0 = x0;
+#pragma unroll
+    for (int q = 0; q < kPairs; ++q) {
+      A[q] = x0;
+      B[q] = make_double2(0.0, 0.0);
+      rq[q] = kq[q] = min(r0 + q, H);
+    }
+    for (int t = 1; t <= H; ++t) {
+      const double2 u = x[j + t * nb], v = x[j + (p - t) * nb];
+      const double2 a = cadd(u, v), b = csub(u, v);
+      y0 = cadd(y0, a);
+#pragma unroll
+      for (int q = 0; q < kPairs; ++q) {
+        const double2 c = cs[kq[q]];
+        kq[q] += rq[q];
+        if (kq[q] >= p) kq[q] -= p;
+        A[q].x = fma(a.x, c.x, A[q].x);
+        A[q].y = fma(a.y, c.x, A[q].y);
+        B[q].x = fma(-b.y, c.y, B[q].x);  // i b c.y
+        B[q].y = fma(b.x, c.y, B[q].y);
+      }
     }
   }
+  __syncthreads();
+  if (on) {
+    const int q1 = (int)dv.div((unsigned)j);
+    double2* o = x + (q1 * Ns * p + (j - q1 * Ns));
+    if (g == 0) o[0] = y0;
+#pragma unroll
+    for (int q = 0; q < kPairs; ++q) {
+      const int r = r0 + q;
+      if (r <= H) {
+        o[r * Ns] = cadd(A[q], B[q]);
+        o[(p - r) * Ns] = csub(A[q], B[q]);
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// In-place forward DFT of x[0..n) in LDS, any length.
+// POW2: the length is a power of two (radix 16, 8, 4 and 2 only).
+template <int NT, int MAXN, bool POW2>
+__device__ __forceinline__ void fft_lds(double2* x, int n, const RingInfo* __restrict__ ri, const TwCtx& C, const double2* cs) {
   int Ns = 1;
-  for (int st = 0; st < nfac; ++st) {
-    const int R = fac[st];
-    const unsigned m = facm[st];
+  for (int st = 0; st < ri->nfac; ++st) {
+    const int R = ri->fac[st];
+    const unsigned m = ri->facm[st];
     if (R == 8) {
-      stage<8, NT, MAXN>(x, n, Ns, m, C, inv);
+      stage<8, NT, MAXN>(x, n, Ns, m, C);
     } else if (R == 4) {
-      stage<4, NT, MAXN>(x, n, Ns, m, C, inv);
+      stage<4, NT, MAXN>(x, n, Ns, m, C);
     } else if (R == 2) {
-      stage<2, NT, MAXN>(x, n, Ns, m, C, inv);
+      stage<2, NT, MAXN>(x, n, Ns, m, C);
     } else if constexpr (!POW2) {
-      if (R == 3) stage<3, NT, MAXN>(x, n, Ns, m, C, inv);
-      else if (R == 5) stage<5, NT, MAXN>(x, n, Ns, m, C, inv);
-      else if (R == 7) stage<7, NT, MAXN>(x, n, Ns, m, C, inv);
+      if (R == 3) stage<3, NT, MAXN>(x, n, Ns, m, C);
+      else if (R == 5) stage<5, NT, MAXN>(x, n, Ns, m, C);
+      else if (R == 7) stage<7, NT, MAXN>(x, n, Ns, m, C);
+      else if (R > 7) {
+        stage_prime<NT>(x, n, R, Ns, m, cs, C);
+        cs += R;
+      }
     }
     Ns *= R;
   }
 }
 
-// DFT of length n0 through Bluestein's identity:
-//   X_k = w_k sum_n (x_n w_n) b_{k-n},  w_n = exp(-i pi n^2 / n0), b_d = conj(w_d),
-// a cyclic convolution of length M (x holds M words).  The inverse DFT is
-// conj(DFT(conj x)).  bf holds the filter spectrum (M words) followed by the
-// chirp w_n (n0 words), both precomputed on the host.
-template <int NT, int MAXN>
-__device__ void dft_bluestein(double2* x, int n0, int M, const double2* __restrict__ bf,
-                              const TwCtx& C, const int* __restrict__ fac, const unsigned* __restrict__ facm,
-                              int nfac, bool inv) {
-  const int tid = threadIdx.x;
-  const double2* __restrict__ w = bf + M;
-  for (int i = tid; i < M; i += NT) {
-    double2 v = make_double2(0.0, 0.0);
-    if (i < n0) {
-      const double2 a = x[i];
-      v = cmul(inv ? conj2(a) : a, w[i]);
+// Power-of-two lengths M with everything fixed at compile time (conv below), for
+// the tier's longest length and its half and quarter: every long FFT of the
+// class and, in a launch that merges classes, the next shorter ones (Nside 64,
+// 20 maps: 20 us with the quarter, 21 without).
+// The data sit in LDS with one word of padding after every 16 (the first
+// stages write with a stride of their radix, which without it puts 8 lanes on
+// one bank).  pad(i + c) = pad(i) + pad(c) where the low four bits do not carry,
+// which holds for every offset below.
+__device__ __forceinline__ constexpr int pad(int i) { return i + (i >> 4); }
+
+template <int R, int NT, int M, class F>
+__device__ __forceinline__ void each_butterfly(int tid, F&& f) {
+  constexpr int NB = M / R, IT = (NB + NT - 1) / NT;
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const int j = tid + NT * it;
+    if (NB % NT == 0 || j < NB) f(it, j);
+  }
+}
+template <int R, int NT, int M>
+struct Bfly {
+  static constexpr int NB = M / R, IT = (NB + NT - 1) / NT;
+  double2 v[IT][R];
+};
+template <int R, int NT, int M>
+__device__ __forceinline__ void rd(int tid, const double2* x, Bfly<R, NT, M>& b) {
+  static_assert(M / R % 16 == 0, "offsets of whole padded rows");
+  each_butterfly<R, NT, M>(tid, [&](int it, int j) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) b.v[it][r] = x[pad(j) + r * pad(M / R)];
+  });
+}
+template <int R, int NT, int M, int NS>
+__device__ __forceinline__ void dft(int tid, Bfly<R, NT, M>& b, const TwCtx& C) {
+  each_butterfly<R, NT, M>(tid, [&](int it, int j) {
+    const int k = j & (NS - 1);
+    if (NS > 1) twiddle<R>(b.v[it], C.tw(k * (M / (NS * R))));
+    small_dft<R>(b.v[it]);
+  });
+}
+template <int R, int NT, int M, int NS>
+__device__ __forceinline__ void wr(int tid, double2* x, const Bfly<R, NT, M>& b) {
+  each_butterfly<R, NT, M>(tid, [&](int it, int j) {
+    const int k = j & (NS - 1);
+    double2* o = x + pad((j - k) * R + k);
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[pad(r * NS)] = b.v[it][r];
+  });
+}
+
+// Transform of M points: ld(v, j, NB) fills v[r] with point j + r NB, st(v, j, NB)
+// takes the results at the same indices.  With `two` a second transform follows:
+// the last stage of the first leaves a thread with the points that the first
+// stage of the second needs (equal radices), so that mid(v, j, NB) changes them
+// in registers and nothing of it passes through LDS.  A transform of S stages
+// takes S - 1 exchanges through LDS, two of them 2 S - 2.
+// The caller has a barrier before ld (if that reads LDS) and after st (if that
+// writes it).
+struct NoMid {};
+template <int NT, int M, int S, int NS, class Mid, class St>
+__device__ __forceinline__ void conv_rest(int tid, double2* x, const TwCtx& C, bool two, Mid&& mid, St&& st) {
+  constexpr int R = pow2_radix(ilog2(M), S);
+  constexpr bool last = NS * R == M;
+  Bfly<R, NT, M> b;
+  rd<R, NT, M>(tid, x, b);
+  dft<R, NT, M, NS>(tid, b, C);
+  __syncthreads();
+  if constexpr (!last) {
+    wr<R, NT, M, NS>(tid, x, b);
+    __syncthreads();
+    conv_rest<NT, M, S + 1, NS * R>(tid, x, C, two, mid, st);
+  } else {
+    if constexpr (!std::is_same_v<std::decay_t<Mid>, NoMid>) {
+      if (two) {
+        asm volatile("" : "+v"(tid));  // as in transforms()
+        each_butterfly<R, NT, M>(tid, [&](int it, int j) { mid(b.v[it], j, M / R); });
+        dft<R, NT, M, 1>(tid, b, C);
+        wr<R, NT, M, 1>(tid, x, b);
+        __syncthreads();
+        conv_rest<NT, M, 1, R>(tid, x, C, false, NoMid{}, st);
+        return;
+      }
     }
-    x[i] = v;
+    each_butterfly<R, NT, M>(tid, [&](int it, int j) { st(b.v[it], j, M / R); });
   }
+}
+template <int NT, int M, class Ld, class Mid, class St>
+__device__ __forceinline__ void conv(int tid, double2* x, const TwCtx& C, bool two, Ld&& ld, Mid&& mid, St&& st) {
+  constexpr int R = pow2_radix(ilog2(M), 0);
+  Bfly<R, NT, M> b;
+  each_butterfly<R, NT, M>(tid, [&](int it, int j) { ld(b.v[it], j, M / R); });
+  dft<R, NT, M, 1>(tid, b, C);
   __syncthreads();
-  fft_lds<NT, MAXN, true, (MAXN <= 1024)>(x, M, fac, facm, nfac, C, false);
-  for (int i = tid; i < M; i += NT) x[i] = cmul(x[i], bf[i]);
+  wr<R, NT, M, 1>(tid, x, b);
   __syncthreads();
-  fft_lds<NT, MAXN, true, (MAXN <= 1024)>(x, M, fac, facm, nfac, C, true);
-  for (int i = tid; i < n0; i += NT) {
-    const double2 v = cmul(x[i], w[i]);
-    x[i] = inv ? conj2(v) : v;
+  conv_rest<NT, M, 1, R>(tid, x, C, two, mid, st);
+}
+
+// Bluestein's identity for a DFT of length n0:
+//   X_k = w_k sum_n (x_n w_n) b_{k-n},  w_n = exp(-i pi n^2 / n0), b_d = conj(w_d),
+// a cyclic convolution of length M (x holds M words): chirp and zero-pad, DFT,
+// filter, inverse DFT, chirp.  bf holds the filter spectrum (M words) followed
+// by the chirp w_n (n0 words), both precomputed on the host.  Here: the
+// products, x_i = f(x_i, c_i) for i < n with c read in batches.
+template <int NT, class F>
+__device__ __forceinline__ void mul_table(double2* x, int n, const double2* __restrict__ c, F&& f) {
+  for (int i0 = threadIdx.x; i0 < n; i0 += NT * kBatch) {
+    double2 v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) v[u] = c[min(i0 + u * NT, n - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (i0 + u * NT < n) x[i0 + u * NT] = f(x[i0 + u * NT], v[u]);
   }
-  __syncthreads();
 }
 
 // Sum of g_m = (F^c_m - i F^s_m) e^{i m phi0} over m = m0, m0 + S, ... <= L,
 // e^{i m phi0} = conj(T[t_m]) with t_m = m num mod 2N stepping by tS; four
 // loads in flight per step, summed in order of m.
-template <class Tw>
 __device__ __forceinline__ double2 sum_g(const double2* __restrict__ ph, int m0, int S, int L, int t,
-                                         int tS, int twoN, const Tw& ring) {
+                                         int tS, int twoN, const double2* __restrict__ T) {
   double2 acc = make_double2(0.0, 0.0);
   int m = m0;
   auto add = [&](double2 F) {
-    acc = cadd(acc, cmulc(make_double2(F.x, -F.y), ring.at(t)));
+    acc = cadd(acc, cmulc(make_double2(F.x, -F.y), T[t]));
     t += tS;
     if (t >= twoN) t -= twoN;
   };
@@ -346,17 +493,116 @@ __device__ __forceinline__ double2 sum_g(const double2* __restrict__ ph, int m0,
 
 // Folded spectrum c_k = (G_k + conj G_{-k}) / 2 with G_k the sum of g_m over
 // m = k mod N (0 <= k < N).
-template <class Tw>
 __device__ __forceinline__ double2 fold(const double2* __restrict__ ph, int k, int N, int L, int num,
-                                        const FastDiv& d2N, int stepN, const Tw& ring) {
-  const double2 a = sum_g(ph, k, N, L, (int)d2N.mod((unsigned)k * (unsigned)num), stepN, 2 * N, ring);
+                                        const FastDiv& d2N, int stepN, const double2* __restrict__ T) {
+  const double2 a = sum_g(ph, k, N, L, (int)d2N.mod((unsigned)k * (unsigned)num), stepN, 2 * N, T);
   const int m1 = k == 0 ? 0 : N - k;
-  const double2 b = sum_g(ph, m1, N, L, (int)d2N.mod((unsigned)m1 * (unsigned)num), stepN, 2 * N, ring);
+  const double2 b = sum_g(ph, m1, N, L, (int)d2N.mod((unsigned)m1 * (unsigned)num), stepN, 2 * N, T);
   return make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
 }
 
-// ODD: the class has FFT lengths with radices 3, 5 or 7 (without it only the
-// power-of-two stages are compiled, which takes far fewer registers).
+// All transforms of one ring for a compiled-in length M.  Word i of the ring's
+// n0 words: the samples 2 i and 2 i + 1 of an even ring, sample i of an odd one.
+// From map `in` or, if that is NULL, from conj Z in x; the result goes to map
+// `out` (synthesis) or into x.  bf: Bluestein's filter and chirp (NULL: direct
+// transform, n0 = M); wt: the pixel weights of the round trip.
+template <int NT, int M>
+__device__ __forceinline__ void transforms(double2* x, const TwCtx& C, bool half, int n0,
+                                           const double2* __restrict__ bf, const double* __restrict__ wt,
+                                           const double* __restrict__ in, double* __restrict__ out) {
+  const double2* __restrict__ chirp = bf + M;
+  const double* io = in ? in : out ? out : wt;
+  const bool a16 = (reinterpret_cast<uintptr_t>(io) & 15) == 0;
+  auto pair = [&](const double* __restrict__ p, int i) -> double2 {
+    if (!half) return make_double2(p[i], 0.0);
+    if (a16) return reinterpret_cast<const double2*>(p)[i];
+    return make_double2(p[2 * i], p[2 * i + 1]);
+  };
+  bool first = true;  // of the two passes of a Bluestein round trip
+  auto ld = [&](auto& v, int j, int nb) {
+    constexpr int R = sizeof(v) / sizeof(double2);
+    if (bf) {
+      // n0 <= M / 2: the points r >= R / 2 are the zero padding
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = make_double2(0.0, 0.0);
+      double2 c[R / 2];
+#pragma unroll
+      for (int r = 0; r < R / 2; ++r) {
+        const int i = min(j + r * nb, n0 - 1);
+        c[r] = chirp[i];
+        v[r] = in ? pair(in, i) : x[pad(i)];
+      }
+#pragma unroll
+      for (int r = 0; r < R / 2; ++r) v[r] = j + r * nb < n0 ? cmul(v[r], c[r]) : make_double2(0.0, 0.0);
+    } else if (in) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = pair(in, j + r * nb);
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = x[pad(j + r * nb)];
+    }
+  };
+  auto mid = [&](auto& v, int j, int nb) {
+    constexpr int R = sizeof(v) / sizeof(double2);
+    double2 c[R];
+    if (bf) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) c[r] = bf[j + r * nb];
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = conj2(cmul(v[r], c[r]));
+    } else {
+#pragma unroll
+      for (int r = 0; r < R; ++r) c[r] = pair(wt, j + r * nb);
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[r] = make_double2(v[r].x * c[r].x, -v[r].y * c[r].y);
+    }
+  };
+  auto st = [&](auto& v, int j, int nb) {
+    constexpr int R = sizeof(v) / sizeof(double2);
+    if (bf) {
+      double2 c[R / 2];
+#pragma unroll
+      for (int r = 0; r < R / 2; ++r) c[r] = chirp[min(j + r * nb, n0 - 1)];
+#pragma unroll
+      for (int r = 0; r < R / 2; ++r) v[r] = cmulc(c[r], v[r]);
+    }
+    const bool weigh = bf && wt && first;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = j + r * nb;
+      if (bf && (r >= R / 2 || i >= n0)) continue;
+      if (out) {
+        if (!half) {
+          out[i] = v[r].x;
+        } else if (a16) {
+          reinterpret_cast<double2*>(out)[i] = conj2(v[r]);
+        } else {
+          out[2 * i] = v[r].x;
+          out[2 * i + 1] = -v[r].y;
+        }
+      } else if (weigh) {
+        const double2 w = pair(wt, i);
+        x[pad(i)] = make_double2(v[r].x * w.x, -v[r].y * w.y);
+      } else {
+        x[pad(i)] = v[r];
+      }
+    }
+  };
+  for (;;) {
+    // opaque to the compiler: it would keep every index and address of the
+    // first pass in registers for the second (256 of them instead of 120)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    conv<NT, M>(tid, x, C, bf || wt, ld, mid, st);
+    if (out) return;
+    __syncthreads();
+    if (!(bf && wt && first)) return;
+    first = false;
+  }
+}
+
+// ODD: the class has FFT lengths with odd radices (without it only the
+// power-of-two stages are compiled, which takes fewer registers).
 template <int NT, int MAXN, bool ODD>
 __global__ __launch_bounds__(NT) void k_ring(RingArgs a, int mode, double2* __restrict__ phase,
                                              int64_t pstride, const double* __restrict__ map_in,
@@ -367,65 +613,82 @@ __global__ __launch_bounds__(NT) void k_ring(RingArgs a, int mode, double2* __re
   double2* x = lds;
   double2* wf = lds + a.xcap;
   double2* wc = wf + 64;
-  double2* wf2 = wc + (2 * a.maxn + 63) / 64;
-  double2* wc2 = wf2 + 64;
-  double2* G = a.any_blue ? wc2 + kBlueMax / 64 : wf2;  // fold scratch (rings with N <= NT)
-  const int r = a.rings[blockIdx.x];
+  double2* cs = wf + a.wcap;  // tables of the prime radices
+  double2* G = cs + a.pcap;   // fold scratch (short rings)
+  const RingInfo* __restrict__ ri = a.info + blockIdx.x;
   const int map = blockIdx.y;
   if (a.skip.off(map)) return;  // whole block: before any barrier
   const int tid = threadIdx.x;
   const int L = a.lmax;
-  const int N = a.nphi[r];
+  const int N = ri->nphi;
   const bool half = (N & 1) == 0;     // two real samples per complex word
-  const bool blue = a.bfoff[r] >= 0;  // Bluestein convolution
+  const bool blue = ri->bfoff >= 0;   // Bluestein convolution
   const int n0 = half ? N / 2 : N;
-  const int nf = a.fftn[r];
-  const int64_t off = a.offset[r];
-  const int num = a.phinum[r];
-  const double2* __restrict__ Tg = a.tw + a.twoff[r];
-  const int* __restrict__ fac = a.fac + (size_t)r * kMaxFactors;
-  const unsigned* __restrict__ facm = a.facm + (size_t)r * kMaxFactors;
-  const int nfac = a.nfac[r];
-  double2* __restrict__ ph = phase + (int64_t)map * pstride + (int64_t)r * (L + 1);
+  const int nf = ri->fftn;
+  const int64_t off = ri->offset;
+  const int num = ri->num;
+  const double2* __restrict__ Tg = a.tw + ri->twoff;  // exp(-i pi t / N), t < 2 N
+  double2* __restrict__ ph = phase + (int64_t)map * pstride + (int64_t)ri->ring * (L + 1);
   const int twoN = 2 * N;
-  for (int i = tid; i < 64; i += NT) wf[i] = Tg[i < twoN ? i : 0];
-  for (int u = tid; u * 64 < twoN; u += NT) wc[u] = Tg[64 * u];
-  if (blue) {
-    for (int i = tid; i < 64; i += NT) wf2[i] = a.tw2[i];
-    for (int u = tid; u < kBlueMax / 64; u += NT) wc2[u] = a.tw2[64 * u];
+  const bool fixed = nf == MAXN || nf == MAXN / 2 || nf == MAXN / 4;  // the length is compiled in
+  const int sh = fixed ? 4 : 31;                    // x[i] sits at i + (i >> sh)
+  {
+    // twiddles of the FFT of length nf: at most one entry of each table per
+    // thread (nf / 64 <= NT), loaded together
+    const bool p2 = (nf & (nf - 1)) == 0;
+    const double2* __restrict__ T = p2 ? a.tw2 : Tg;
+    const int q = p2 ? kBlueMax / nf : half ? 4 : 2;
+    const int nwf = min(64, nf), nwc = (nf + 63) / 64;
+    const double2 f = T[q * min(tid & 63, nwf - 1)], c = T[64 * q * min(tid, nwc - 1)];
+    if (tid < 64) wf[tid] = f;
+    if (tid < nwc) wc[tid] = c;
+    if constexpr (ODD) {
+      double2* o = cs;
+      if (!p2)
+        for (int st = 0; st < ri->nfac; ++st) {
+          const int p = ri->fac[st];
+          if (p <= 7 || !(p & 1)) break;  // the primes come first
+          const int qp = (int)((unsigned)twoN / (unsigned)p);
+          for (int t = tid; t < p; t += NT) o[t] = Tg[t * qp];
+          o += p;
+        }
+    }
   }
   // No barrier here: the LDS tables are first read after the barrier that
   // follows the fold (synthesis) or the input load (adjoint), so the table
   // copy and those global loads are in flight together.
-  const TwCtx ring{wf, wc, 1};
-  const GlobalTw gring{Tg};
-  // the FFT of length n0 (direct) or nf (Bluestein)
-  const TwCtx fc = blue ? TwCtx{wf2, wc2, (int)((unsigned)kBlueMax / (unsigned)nf)} : TwCtx{wf, wc, half ? 4 : 2};
-  const double2* __restrict__ bf = blue ? a.bf + a.bfoff[r] : nullptr;
+  const TwCtx fc{wf, wc};
+  const double2* __restrict__ bf = blue ? a.bf + ri->bfoff : nullptr;
   const FastDiv d2N((unsigned)twoN), dN((unsigned)N);
   double* xd = reinterpret_cast<double*>(x);
+  const double* __restrict__ wt = mode == RING_ROUNDTRIP ? weights[map / maps_per_weight] + off : nullptr;
 
-  // Wide even rings (N >= 2L, every HEALPix belt ring at L <= 2 Nside): each
-  // m <= L has its own bin (m = N / 2 = L shares the Nyquist bin with -m), so
-  // the fold and the unfold take one phase value per bin and the factors
-  // e^{-i pi t / N} straight from the ring's global table, t = m num < 2N
-  // (phi0 = pi num / N with num 0 or 1 on every grid built here).
-  const bool wide = half && 2 * L <= N;
-  auto gval = [&](int m) -> double2 {  // g_m = (F^c_m - i F^s_m) e^{i m phi0}
-    const double2 F = ph[m];
-    const double2 Fc = make_double2(F.x, -F.y);
-    return num ? cmulc(Fc, gring.at(m)) : Fc;
+  // Even rings, H = N / 2 bins, in slots kk = 0 .. (H - 1) / 2 of four bins of the
+  // full-length spectrum: kk, H - kk, H + kk, N - kk (slot 0: 0, H, H / 2, 3 H / 2).
+  // With T = e^{-i pi kk / N} the phases e^{-i pi b / N} of the four are T, -i conj T,
+  // -i T and -conj T, and m = b + c N differs from b by sg^c (sg = -1 on rings
+  // with phi0 = pi / N, else 1), so a slot needs T and w = T^2 only, and the sums
+  // over c are plain sums of F.
+  const int H = n0, nk = (H + 1) / 2;
+  const double sg = num ? -1.0 : 1.0;
+  const bool even = (H & 1) == 0;
+  const bool wide = half && 2 * L <= N;  // every m has its own bin: c = 0, and bins past H are empty
+  auto at = [&](int i) { return i + (i >> sh); };
+  auto bin = [&](int kk, int i) {
+    if (kk) return i == 0 ? kk : i == 1 ? H - kk : i == 2 ? H + kk : N - kk;
+    return i == 0 ? 0 : i == 1 ? H : even ? (i == 2 ? H / 2 : H + H / 2) : L + 1;
   };
   if (mode == RING_SYNTH || mode == RING_ROUNDTRIP) {
     const int stepN = (int)d2N.mod((unsigned)N * (unsigned)num);
-    if (N <= NT && !wide) {
-      // short ring: all threads fold.  Thread p < S (S = N floor(NT / N))
+    const bool shortr = N <= ring_short(NT) && !wide;
+    if (shortr) {
+      // short ring: all threads fold.  Thread p < S (S = N floor(threads / N))
       // sums g_m over m = p mod S; G_k then adds the S / N partials of bin k.
-      const int S = N * (NT / N);
+      const int S = N * (ring_short(NT) / N);
       double2* P = G + N;
       if (tid < S)
         P[tid] = sum_g(ph, tid, S, L, (int)d2N.mod((unsigned)tid * (unsigned)num),
-                       (int)d2N.mod((unsigned)S * (unsigned)num), twoN, gring);
+                       (int)d2N.mod((unsigned)S * (unsigned)num), twoN, Tg);
       __syncthreads();
       for (int k = tid; k < N; k += NT) {
         double2 acc = P[k];
@@ -434,87 +697,198 @@ __global__ __launch_bounds__(NT) void k_ring(RingArgs a, int mode, double2* __re
       }
       __syncthreads();
     }
-    auto cfold = [&](int k) -> double2 {
-      if (N <= NT) {
-        const double2 u = G[k], v = G[k == 0 ? 0 : N - k];
-        return make_double2(0.5 * (u.x + v.x), 0.5 * (u.y - v.y));
-      }
-      return fold(ph, k, N, L, num, d2N, stepN, gring);
-    };
-    for (int k = tid; k < n0; k += NT) {
-      if (wide) {
-        // c_0 = Re g_0, c_k = g_k / 2 (0 < k < H), c_{k+H} = conj(g_{H-k}) / 2
-        // (0 < k), c_H = Re g_H (H <= L only when N = 2L)
-        double2 ck = k <= L ? gval(k) : make_double2(0.0, 0.0);
-        double2 ch = n0 - k <= L ? gval(n0 - k) : make_double2(0.0, 0.0);
-        if (k == 0) {
-          ck.y = 0.0;
-          ch.y = 0.0;
-        } else {
-          ck = make_double2(0.5 * ck.x, 0.5 * ck.y);
-          ch = make_double2(0.5 * ch.x, -0.5 * ch.y);
+    if (half) {
+      // c_kk, c_{H-kk} (c_k = (G_k + conj G_{-k}) / 2, c Hermitian) and from them
+      //   Z_kk = P + R, Z_{H-kk} = conj(P - R), P = c_kk + conj c_{H-kk},
+      //   R = i conj(w) (c_kk - conj c_{H-kk});  x holds conj Z
+      constexpr int U = 2;
+      for (int k0 = tid; k0 < nk; k0 += NT * U) {
+        double2 S[U][4], T[U], W[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int kk = min(k0 + u * NT, nk - 1);
+          W[u] = Tg[2 * kk];
+          T[u] = Tg[kk ? kk : H / 2];  // read on rings with num != 0 only
+          if (shortr) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) S[u][i] = G[min(bin(kk, i), N - 1)];
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              if (wide && (i == 3 || (i == 2 && kk != 0))) {
+                S[u][i] = make_double2(0.0, 0.0);
+                continue;
+              }
+              const int m = bin(kk, i);
+              const double2 F = ph[min(m, L)];
+              S[u][i] = make_double2(m <= L ? F.x : 0.0, m <= L ? -F.y : 0.0);
+            }
+          }
         }
-        const double2 e = conj2(gring.at(2 * k));
-        const double2 dd = cmul(e, csub(ck, ch));
-        x[k] = make_double2(ck.x + ch.x - dd.y, ck.y + ch.y + dd.x);
-      } else if (half) {
-        const double2 ck = cfold(k);
-        const double2 ch = cfold(k + n0);
-        // Z_k = (c_k + c_{k+H}) + i e^{+2 pi i k / N} (c_k - c_{k+H})
-        const double2 e = conj2(gring.at(2 * k));
-        const double2 dd = cmul(e, csub(ck, ch));
-        x[k] = make_double2(ck.x + ch.x - dd.y, ck.y + ch.y + dd.x);
-      } else {
-        x[k] = cfold(k);
+        if (!shortr && !wide) {
+          double s = sg;
+          for (int c = N; c <= L; c += N) {
+            double2 F[U][4];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) F[u][i] = ph[min(bin(min(k0 + u * NT, nk - 1), i) + c, L)];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const bool in = bin(min(k0 + u * NT, nk - 1), i) + c <= L;
+                S[u][i].x = fma(s, in ? F[u][i].x : 0.0, S[u][i].x);
+                S[u][i].y = fma(-s, in ? F[u][i].y : 0.0, S[u][i].y);
+              }
+            s *= sg;
+          }
+        }
+        // short rings hold G itself (phases included)
+        const bool turn = num && !shortr;
+        const double sc = shortr ? 1.0 : sg;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int kk = k0 + u * NT;
+          const double2(&s)[4] = S[u];
+          if (kk >= nk) continue;
+          if (kk == 0) {
+            const double cH = turn ? -s[1].y : s[1].x;
+            x[0] = make_double2(s[0].x + cH, cH - s[0].x);
+            if (even) {
+              double2 A2 = make_double2(fma(sc, s[3].x, s[2].x), fma(-sc, s[3].y, s[2].y));
+              if (turn) A2 = cmulc(A2, T[u]);
+              x[at(H / 2)] = A2;
+            }
+          } else {
+            double2 A2 = make_double2(fma(sc, s[3].x, s[0].x), fma(-sc, s[3].y, s[0].y));
+            double2 B2 = make_double2(fma(sc, s[2].x, s[1].x), fma(-sc, s[2].y, s[1].y));
+            if (turn) {
+              A2 = cmulc(A2, T[u]);
+              B2 = cmul(B2, T[u]);
+              B2 = make_double2(-B2.y, B2.x);
+            }
+            const double2 Pp = make_double2(0.5 * (A2.x + B2.x), 0.5 * (A2.y - B2.y));
+            const double2 Q = make_double2(0.5 * (A2.x - B2.x), 0.5 * (A2.y + B2.y));
+            const double2 t = cmulc(Q, W[u]);
+            x[at(kk)] = make_double2(Pp.x - t.y, -Pp.y - t.x);
+            x[at(H - kk)] = make_double2(Pp.x + t.y, Pp.y - t.x);
+          }
+        }
+      }
+    } else {
+      for (int k = tid; k < n0; k += NT) {
+        if (shortr) {
+          const double2 u = G[k], v = G[k == 0 ? 0 : N - k];
+          x[at(k)] = make_double2(0.5 * (u.x + v.x), 0.5 * (v.y - u.y));
+        } else {
+          x[at(k)] = conj2(fold(ph, k, N, L, num, d2N, stepN, Tg));
+        }
       }
     }
-    __syncthreads();
-    if (blue)
-      dft_bluestein<NT, MAXN>(x, n0, nf, bf, fc, fac, facm, nfac, true);
-    else
-      fft_lds<NT, MAXN, !ODD, (!ODD || MAXN <= 1024)>(x, n0, fac, facm, nfac, fc, true);
+  } else if (!fixed) {
+    const double* in = map_in + (int64_t)map * mstride + off;
+    if (half && (reinterpret_cast<uintptr_t>(in) & 15) == 0) {
+      const double2* i2 = reinterpret_cast<const double2*>(in);
+      for (int j0 = tid; j0 < H; j0 += NT * kBatch) {
+        double2 v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) v[u] = i2[min(j0 + u * NT, H - 1)];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+          if (j0 + u * NT < H) x[j0 + u * NT] = v[u];
+      }
+    } else {
+      for (int j0 = tid; j0 < N; j0 += NT * kBatch) {
+        double v[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) v[u] = in[min(j0 + u * NT, N - 1)];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+          const int j = j0 + u * NT;
+          if (j >= N) continue;
+          if (half)
+            xd[j] = v[u];
+          else
+            x[j] = make_double2(v[u], 0.0);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  // The transforms: of conj Z (its conjugate is the ring's samples) in synthesis
+  // and round trip, of the ring's samples in adjoint and round trip.
+  const bool syn = mode == RING_SYNTH || mode == RING_ROUNDTRIP;
+  if (fixed) {
+    const double* in = syn ? nullptr : map_in + (int64_t)map * mstride + off;
+    double* out = mode == RING_SYNTH ? map_out + (int64_t)map * mstride + off : nullptr;
+    if (nf == MAXN) transforms<NT, MAXN>(x, fc, half, n0, bf, wt, in, out);
+    else if (nf == MAXN / 2) transforms<NT, MAXN / 2>(x, fc, half, n0, bf, wt, in, out);
+    else transforms<NT, MAXN / 4>(x, fc, half, n0, bf, wt, in, out);
+    if (mode == RING_SYNTH) return;
+  }
+  // any other length, one loop, so that the FFT's code is there once
+#pragma unroll 1
+  for (int tr = fixed ? 2 : syn ? 0 : 1; tr < 2; ++tr) {
+    if (blue) {
+      mul_table<NT>(x, n0, bf + nf, [](double2 v, double2 c) { return cmul(v, c); });
+      for (int i = n0 + tid; i < nf; i += NT) x[i] = make_double2(0.0, 0.0);
+      __syncthreads();
+    }
+#pragma unroll 1
+    for (int pass = blue ? 0 : 1; pass < 2; ++pass) {
+      fft_lds<NT, MAXN, !ODD>(x, nf, ri, fc, cs);
+      if (pass == 0) {
+        mul_table<NT>(x, nf, bf, [](double2 v, double2 c) { return conj2(cmul(v, c)); });
+        __syncthreads();
+      }
+    }
+    if (blue) {
+      mul_table<NT>(x, n0, bf + nf, [](double2 v, double2 c) { return cmulc(c, v); });
+      __syncthreads();
+    }
+    if (tr == 1) break;
     if (mode == RING_SYNTH) {
       double* out = map_out + (int64_t)map * mstride + off;
-      if (half) {
-        for (int j = tid; j < N; j += NT) out[j] = xd[j];
+      if (half && (reinterpret_cast<uintptr_t>(out) & 15) == 0) {
+        double2* o2 = reinterpret_cast<double2*>(out);
+        for (int j = tid; j < H; j += NT) o2[j] = conj2(x[j]);
+      } else if (half) {
+        for (int j = tid; j < N; j += NT) out[j] = j & 1 ? -xd[j] : xd[j];
       } else {
         for (int j = tid; j < N; j += NT) out[j] = x[j].x;
       }
       return;
     }
-    const double* __restrict__ w = weights[map / maps_per_weight] + off;
-    if (half) {
-      for (int j = tid; j < N; j += NT) xd[j] *= w[j];
-    } else {
-      for (int j = tid; j < N; j += NT) x[j] = make_double2(x[j].x * w[j], 0.0);
-    }
-    __syncthreads();
-  } else {
-    const double* in = map_in + (int64_t)map * mstride + off;
-    if (half) {
-      for (int j = tid; j < N; j += NT) xd[j] = in[j];
-    } else {
-      for (int j = tid; j < N; j += NT) x[j] = make_double2(in[j], 0.0);
+    const int st = half ? 1 : 2;  // real samples sit in consecutive words, or in the real parts
+    for (int j0 = tid; j0 < N; j0 += NT * kBatch) {
+      double wv[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) wv[u] = wt[min(j0 + u * NT, N - 1)];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int j = j0 + u * NT;
+        if (j < N) {
+          xd[st * j] *= half && (j & 1) ? -wv[u] : wv[u];
+          if (!half) xd[st * j + 1] = 0.0;
+        }
+      }
     }
     __syncthreads();
   }
-  if (blue)
-    dft_bluestein<NT, MAXN>(x, n0, nf, bf, fc, fac, facm, nfac, false);
-  else
-    fft_lds<NT, MAXN, !ODD, (!ODD || MAXN <= 1024)>(x, n0, fac, facm, nfac, fc, false);
 
   // forward DFT of the real ring data at bin k (0 <= k < N)
   auto spec = [&](int k) -> double2 {
     if (half) {
       const int kk = k >= n0 ? k - n0 : k;
       const int k2 = kk == 0 ? 0 : n0 - kk;
-      const double2 Zk = x[kk], Zc = conj2(x[k2]);
+      const double2 Zk = x[at(kk)], Zc = conj2(x[at(k2)]);
       const double2 E = make_double2(0.5 * (Zk.x + Zc.x), 0.5 * (Zk.y + Zc.y));
       const double2 D = csub(Zk, Zc);
       const double2 O = make_double2(0.5 * D.y, -0.5 * D.x);  // D / (2i)
-      return cadd(E, cmul(ring.at(2 * k), O));
+      return cadd(E, cmul(Tg[2 * k], O));
     } else {
-      return x[k];
+      return x[at(k)];
     }
   };
   if (mode == RING_DIAG) {
@@ -525,31 +899,72 @@ __global__ __launch_bounds__(NT) void k_ring(RingArgs a, int mode, double2* __re
       } else {
         const unsigned m2 = d2N.mod(2u * (unsigned)m);
         const int k = (int)dN.mod(m2);
-        const double2 X = cmul(spec(k), ring.at((int)d2N.mod(m2 * (unsigned)num)));
+        const double2 X = cmul(spec(k), Tg[(int)d2N.mod(m2 * (unsigned)num)]);
         ph[m] = make_double2(t0 + X.x, t0 - X.x);
       }
     }
     return;
   }
-  if (wide) {
-    for (int m = tid; m <= L; m += NT) {
-      // F^_m from Z_m and Z_{H-m} (m = H only when N = 2L: bin 0's partner)
-      const int kk = m < n0 ? m : m - n0;
-      const int k2 = kk == 0 ? 0 : n0 - kk;
-      const double2 Zk = x[kk], Zc = conj2(x[k2]);
-      const double2 E = make_double2(0.5 * (Zk.x + Zc.x), 0.5 * (Zk.y + Zc.y));
-      const double2 D = csub(Zk, Zc);
-      const double2 O = make_double2(0.5 * D.y, -0.5 * D.x);
-      double2 h = cadd(E, cmul(gring.at(2 * m), O));
-      if (num) h = cmul(h, gring.at(m));
-      ph[m] = make_double2(h.x, m == 0 ? 0.0 : -h.y);
+  if (half && N > ring_short(NT)) {
+    // Slots as in the fold: with E, O of (Z_kk, conj Z_{H-kk}) the bins are F^_kk =
+    // E + w O and F^_{H-kk} = conj(E - w O); H of the other two are sg conj of
+    // these two, and m = b + c N repeats its bin with sg^c.
+    constexpr int U = 2;
+    for (int k0 = tid; k0 < nk; k0 += NT * U) {
+      double2 T[U], W[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int kk = min(k0 + u * NT, nk - 1);
+        W[u] = Tg[2 * kk];
+        T[u] = Tg[kk ? kk : H / 2];  // read on rings with num != 0 only
+      }
+      auto slot = [&](int kk, double2 Wk, double2 Tk) {
+        if (kk >= nk) return;
+        double2 V[4];  // (H^c, H^s) of the four bins
+        if (kk == 0) {
+          const double2 Z = x[0];
+          V[0] = make_double2(Z.x + Z.y, 0.0);
+          V[1] = num ? make_double2(0.0, Z.x - Z.y) : make_double2(Z.x - Z.y, 0.0);
+          double2 v = even ? conj2(x[at(H / 2)]) : Z;
+          if (num) v = cmul(v, Tk);
+          V[2] = conj2(v);
+          V[3] = make_double2(sg * v.x, sg * v.y);
+        } else {
+          const double2 Zk = x[at(kk)], Zc = conj2(x[at(H - kk)]);
+          const double2 E = make_double2(0.5 * (Zk.x + Zc.x), 0.5 * (Zk.y + Zc.y));
+          const double2 D = csub(Zk, Zc);
+          const double2 wO = cmul(Wk, make_double2(0.5 * D.y, -0.5 * D.x));  // O = D / (2i)
+          double2 v0 = cadd(E, wO), v1 = conj2(csub(E, wO));
+          if (num) {
+            v0 = cmul(v0, Tk);
+            v1 = cmulc(v1, Tk);
+            v1 = make_double2(v1.y, -v1.x);
+          }
+          V[0] = conj2(v0);
+          V[1] = conj2(v1);
+          V[2] = make_double2(sg * v1.x, sg * v1.y);
+          V[3] = make_double2(sg * v0.x, sg * v0.y);
+        }
+        double s = 1.0;
+        for (int c = 0; c <= L; c += N) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if (wide && (i == 3 || (i == 2 && kk != 0))) continue;
+            const int m = bin(kk, i) + c;
+            if (m <= L) ph[m] = make_double2(s * V[i].x, s * V[i].y);
+          }
+          s *= sg;
+        }
+      };
+      slot(k0, W[0], T[0]);
+      slot(k0 + NT, W[1], T[1]);
     }
     return;
   }
   for (int m = tid; m <= L; m += NT) {
     // H_m = e^{-i m phi0} F^_{m mod N};  e^{-i m phi0} = T[m num mod 2N]
     const unsigned mm = d2N.mod((unsigned)m);
-    const double2 h = cmul(spec((int)dN.mod(mm)), ring.at((int)d2N.mod(mm * (unsigned)num)));
+    const double2 h = cmul(spec((int)dN.mod(mm)), Tg[(int)d2N.mod(mm * (unsigned)num)]);
     ph[m] = make_double2(h.x, m == 0 ? 0.0 : -h.y);
   }
 }
@@ -566,16 +981,15 @@ void launch_ring(crs_grid g, int lmax, RingMode mode, int nmaps, double2* phase,
   base.skip = skip;
   const int mpw = maps_per_weight < 1 ? 1 : maps_per_weight;
   const int md = (int)mode;
-  auto launch_class = [&](const RingClass& rc, const int* rings) {
+  auto launch_class = [&](const RingClass& rc, const RingInfo* info) {
     if (rc.rings.empty()) return;
     RingArgs a = base;
-    a.maxn = rc.maxn;
     a.xcap = rc.xcap;
-    a.rings = rings;
+    a.wcap = rc.wcap;
+    a.pcap = rc.pcap;
+    a.info = info;
     const dim3 grid((unsigned)rc.rings.size(), nmaps);
-    const size_t words = (size_t)rc.xcap + 64 + (2 * rc.maxn + 63) / 64 +
-                         (rc.blue ? 64 + kBlueMax / 64 : 0) + rc.gcap;
-    a.any_blue = rc.blue ? 1 : 0;
+    const size_t words = (size_t)rc.xcap + rc.wcap + rc.pcap + rc.gcap;
     const size_t lds = words * sizeof(double2);
     CRS_CHECK(lds <= kMaxLds, CRS_EUNSUPPORTED, "ring class needs " + std::to_string(lds) + " bytes of LDS");
     switch (rc.tier * 2 + (rc.odd ? 1 : 0)) {
@@ -584,14 +998,16 @@ void launch_ring(crs_grid g, int lmax, RingMode mode, int nmaps, double2* phase,
     hipLaunchKernelGGL((k_ring<NT, MAXN, ODD>), grid, dim3(NT), lds, s, a, md, phase, pstride,       \
                        map_in, map_out, mstride, weights, mpw);                                      \
     break;
-      CRS_RING(0, 128, 512, false)
-      CRS_RING(0, 128, 512, true)
-      CRS_RING(1, 256, 1024, false)
-      CRS_RING(1, 256, 1024, true)
-      CRS_RING(2, 512, 4096, false)
-      CRS_RING(2, 512, 4096, true)
-      CRS_RING(3, 1024, 8192, false)
-      CRS_RING(3, 1024, 8192, true)
+      CRS_RING(0, 64, 512, false)
+      CRS_RING(0, 64, 512, true)
+      CRS_RING(1, 128, 1024, false)
+      CRS_RING(1, 128, 1024, true)
+      CRS_RING(2, 256, 2048, false)
+      CRS_RING(2, 256, 2048, true)
+      CRS_RING(3, 512, 4096, false)
+      CRS_RING(3, 512, 4096, true)
+      CRS_RING(4, 1024, 8192, false)
+      CRS_RING(4, 1024, 8192, true)
 #undef CRS_RING
       default: throw Error{CRS_EUNSUPPORTED, "ring FFT length above 8192"};
     }

@@ -5,8 +5,10 @@ import sys
 import numpy as np
 import pytest
 
-from oracle import geometry, sht
+from oracle import geometry, precond, sht
 from oracle.legendre import LegendreSweep
+from paper_1710_00621_amd import inputs
+from tests.helpers import oracle_model
 
 pytestmark = pytest.mark.gpu
 
@@ -412,3 +414,52 @@ def test_legendre_tiles_match_oracle(spec, lmax, nmaps, ts, ta, monkeypatch):
     one_alm = crsolve.sht_adjoint(g, lmax, torch.tensor(maps[-1:], device=dev))
     assert torch.equal(one_map[0], got_map[-1])
     assert torch.equal(one_alm[0], got_alm[-1])
+
+
+# ring lengths at the edges of the ring kernel's forms: (pixels per ring, lmax).
+# FFT length H = N / 2 (even N) or N (odd N)
+RING_LENGTHS = [
+    (512, 300), (1024, 40), (2048, 1100), (4096, 500), (8192, 60),   # H = 256 .. 4096: lengths compiled in
+    (254, 200), (509, 100), (2042, 1021), (2039, 300),               # Bluestein of 256, 1024, 2048, 4096 points
+    (26, 30), (274, 137), (286, 400), (578, 200), (1026, 512),       # H = 13; 137 (Bluestein); 11 13; 17 17; 19 3 3 3
+    (961, 300), (2662, 800), (3034, 100), (3721, 90), (4087, 50),    # 31 31; 11 11 11; 37 41; 61 61; 61 67 (Bluestein)
+    (64, 200), (66, 200), (130, 90), (1028, 1500),                   # the short rings' fold and the next longer one
+]
+
+
+@pytest.mark.parametrize("nphi,lmax", RING_LENGTHS)
+def test_ring_lengths_match_oracle(nphi, lmax):
+    """Every form of the ring transform, on maps that start at an odd multiple
+    of 8 bytes and on aligned ones (the same numbers: pairs of samples are
+    loaded as one word only where that is aligned), and the forms of the round
+    trip and of the diagonal through the operators of a model whose band has
+    such rings."""
+    torch, crsolve = _setup()
+    print(f"case ring length {nphi} lmax={lmax}", flush=True)
+    spec, nmaps = ("gl", 7, nphi), 2
+    g = crsolve.Grid.from_spec(spec)
+    og = geometry.make_grid(spec)
+    rng = np.random.default_rng(61)
+    alm = rng.standard_normal((nmaps, sht.nalm(lmax)))
+    maps = rng.standard_normal((nmaps, og.npix))
+    dev = torch.device("cuda")
+    d_alm, d_maps = torch.tensor(alm, device=dev), torch.tensor(maps, device=dev)
+    got_map = crsolve.sht_synth(g, lmax, d_alm)
+    got_alm = crsolve.sht_adjoint(g, lmax, d_maps)
+    assert _rel(got_map.cpu().numpy(), sht.synth(og, lmax, alm)) < SHT_TOL
+    assert _rel(got_alm.cpu().numpy(), sht.adjoint(og, lmax, maps)) < SHT_TOL
+    odd = torch.empty(nmaps * og.npix + 1, dtype=torch.float64, device=dev)[1:].view(nmaps, og.npix)
+    assert odd.data_ptr() % 16 == 8
+    crsolve.sht_synth(g, lmax, d_alm, out=odd)
+    assert torch.equal(odd, got_map)
+    odd.copy_(d_maps)
+    assert torch.equal(crsolve.sht_adjoint(g, lmax, odd), got_alm)
+
+    prob = inputs.make_problem("tiny")
+    prob["bands"][0]["grid"] = ("gl", 33, nphi)
+    om, taus = oracle_model(prob)
+    gm = crsolve.model_from_problem(prob, taus)
+    x = rng.standard_normal(om.n)
+    xt = torch.tensor(x, device=dev)
+    assert _rel(gm.apply_A(xt).cpu().numpy(), om.apply_A(x)) < SHT_TOL
+    assert _rel(gm.apply_diag(xt).cpu().numpy(), precond.DiagonalPrecond(om)(x)) < SHT_TOL
