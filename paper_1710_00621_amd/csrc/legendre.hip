@@ -621,6 +621,7 @@ __global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = mb * 4 + wave;
   if (m > a.lmax) return;
+  map0 += blockIdx.y * NM;
   const int ns = leg_nslots(a, nmaps);
   if (!leg_any(a, map0, NM, ns)) return;
   const TileRange tr = tile_range<T>(a, tg);
@@ -820,12 +821,16 @@ __global__ __launch_bounds__(256) void k_leg_adj_sq(LegArgs a, const double2* __
 //   Nside 1024 / L 2000 x1 0.84  / 0.56  / 0.52    1.09  / 0.82  / 0.76    (64032)
 //   Nside 1024 / L 2000 x4 1.27  / 1.15            3.63  / 2.64  / 2.29
 //   Nside 256 / L 512 x42  0.346 / 0.366           1.04  / 0.89  / 0.86
-// so the rules take the largest T that leaves 8192 waves (synthesis) or 4096
-// (adjoint).  The autotuner replaces them per shape.
-static int largest_t(long tiles, int L, int tmax, long groups, long want) {
+//   Nside 512 / L 1024 x4  0.216 / 0.221           0.312 / 0.305 / 0.274
+//   Nside 256 / L 512 x6                           0.143 / 0.128 / 0.157
+//   Nside 256 / L 512 x15                          0.337 / 0.281 / 0.296
+// so the rules take the largest T that leaves 8192 waves (synthesis; 16384 from
+// three maps on, whose waves run longer) or 4096 (adjoint; 6144 for T = 4).
+// The autotuner replaces them per shape.
+static int largest_t(long tiles, int L, int tmax, long groups, long want2, long want4) {
   for (int T : {4, 2}) {
     if (T > tmax || T >= 2 * tiles) continue;
-    if ((long)(L + 1) * ((tiles + T - 1) / T) * groups >= want) return T;
+    if ((long)(L + 1) * ((tiles + T - 1) / T) * groups >= (T == 4 ? want4 : want2)) return T;
   }
   return 1;
 }
@@ -835,11 +840,50 @@ static int largest_t(long tiles, int L, int tmax, long groups, long want) {
 static int syn_tmax(int nmaps) { return nmaps == 1 ? 4 : nmaps <= 4 ? 2 : 1; }
 constexpr int kAdjTmax = 4;
 
+// waves of a launch with one tile and one group of maps per wave
+static long leg_waves(int npairs, int L) { return (long)(L + 1) * ((npairs + 63) / 64); }
+
+// Maps of the adjoint: n16 groups of four on the 16-column kernel, then groups of
+// nm on the per-map kernel.  Four or three maps per wave cost the same per map
+// where the waves fill the GPU (Nside 1024 / L 2000: 1515 and 1138 us), so that
+// any count from six on splits exactly; few waves are a matter of latency,
+// and there the maps spread over more, shorter ones.  Measured (us, the
+// Legendre kernel alone up to Nside 128, else the whole transform; groups of
+// 1 / 2 / 3 maps / of four, a remainder padded or on its own kernel):
+//   Nside 16 / L 32 x6        8.0 /   9.4 /  10.7 /  11.0   (   33 waves per group)
+//   Nside 64 / L 128 x12     13.7 /  15.4 /  18.3 /  21.1   (  258)
+//   Nside 64 / L 128 x16     18.5 /  16.8 /  18.8 /  22.6
+//   Nside 128 / L 256 x8     32.3 /  29.6 /  31.6 /  34.7   ( 1028)
+//   Nside 128 / L 256 x20              91 /    95 /    96
+//   Nside 256 / L 512 x5              129 /   123 /   142   ( 4104)
+//   Nside 256 / L 512 x10             200 /   206 /   214
+//   Nside 256 / L 512 x16             217 /   212 /   199   (kernel alone)
+//   Nside 256 / L 512 x42             736 /   738 /   743
+//   Nside 512 / L 1024 x6             636 /   591 /   634   (16400)
+//   Nside 512 / L 1024 x10           1016 /  1041 /   997
+//   Nside 1024 / L 2000 x6           3593 /  3081 /  3232   (64032)
+//   Nside 1024 / L 2000 x7           4495 /  4198 /  3880
+struct AdjGroups {
+  int n16, nm;  // groups of four, then groups of nm maps (0: none)
+};
+static AdjGroups adj_groups(int npairs, int L, int nmaps) {
+  const long w = leg_waves(npairs, L);
+  if (nmaps == 1 || w * nmaps <= 4096) return {0, 1};
+  if (nmaps == 2 || w * ((nmaps + 1) / 2) <= 5200) return {0, 2};
+  if (nmaps % 3 == 0 || (nmaps == 5 && w < 32768)) return {0, 3};
+  if (nmaps % 4 == 0 && w >= 2048) return {nmaps / 4, 0};
+  if (w < 16384) return {0, 2};
+  if (nmaps == 5) return {1, 1};
+  return {nmaps / 4 - (3 - nmaps % 4), 3};  // nmaps = 4 n16 + 3 (4 - nmaps % 4)
+}
+
 static LegChoice default_choice(int npairs, int L, int nmaps) {
   LegChoice c;
   const long tiles = (npairs + 63) / 64;
-  c.syn_t = largest_t(tiles, L, syn_tmax(nmaps), 1, 8192);
-  c.adj_t = largest_t(tiles, L, kAdjTmax, std::max(1, nmaps / 4), 4096);
+  c.syn_t = largest_t(tiles, L, syn_tmax(nmaps), 1, nmaps >= 3 ? 16384 : 8192, 8192);
+  const AdjGroups g = adj_groups(npairs, L, nmaps);
+  const int rest = nmaps - 4 * g.n16;
+  c.adj_t = largest_t(tiles, L, kAdjTmax, g.n16 + (g.nm ? (rest + g.nm - 1) / g.nm : 0), 4096, 6144);
   return c;
 }
 
@@ -885,16 +929,35 @@ void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const dou
     hipLaunchKernelGGL((k_leg_syn<G16, G4, TT>), dim3(leg_blocks(a.lmax, ntg), (nmaps + per - 1) / per), \
                        dim3(256), 0, s, a, nmaps, u, ustride, phase, pstride, ntg);                   \
   } while (0)
-  // up to eight maps: one wave carries exactly nmaps; more: eight per wave, the
-  // last group's second half skipped when it is empty
-  switch (std::min(nmaps, 9)) {
-    case 1: if (c.syn_t == 4) CRS_SYN(0, 1, 4); else if (c.syn_t == 2) CRS_SYN(0, 1, 2); else CRS_SYN(0, 1, 1); break;
-    case 2: if (c.syn_t == 2) CRS_SYN(0, 2, 2); else CRS_SYN(0, 2, 1); break;
-    case 3: if (c.syn_t == 2) CRS_SYN(0, 3, 2); else CRS_SYN(0, 3, 1); break;
-    case 4: if (c.syn_t == 2) CRS_SYN(1, 0, 2); else CRS_SYN(1, 0, 1); break;
-    case 5: CRS_SYN(1, 1, 1); break;
-    case 6: CRS_SYN(1, 2, 1); break;
-    default: CRS_SYN(2, 0, 1); break;
+  // Large launches carry up to eight maps per wave: the recurrence is shared.
+  // Few waves are a matter of latency: one map per wave while all of them are in
+  // flight together, then four.  Measured (us, 1 / 4 / up to 8 maps per wave):
+  //   Nside 16 / L 32 x6         7.0 /   9.2 /  11.4   (   33 waves per group)
+  //   Nside 64 / L 128 x12      14.0 /  15.3 /  18.4   (  258)
+  //   Nside 64 / L 128 x24      22.3 /  17.9 /  20.2
+  //   Nside 128 / L 256 x3      18.9 /  20.1 /  19.9   ( 1028)
+  //   Nside 128 / L 256 x8      33.7 /  24.1 /  27.9
+  //   Nside 256 / L 512 x5      98.6 /  76.9 /  54.4   ( 4104)
+  //   Nside 256 / L 512 x12      217 /  99.7 /   102
+  //   Nside 512 / L 1024 x9     1006 /   548 /   576   (16400)
+  //   Nside 512 / L 1024 x16    1782 /   737 /   697
+  // Three maps on one tile run as four, one of them empty (Nside 256: 40 us
+  // instead of 52; Nside 512: 176 and 185).
+  const long w = leg_waves(a.npairs, a.lmax);
+  if (nmaps > 1 && c.syn_t == 1 && w * nmaps <= 4096) {
+    CRS_SYN(0, 1, 1);
+  } else if (nmaps > 4 && (w * ((nmaps + 3) / 4) <= 4608 || (nmaps > 8 && nmaps <= 12))) {
+    CRS_SYN(1, 0, 1);
+  } else {
+    switch (nmaps) {
+      case 1: if (c.syn_t == 4) CRS_SYN(0, 1, 4); else if (c.syn_t == 2) CRS_SYN(0, 1, 2); else CRS_SYN(0, 1, 1); break;
+      case 2: if (c.syn_t == 2) CRS_SYN(0, 2, 2); else CRS_SYN(0, 2, 1); break;
+      case 3: if (c.syn_t == 2) CRS_SYN(0, 3, 2); else CRS_SYN(1, 0, 1); break;
+      case 4: if (c.syn_t == 2) CRS_SYN(1, 0, 2); else CRS_SYN(1, 0, 1); break;
+      case 5: CRS_SYN(1, 1, 1); break;
+      case 6: CRS_SYN(1, 2, 1); break;
+      default: CRS_SYN(2, 0, 1); break;
+    }
   }
 #undef CRS_SYN
   CRS_HIP(hipGetLastError());
@@ -915,20 +978,13 @@ void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const d
     CRS_HIP(hipGetLastError());
     return;
   }
-  // groups of four maps on the 16-column kernel; a remainder of one or two
-  // maps takes the per-map kernel where that saves columns worth a launch (up
-  // to ten maps), otherwise the last group runs partly empty.  Lists of active
-  // maps are formed on the device: their remainder is not known here.
-  int g16 = nmaps <= 3 ? 0 : nmaps / 4, rest = nmaps - 4 * g16;
-  if (g16 > 0 && rest > 0 && (rest == 3 || nmaps > 10 || a.mlist)) {
-    ++g16;
-    rest = 0;
-  }
+  const AdjGroups g = adj_groups(a.npairs, a.lmax, nmaps);
+  const int g16 = g.n16;
 #define CRS_ADJ16(TT)                                                                                 \
   hipLaunchKernelGGL((k_leg_adj16<TT>), dim3(nb, g16), dim3(256), 0, s, a, nmaps, phase, pstride,     \
                      vpart, vstride, tstride, ntg)
 #define CRS_ADJ4(N, TT)                                                                               \
-  hipLaunchKernelGGL((k_leg_adj4<N, TT>), dim3(nb), dim3(256), 0, s, a, nmaps, 4 * g16, phase,        \
+  hipLaunchKernelGGL((k_leg_adj4<N, TT>), dim3(nb, (nmaps - 4 * g16 + N - 1) / N), dim3(256), 0, s, a, nmaps, 4 * g16, phase,        \
                      pstride, vpart, vstride, tstride, ntg)
 #define CRS_ADJ4T(N)                                                                                  \
   do {                                                                                                \
@@ -941,9 +997,9 @@ void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const d
     else if (c.adj_t == 2) CRS_ADJ16(2);
     else CRS_ADJ16(1);
   }
-  if (rest == 1) CRS_ADJ4T(1);
-  else if (rest == 2) CRS_ADJ4T(2);
-  else if (rest == 3) CRS_ADJ4T(3);
+  if (g.nm == 1) CRS_ADJ4T(1);
+  else if (g.nm == 2) CRS_ADJ4T(2);
+  else if (g.nm == 3) CRS_ADJ4T(3);
 #undef CRS_ADJ16
 #undef CRS_ADJ4
 #undef CRS_ADJ4T

@@ -463,3 +463,27 @@ def test_ring_lengths_match_oracle(nphi, lmax):
     xt = torch.tensor(x, device=dev)
     assert _rel(gm.apply_A(xt).cpu().numpy(), om.apply_A(x)) < SHT_TOL
     assert _rel(gm.apply_diag(xt).cpu().numpy(), precond.DiagonalPrecond(om)(x)) < SHT_TOL
+
+
+@pytest.mark.parametrize("nside,lmax,nmaps", [
+    (16, 32, 6), (32, 64, 70), (64, 128, 16), (64, 128, 41),        # 1 map per wave; then 2 (adjoint) and 4 or 8
+    (128, 256, 5), (128, 256, 9), (128, 256, 12), (128, 256, 16),   # 4 / 8 maps; groups of 2 and of 3
+    (256, 512, 5), (256, 512, 7), (256, 512, 10),                   # 5 = 3 + 2; odd remainder of pairs; 9 .. 12 maps
+    (512, 1024, 5), (512, 1024, 7), (512, 1024, 10), (512, 1024, 13),  # fours and threes: 4 + 3, 4 + 6, 4 + 9
+])
+def test_map_groups_match_single_maps(nside, lmax, nmaps):
+    """How the maps of a transform are grouped onto waves depends on their
+    number and on the size; each map's result does not.  Rounding only: rings
+    shorter than a block fold with another block size, and one map may run on
+    another number of ring tiles per wave."""
+    torch, crsolve = _setup()
+    print(f"case map groups nside={nside} lmax={lmax} nmaps={nmaps}", flush=True)
+    g = crsolve.Grid.healpix(nside)
+    gen = torch.Generator(device="cpu").manual_seed(67)
+    alm = torch.randn(nmaps, (lmax + 1) ** 2, generator=gen, dtype=torch.float64).to("cuda")
+    maps = torch.randn(nmaps, g.npix, generator=gen, dtype=torch.float64).to("cuda")
+    got_map, got_alm = crsolve.sht_synth(g, lmax, alm), crsolve.sht_adjoint(g, lmax, maps)
+    for j in range(nmaps):
+        one_map, one_alm = crsolve.sht_synth(g, lmax, alm[j:j + 1]), crsolve.sht_adjoint(g, lmax, maps[j:j + 1])
+        assert float((one_map[0] - got_map[j]).abs().max() / one_map.abs().max()) < 1e-13, j
+        assert float((one_alm[0] - got_alm[j]).abs().max() / one_alm.abs().max()) < 1e-13, j
