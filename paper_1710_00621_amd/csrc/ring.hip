@@ -1017,12 +1017,24 @@ void launch_ring(crs_grid g, int lmax, RingMode mode, int nmaps, double2* phase,
   // blocks would leave most CUs idle for a whole block's duration: the
   // classes with fewer than kMinClassBlocks blocks (the first `nsmall` in
   // order of ring count) run together as one launch, the others on their own.
-  constexpr int64_t kMinClassBlocks = 1024;
+  // Where that launch's blocks are small (up to 256 threads) it takes further
+  // classes up to kMergedBlocks blocks, which all fit on the GPU in two or
+  // three turns.  Ring stage in us, separate / merged: Nside 256 x2 30.7 / 22.8,
+  // x4 40.9 / 33.3, x6 47.1 / 43.9, x8 53.1 / 54.2; Nside 512 x1 45.1 / 35.2, x2 65.0 /
+  // 58.0, x3 84.2 / 81.4, x4 100 / 104; with blocks of 512 threads Nside 1024 x1 147 /
+  // 171, x2 202 / 279.
+  constexpr int64_t kMinClassBlocks = 1024, kMergedBlocks = 6144;
+  constexpr int kMergedTier = 2;
   const int ncls = (int)g->ring_classes.size();
   int nsmall = 0;
-  while (nsmall < ncls &&
-         (int64_t)g->ring_classes[g->ring_small_order[nsmall]].rings.size() * nmaps < kMinClassBlocks)
+  while (nsmall < ncls) {
+    const RingClass& m = g->ring_prefix[nsmall];
+    const int64_t own = (int64_t)g->ring_classes[g->ring_small_order[nsmall]].rings.size() * nmaps;
+    if (own >= kMinClassBlocks &&
+        (m.tier > kMergedTier || (int64_t)m.rings.size() * nmaps >= kMergedBlocks))
+      break;
     ++nsmall;
+  }
   bool small[kMaxRingClasses] = {};
   for (int k = 0; k < nsmall; ++k) small[g->ring_small_order[k]] = true;
   for (int c = 0; c < ncls; ++c)
