@@ -389,13 +389,14 @@ int crs_batch_solve(crs_batch b, int mode, const double* const* const* d, const 
  * flags. */
 int crs_batch_stats(crs_batch b, int* out);
 /* Runs the batch's transform groups (the bands sharing a grid and
- * band-limit) on up to nstreams HIP streams (1..8; default 1, or the
- * environment variable CRS_GROUP_STREAMS at creation): the groups of one
- * operator application are independent until the back-mix (eq:A sums over
- * bands), so their launches may overlap, forked from and joined back into the
- * solve's stream by events (graph edges inside the captured chunks).  The
- * extra streams have the default priority and are created here; results do
- * not depend on nstreams.  CRS_EINVAL outside 1..8. */
+ * band-limit) on up to nstreams HIP streams (1..8; without this call the
+ * environment variable CRS_GROUP_STREAMS at creation or, without that, 3 where
+ * the groups are large enough and 1 while kernel statistics are taken): the
+ * groups of one operator application are independent until the back-mix (eq:A
+ * sums over bands), so their launches may overlap, forked from and joined back
+ * into the solve's stream by events (graph edges inside the captured chunks).
+ * The extra streams have the default priority; results do not depend on
+ * nstreams.  CRS_EINVAL outside 1..8. */
 int crs_batch_set_streams(crs_batch b, int nstreams);
 
 /* ------------------------------------------------------------- profiling

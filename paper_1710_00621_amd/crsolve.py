@@ -482,7 +482,8 @@ class Batch:
         return xs, {"status": st, "iters": list(iters), "relres": list(rel)}
 
     def set_streams(self, n):
-        """Run the transform groups on up to n HIP streams (1..8)."""
+        """Run the transform groups on up to n HIP streams (1..8; without this
+        call the library chooses by size)."""
         check(lib().crs_batch_set_streams(self._h, int(n)))
 
     def stats(self):

@@ -661,6 +661,26 @@ int64_t exec_plan_bytes(const std::vector<crs_model>& models, int nrhs) {
   return bytes;
 }
 
+// side streams (and their events) for n streams in all
+static void side_streams(Exec& e, int n) {
+  const int want = std::min<int>(n, (int)e.groups.size()) - 1;
+  while ((int)e.side.size() < want) {
+    hipStream_t t = nullptr;
+    CRS_HIP(hipStreamCreateWithFlags(&t, hipStreamNonBlocking));
+    e.side.push_back(t);
+    hipEvent_t ev = nullptr;
+    CRS_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    e.join.push_back(ev);
+  }
+  if (!e.side.empty() && !e.fork) CRS_HIP(hipEventCreateWithFlags(&e.fork, hipEventDisableTiming));
+}
+
+// streams in use now (while kernels are profiled the groups run one after
+// another unless a count was set: durations of concurrent kernels overlap)
+static int streams_now(const Exec& e) {
+  return e.nstreams > 0 ? e.nstreams : prof_enabled() ? 1 : e.auto_streams;
+}
+
 std::unique_ptr<Exec> make_exec(const std::vector<crs_model>& models, int nrhs, hipStream_t s, bool autotune) {
   CRS_CHECK(!models.empty() && nrhs >= 1, CRS_EINVAL, "no systems");
   {
@@ -861,7 +881,21 @@ std::unique_ptr<Exec> make_exec(const std::vector<crs_model>& models, int nrhs, 
   e->hrows.alloc((size_t)kChunk * e->nsys);
   e->live.assign(e->groups.size(), 1);
   CRS_HIP(hipStreamSynchronize(s));
-  if (const char* v = std::getenv("CRS_GROUP_STREAMS")) exec_set_streams(*e, std::atoi(v));
+  // Streams of the groups.  One group rarely fills the GPU: its Legendre and
+  // ring launches end in tails and the small bands' are too short to fill it at
+  // all.  Below kConcurrentTriples in the largest group the host's launches
+  // bound an application, and events between streams add to them.  A on 1 / 2 /
+  // 3 / 4 streams, us (multires bands divided by 8, 4, 2, 1; one vector): 78 / 95 /
+  // 105 / 96, 91 / 89 / 102 / 93 (1.1e6 triples), 127 / 107 / 114 / 95 (8.5e6), 219 / 186 /
+  // 170 / 175; batch of 12, 24 iterations: 20.0 / 17.8 / 16.7 / 17.2 ms.
+  constexpr int64_t kConcurrentTriples = 4000000;
+  constexpr int kConcurrentStreams = 3;
+  int64_t most = 0;
+  for (const ExecGroup& g : e->groups) most = std::max<int64_t>(most, g.plan->fp64_triples);
+  if (const char* v = std::getenv("CRS_GROUP_STREAMS"))
+    exec_set_streams(*e, std::atoi(v));
+  else if (e->groups.size() > 1 && most >= kConcurrentTriples)
+    e->auto_streams = kConcurrentStreams;  // created by the first application that runs outside a capture
   return e;
 }
 
@@ -892,16 +926,7 @@ Work3 group_work(const Exec& e, int gi, int family, bool masked, bool pi) {
 
 void exec_set_streams(Exec& e, int n) {
   CRS_CHECK(n >= 1 && n <= kMaxGroupStreams, CRS_EINVAL, "stream count out of range");
-  const int want = std::min<int>(n, (int)e.groups.size()) - 1;
-  while ((int)e.side.size() < want) {
-    hipStream_t t = nullptr;
-    CRS_HIP(hipStreamCreateWithFlags(&t, hipStreamNonBlocking));
-    e.side.push_back(t);
-    hipEvent_t ev = nullptr;
-    CRS_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    e.join.push_back(ev);
-  }
-  if (!e.side.empty() && !e.fork) CRS_HIP(hipEventCreateWithFlags(&e.fork, hipEventDisableTiming));
+  side_streams(e, n);
   e.nstreams = n;
 }
 
@@ -924,7 +949,8 @@ void exec_bands(Exec& e, OpKind kind, const double* in, hipStream_t s0, const do
   }
   // groups in order of work over the caller's stream and the side streams
   // (each to the least loaded one)
-  const int nstr = std::min({e.nstreams, 1 + (int)e.side.size(), (int)run.size()});
+  if (!cap) side_streams(e, streams_now(e));
+  const int nstr = std::min({streams_now(e), 1 + (int)e.side.size(), (int)run.size()});
   std::vector<int64_t> load(nstr, 0);
   std::vector<hipStream_t> gstream(e.groups.size(), s0);
   if (nstr > 1) {
@@ -932,14 +958,17 @@ void exec_bands(Exec& e, OpKind kind, const double* in, hipStream_t s0, const do
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
       return e.groups[a].plan->fp64_triples * e.groups[a].nmaps > e.groups[b].plan->fp64_triples * e.groups[b].nmaps;
     });
-    CRS_HIP(hipEventRecord(e.fork, s0));
-    for (int i = 1; i < nstr; ++i) CRS_HIP(hipStreamWaitEvent(e.side[i - 1], e.fork, 0));
     for (int gi : order) {
       const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
       load[k] += (int64_t)(e.groups[gi].plan->fp64_triples * e.groups[gi].nmaps);
       gstream[gi] = k == 0 ? s0 : e.side[k - 1];
     }
   }
+  auto fork = [&] {
+    if (nstr <= 1) return;
+    CRS_HIP(hipEventRecord(e.fork, s0));
+    for (int i = 1; i < nstr; ++i) CRS_HIP(hipStreamWaitEvent(e.side[i - 1], e.fork, 0));
+  };
   // the maps a group's launches skip: merged bands leave M_PI (flags formed
   // on the device), finished systems leave every operator
   auto group_skip = [&](ExecGroup& g, hipStream_t s) {
@@ -985,12 +1014,12 @@ void exec_bands(Exec& e, OpKind kind, const double* in, hipStream_t s0, const do
                          s);
     }
   };
-  // On one stream the groups' mixing and active-map kernels run as one
-  // launch each (fewer launches per operator application; every block does
-  // the same arithmetic as in the per-group launches).
+  // The groups' mixing and active-map kernels run as one launch each on the
+  // caller's stream (fewer launches per operator application; every block
+  // does the same arithmetic as in the per-group launches), before the fork.
   int64_t fwd_blocks = 0;
   for (int gi : run) fwd_blocks += (e.groups[gi].nalm + kWorkBlock - 1) / kWorkBlock * e.groups[gi].nmaps;
-  const bool fuse = nstr <= 1 && run.size() > 1 && run.size() <= (size_t)kFuseGroups && fwd_blocks < (1ll << 31);
+  const bool fuse = run.size() > 1 && run.size() <= (size_t)kFuseGroups && fwd_blocks < (1ll << 31);
   if (fuse) {
     std::vector<MapSkip> sk(run.size());
     for (size_t t = 0; t < run.size(); ++t) sk[t] = group_skip(e.groups[run[t]], s0);
@@ -1016,8 +1045,10 @@ void exec_bands(Exec& e, OpKind kind, const double* in, hipStream_t s0, const do
     hipLaunchKernelGGL(k_mix_fwd_all, dim3((unsigned)first), dim3(256), 0, s0, in, e.dsys.p, e.dprobs.p,
                        pinv ? 1 : 0, act, ma);
     CRS_HIP(hipGetLastError());
-    for (size_t t = 0; t < run.size(); ++t) transforms(run[t], sk[t], s0);
+    fork();
+    for (size_t t = 0; t < run.size(); ++t) transforms(run[t], sk[t], gstream[run[t]]);
   } else {
+    fork();
     for (int gi : run) {
       ExecGroup& g = e.groups[gi];
       hipStream_t s = gstream[gi];
@@ -1501,13 +1532,14 @@ int exec_pcg(Exec& e, int precond, const double* b, double* x, double rtol, int 
     // captured when that set changes; graphs are kept per key for reuse).
     if (!e.cap_stream) CRS_HIP(hipStreamCreateWithFlags(&e.cap_stream, hipStreamNonBlocking));
     hipStream_t cs = e.cap_stream;
+    side_streams(e, streams_now(e));  // before the capture
     e.bbdev.upload(bb, s);
     std::vector<double> hrow((size_t)kChunk * ns), hcand(ns);
     auto get_graph = [&](bool first, int k) -> Exec::GraphEntry& {
       uint64_t mask = 0;
       for (int gi = 0; gi < ng && gi < 64; ++gi)
         if (e.live[gi]) mask |= uint64_t(1) << gi;
-      const auto key = std::make_tuple((precond * 2 + (prof ? 1 : 0)) * 16 + e.nstreams, first ? 1 : 0, k, mask);
+      const auto key = std::make_tuple((precond * 2 + (prof ? 1 : 0)) * 16 + streams_now(e), first ? 1 : 0, k, mask);
       auto itg = e.graphs.find(key);
       if (itg != e.graphs.end() && itg->second->rtol == rtol) return *itg->second;
       auto ge = std::make_unique<Exec::GraphEntry>();

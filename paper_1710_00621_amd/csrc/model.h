@@ -233,12 +233,13 @@ struct Exec {
   // them on the caller's stream and on these side streams (default
   // priority), forked from and joined back into the caller's stream by
   // events (inside a graph capture the same calls become graph edges).
-  // nstreams: streams the groups run on (1: all on the caller's stream; set
-  // by exec_set_streams, part of a captured graph's key).
+  // nstreams: streams the groups run on as set by exec_set_streams (1: all on the
+  // caller's stream), 0: auto_streams (make_exec's rule).  Part of a captured
+  // graph's key.
   std::vector<hipStream_t> side;
   std::vector<hipEvent_t> join;
   hipEvent_t fork = nullptr;
-  int nstreams = 1;
+  int nstreams = 0, auto_streams = 1;
   ~Exec();
 };
 

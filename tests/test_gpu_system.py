@@ -411,3 +411,32 @@ def test_varying_mixing_maps_match_oracle(extra):
                                                        [(b_["lmax"], b_["beam"], b_["tau"]) for b_ in om_c.bands])],
                              om_c.comps, om_c.q, diag=False)
         assert _rel(gm_c.apply_A(xt).cpu().numpy(), scal.apply_A(xt).cpu().numpy()) < 1e-12
+
+
+def test_group_streams_by_size_bitwise(monkeypatch):
+    """The multires bands / 2 are large enough that their transform groups run
+    on three streams by themselves: A, M_PI and a solve give the bits of one
+    stream, also when called from a stream of the caller's."""
+    torch, crsolve = _setup()
+    print("case group streams by size, multires / 2", flush=True)
+    prob = inputs.make_problem("multires", scale=2)
+    taus = inputs.inverse_noise_maps(prob, lambda spec: crsolve.Grid.from_spec(spec).pixel_centres())
+    gen = torch.Generator(device="cpu").manual_seed(71)
+    out = []
+    for n in ("1", None):
+        if n:
+            monkeypatch.setenv("CRS_GROUP_STREAMS", n)
+        else:
+            monkeypatch.delenv("CRS_GROUP_STREAMS")
+        gm = crsolve.model_from_problem(prob, taus)
+        x = torch.randn(3, gm.n, generator=gen.manual_seed(71), dtype=torch.float64).to("cuda")
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            ys = [gm.apply_A(x) for _ in range(3)]
+        torch.cuda.current_stream().wait_stream(s)
+        assert torch.equal(ys[0], ys[1]) and torch.equal(ys[0], ys[2])
+        sol, info = gm.pcg(ys[0], precond="pinv", rtol=1e-9, maxiter=100)
+        out.append([ys[0].cpu(), gm.apply_A(x[:1]).cpu(), gm.apply_pinv(x).cpu(), sol.cpu()])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
