@@ -128,39 +128,6 @@ __device__ __forceinline__ void small_dft(double2 (&v)[R]) {
       v[k] = cadd(e[k], t[k]);
       v[k + 4] = csub(e[k], t[k]);
     }
-  } else if constexpr (R == 16) {
-    // 4 x 4: 4-point DFTs over n1 of x_{4 n1 + n2}, times w^(n2 k1) (w = exp(-i pi
-    // / 8)), 4-point DFTs over n2: X_{k1 + 4 k2}
-    constexpr double c1 = 0.9238795325112867561281832;  // cos(pi / 8)
-    constexpr double s1 = 0.3826834323650897717284600;  // sin(pi / 8)
-    constexpr double h = 0.7071067811865475244008444;
-    auto rot = [](double2 z, double c, double sn) {  // z (c - i sn)
-      return make_double2(fma(z.x, c, z.y * sn), fma(z.y, c, -(z.x * sn)));
-    };
-    auto rot8 = [](double2 z) { return make_double2(h * (z.x + z.y), h * (z.y - z.x)); };
-    double2 u[4][4];  // [n2][k1]
-#pragma unroll
-    for (int n2 = 0; n2 < 4; ++n2) {
-#pragma unroll
-      for (int n1 = 0; n1 < 4; ++n1) u[n2][n1] = v[4 * n1 + n2];
-      small_dft<4>(u[n2]);
-    }
-    u[1][1] = rot(u[1][1], c1, s1);
-    u[1][2] = rot8(u[1][2]);
-    u[1][3] = rot(u[1][3], s1, c1);
-    u[2][1] = rot8(u[2][1]);
-    u[2][2] = make_double2(u[2][2].y, -u[2][2].x);
-    u[2][3] = make_double2(h * (u[2][3].y - u[2][3].x), -h * (u[2][3].x + u[2][3].y));
-    u[3][1] = rot(u[3][1], s1, c1);
-    u[3][2] = make_double2(h * (u[3][2].y - u[3][2].x), -h * (u[3][2].x + u[3][2].y));
-    u[3][3] = rot(u[3][3], -c1, -s1);
-#pragma unroll
-    for (int k1 = 0; k1 < 4; ++k1) {
-      double2 w[4] = {u[0][k1], u[1][k1], u[2][k1], u[3][k1]};
-      small_dft<4>(w);
-#pragma unroll
-      for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = w[k2];
-    }
   } else if constexpr (R == 4) {
     const double2 t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
     const double2 t2 = cadd(v[1], v[3]), t3 = csub(v[1], v[3]);
@@ -326,7 +293,7 @@ __device__ __forceinline__ void stage_prime(double2* x, int n, int p, int Ns, un
 }
 
 // In-place forward DFT of x[0..n) in LDS, any length.
-// POW2: the length is a power of two (radix 16, 8, 4 and 2 only).
+// POW2: the length is a power of two (radix 8, 4 and 2 only).
 template <int NT, int MAXN, bool POW2>
 __device__ __forceinline__ void fft_lds(double2* x, int n, const RingInfo* __restrict__ ri, const TwCtx& C, const double2* cs) {
   int Ns = 1;
