@@ -157,16 +157,20 @@ LegArgs leg_args(crs_grid g, ShtPlan& p) {
   a.bp = p.bp.p;
   a.be = p.be.p;
   a.gi = p.gi.p;
+  a.he = p.he.p;
+  a.re = p.re.p;
   a.ep = p.ep.p;
   a.ks = p.ks.p;
   a.st = p.st.p;
   a.zs = g->d_zs.p;
-  a.ys = g->d_ys.p;
+  a.ya = g->d_ya.p;
+  a.yc = g->d_yc.p;
   a.lmax = p.lmax;
   a.npairs = p.npairs;
   a.nring = g->nring;
   a.nslots = g->nslots;
   a.pol_tiles = g->pol_tiles;
+  a.eq_pairs = g->eq_pairs;
   a.pol_pairs = g->pol_pairs;
   a.skip = MapSkip{};
   return a;

@@ -171,20 +171,49 @@ void gl_nodes(int n, std::vector<double>& z, std::vector<double>& st, std::vecto
 // Ring pairs in slots, tiles of 64, for the Legendre kernels: every tile runs
 // one form of the recurrence (legendre.hip), whose errors grow as 1 / sin(2
 // theta) away from its own end.  The forms meet at 45 degrees; the boundary
-// moves to the nearest whole tile if that stays within 35 and 55 degrees (no
-// padding: every HEALPix grid from Nside 64 on), else it stays at 45 degrees
-// and the polar slots are padded.
+// moves to the nearest whole group of four tiles, else to the nearest whole
+// tile, if that stays within 35 and 55 degrees, else it stays at 45 degrees and
+// the polar slots are padded (HEALPix Nside 2 to 32 and 89 to 96).
+//
+// The 32 pairs next to the equator sit in the last tile, each in slots i and 32 +
+// i: the even functions are taken from the second (see legendre.hip).  Beyond
+// them (|z| 0.08 at Nside 256, 0.02 at Nside 1024) the even functions'
+// cancellation 1 / |z| is below the sqrt(L) by which rounding adds up in any form.
 static void slot_layout(crs_grid g) {
   const int np = (g->nring + 1) / 2;
   int p45 = 0;
   while (p45 < np && g->z[p45] * g->z[p45] >= 0.5) ++p45;
-  const int c = (p45 + 32) / 64 * 64;
   const double lo = 0.329, hi = 0.671;  // cos^2 of 55 and 35 degrees
-  const bool whole = c <= np && (c == 0 || g->z[c - 1] * g->z[c - 1] >= lo) &&
-                     (c == np || g->z[c] * g->z[c] <= hi);
-  g->pol_pairs = whole ? c : p45;
+  g->pol_pairs = p45;
+  for (const int unit : {256, 64}) {
+    const int c = (p45 + unit / 2) / unit * unit;
+    if (c <= np && (c == 0 || g->z[c - 1] * g->z[c - 1] >= lo) && (c == np || g->z[c] * g->z[c] <= hi)) {
+      g->pol_pairs = c;
+      break;
+    }
+  }
   g->pol_tiles = (g->pol_pairs + 63) / 64;
-  g->nslots = 64 * (g->pol_tiles + (np - g->pol_pairs + 63) / 64);
+  g->eq_pairs = std::min(32, np - g->pol_pairs);
+  g->nslots = 64 * (g->pol_tiles + (np - g->pol_pairs - g->eq_pairs + 63) / 64 + 1);
+}
+
+// Two doubles whose product is sin^2 theta = (1 - z)(1 + z) to about 2^-60: the
+// recurrence takes the product inside an FMA, so its rounding does not enter.
+// Neighbouring doubles a give products a fl(sin^2 / a) with residuals spread
+// over an ulp; the best of 64 is taken.
+static void sin2_factors(double z, double* fa, double* fc) {
+  const double w = 1.0 - z;  // exact for z >= 1/2
+  const double p = std::fma(-w, w, 2.0 * w), pe = std::fma(-w, w, 2.0 * w - p);  // sin^2 = 2 w - w^2 = p + pe
+  double a = w, best = HUGE_VAL;
+  for (int i = 0; i < 64; ++i, a = std::nextafter(a, 2.0)) {
+    const double c = p / a;
+    const double r = std::fabs(std::fma(a, c, -p) - pe);
+    if (r < best) {
+      best = r;
+      *fa = a;
+      *fc = c;
+    }
+  }
 }
 
 // Uploads per-ring tables (lengths, offsets, phi0, FFT factors, twiddles).
@@ -356,20 +385,25 @@ void grid_finalize(crs_grid g, hipStream_t s) {
   }
   if (!bf.empty()) g->d_bf.upload(bf, s);
   slot_layout(g);
-  std::vector<double> zs(g->nslots, 0.0), ss(g->nslots, 1.0), ys(g->nslots, 0.0);
+  std::vector<double> zs(g->nslots, 0.0), ss(g->nslots, 1.0), ya(g->nslots, 0.0), yc(g->nslots, 0.0);
   for (int p = 0; p < (nr + 1) / 2; ++p) {
     const bool polar = p < g->pol_pairs;
-    const int i = polar ? p : p - g->pol_pairs + 64 * g->pol_tiles;
+    const int e = p - ((nr + 1) / 2 - g->eq_pairs);  // pair of the equator's tile
+    const int i = polar ? p : e >= 0 ? g->nslots - 64 + e : p - g->pol_pairs + 64 * g->pol_tiles;
     zs[i] = g->z[p];
     ss[i] = g->sint[p];
-    // sin^2 theta of the ring's z as stored (1 - z is exact for z >= 1/2): the
-    // functions are those at the pixel centres the grid reports
-    ys[i] = polar ? -(1.0 - g->z[p]) * (1.0 + g->z[p]) : -g->z[p] * g->z[p];
+    // sin^2 theta of the ring's z as stored: the functions are those at the
+    // pixel centres the grid reports
+    ya[i] = yc[i] = g->z[p];
+    if (polar) sin2_factors(g->z[p], &ya[i], &yc[i]);
+    if (e >= 0)
+      for (auto* v : {&zs, &ss, &ya, &yc}) (*v)[i + 32] = (*v)[i];
   }
   g->d_tw.upload(tw, s);
   g->d_zs.upload(zs, s);
   g->d_ss.upload(ss, s);
-  g->d_ys.upload(ys, s);
+  g->d_ya.upload(ya, s);
+  g->d_yc.upload(yc, s);
   CRS_HIP(hipStreamSynchronize(s));
 }
 
@@ -424,12 +458,16 @@ void build_gl(crs_grid g, int nrings, int nphi) {
 // ----------------------------------------------------------- Legendre plan
 // Coefficients of the recurrence in legendre.hip.  With eta_l = (4 m^2 - 1) /
 // (4 (4 l^2 - 1)), eps_l^2 = 1/4 - eta_l; g = eps_l eps_{l-1} = 1/4 - delta with
-// delta = (eta_l / 4 + eta_{l-1} eps_l^2) / (1/4 + g).  At l = m + 2k + 1 the sums
+// delta = (eta_l / 4 + eta_{l-1} eps_l^2) / (1/4 + g).  At l = m + 2k + 1
 //     1 - eps_{l+1}^2 - eps_l^2 - g_k - g_{k+1} = (eta_l + eta_{l+1}) + (delta_k + delta_{k+1})
-//     eps_{l+1}^2 + eps_l^2 - g_k - g_{k+1} = (delta_k + delta_{k+1}) - (eta_l + eta_{l+1})
-// come out of small terms instead of cancelling to them.
+//     eps_{l+1}^2 + eps_l^2 - g_k - g_{k+1} = eps_l s_l - eps_{l+1} s_{l+2},
+// s_l = eps_l - eps_{l-1} = (eta_{l-1} - eta_l) / (eps_l + eps_{l-1}) with eta_{l-1} - eta_l =
+// (4 m^2 - 1) / ((2l - 3)(2l - 1)(2l + 1)): the second, O(m^2 / l^3), is multiplied
+// by q, l times lambda next to the equator, and as (delta_k + delta_{k+1}) - (eta_l
+// + eta_{l+1}) its rounding, O(m^2 / l^2), was up to 300 times what the functions
+// need there (6e-13 at L 2000).  h_k = eps_l s_l.
 __global__ void k_rec_tables(int L, double* __restrict__ bp, double* __restrict__ be, double* __restrict__ gi,
-                             double* __restrict__ ep) {
+                             double* __restrict__ he, double* __restrict__ re, double* __restrict__ ep) {
   const int m = blockIdx.y;
   const int K = (L - m) / 2 + 1;
   const double m2 = 4.0 * (double)m * m - 1.0;
@@ -441,16 +479,21 @@ __global__ void k_rec_tables(int L, double* __restrict__ bp, double* __restrict_
     const double g0 = sqrt(e0 * e1), g1 = sqrt(e2 * e3);
     const double d0 = (eta(l) * 0.25 + eta(l - 1.0) * e1) / (0.25 + g0);
     const double d1 = (eta(l + 2.0) * 0.25 + eta(l + 1.0) * e3) / (0.25 + g1);
-    const double se = eta(l) + eta(l + 1.0);
+    // eta_{j-1} - eta_j
+    auto deta = [&](double j) { return m2 / ((2.0 * j - 3.0) * (2.0 * j - 1.0) * (2.0 * j + 1.0)); };
+    const double r0 = sqrt(e0), r1 = sqrt(e1), r2 = sqrt(e2), r3 = sqrt(e3);
+    const double s0 = deta(l) / (r1 + r0), s2 = deta(l + 2.0) / (r3 + r2);
     const int64_t o = krow(L, m) + k;
-    bp[o] = se + (d0 + d1);
-    be[o] = (d0 + d1) - se;
+    bp[o] = (eta(l) + eta(l + 1.0)) + (d0 + d1);
+    be[o] = r1 * s0 - r2 * s2;
     gi[o] = 1.0 / g1;
+    he[o] = r1 * s0;
+    re[o] = 1.0 / r1;
     // eps of l - 1 and l (row entries m + 2k, m + 2k + 1; the row ends at L + 1)
     double* er = ep + 4 + erow(L, m);
-    er[2 * k] = sqrt(e0);
-    if (2 * k + 1 <= L + 1 - m) er[2 * k + 1] = sqrt(e1);
-    if (k == K - 1 && 2 * k + 2 <= L + 1 - m) er[2 * k + 2] = sqrt(e2);
+    er[2 * k] = r0;
+    if (2 * k + 1 <= L + 1 - m) er[2 * k + 1] = r1;
+    if (k == K - 1 && 2 * k + 2 <= L + 1 - m) er[2 * k + 2] = r2;
   }
   if (m == 0 && blockIdx.x == 0 && threadIdx.x < 4) ep[threadIdx.x] = threadIdx.x & 1 ? 0.0 : 1.0;
 }
@@ -462,39 +505,53 @@ __global__ void k_rec_tables(int L, double* __restrict__ bp, double* __restrict_
 __global__ void k_start_table(const double* __restrict__ bp, const double* __restrict__ be,
                               const double* __restrict__ gi, const double* __restrict__ ep,
                               const double* __restrict__ zs, const double* __restrict__ ss,
-                              const double* __restrict__ ys, const double* __restrict__ pm_mant,
-                              const int* __restrict__ pm_exp, int L, int nslots, int pol_pairs, int pol_tiles,
+                              const double* __restrict__ ya, const double* __restrict__ yc,
+                              const double* __restrict__ pm_mant,
+                              const int* __restrict__ pm_exp, int L, int nslots, int pol_pairs, int pol_tiles, int eq_pairs,
                               int npairs, double thr, double thr_lo, int* __restrict__ ks_out,
                               double2* __restrict__ st_out, unsigned long long* __restrict__ counts) {
   const int slot = blockIdx.x * blockDim.x + threadIdx.x;
   const int m = blockIdx.y;
   const bool polar = slot < 64 * pol_tiles;
-  const int p = polar ? (slot < pol_pairs ? slot : -1) : slot - 64 * pol_tiles + pol_pairs;
+  // the slot's ring pair (-1: none), and whether it is counted (once)
+  const int e = slot - (nslots - 64);
+  int p = polar ? slot : slot - 64 * pol_tiles + pol_pairs;
+  if (polar ? p >= pol_pairs : e < 0 && p >= npairs - eq_pairs) p = -1;
+  if (e >= 0) p = (e & 31) < eq_pairs ? npairs - eq_pairs + (e & 31) : -1;
+  const bool counted = e < 32;
   unsigned long long n0 = 0, n1 = 0;
   if (slot < nslots) {
     int ksv = INT_MAX;
     double2 stv = make_double2(0.0, 0.0);
-    if (p >= 0 && p < npairs) {
-      const double z = zs[slot], s = ss[slot], y = ys[slot];
+    if (p >= 0) {
+      const double z = zs[slot], s = ss[slot], a = ya[slot], c = yc[slot];
       // lambda_mm = P_m sin^m(theta), carried as mantissa * 2^e
       double mant = pm_mant[m];
       long e = pm_exp[m];
       if (m > 0) {
-        int se;
-        double base = frexp(s, &se), r = 1.0;
-        long er = 0, eb = se;
-        for (int j = m; j; j >>= 1) {
+        // powers of two doubles: squaring one would add up m / 2 of its roundings
+        struct Num {
+          double h, l;
+          long e;
+        };
+        auto norm = [](double h, double l, long e) {
           int t;
-          if (j & 1) {
-            r = frexp(r * base, &t);
-            er += eb + t;
-          }
-          base = frexp(base * base, &t);
-          eb = 2 * eb + t;
+          const double f = frexp(h, &t);
+          return Num{f, ldexp(l, -t), e + t};
+        };
+        auto mul = [&](const Num& u, const Num& v) {
+#pragma clang fp contract(off)
+          const double q = u.h * v.h, r = fma(u.h, v.h, -q) + (u.h * v.l + u.l * v.h), h = q + r;
+          return norm(h, r - (h - q), u.e + v.e);
+        };
+        Num base = norm(s, 0.0, 0), r{1.0, 0.0, 0};
+        for (int j = m; j; j >>= 1) {
+          if (j & 1) r = mul(r, base);
+          base = mul(base, base);
         }
-        int t;
-        mant = frexp(mant * r, &t);
-        e += er + t;
+        const Num v = norm(fma(mant, r.h, mant * r.l), 0.0, e + r.e);
+        mant = v.h;
+        e = v.e;
       }
       const double* b = (polar ? bp : be) + krow(L, m);
       const double* g = gi + krow(L, m);
@@ -525,11 +582,11 @@ __global__ void k_start_table(const double* __restrict__ bp, const double* __res
         if (hit >= 0) {
           ksv = k & ~7;
           stv = make_double2(ldexp(sq, (int)se), ldexp(sd, (int)se));
-          n0 = (unsigned long long)(L - hit + 1);
+          n0 = counted ? (unsigned long long)(L - hit + 1) : 0;
           break;
         }
         qm = sg * q;
-        d = fma(y + b[k], q, d);
+        d = fma(fma(-a, c, b[k]), q, d);
         q = fma(g[k], d, q);
         if (fabs(q) > 0x1p600) {
           q *= 0x1p-600;
@@ -538,7 +595,7 @@ __global__ void k_start_table(const double* __restrict__ bp, const double* __res
           e += 600;
         }
       }
-      if (lo_l <= L) n1 = (unsigned long long)(L - lo_l + 1);
+      if (counted && lo_l <= L) n1 = (unsigned long long)(L - lo_l + 1);
     }
     ks_out[(size_t)m * nslots + slot] = ksv;
     st_out[(size_t)m * nslots + slot] = stv;
@@ -588,14 +645,14 @@ ShtPlan& get_plan(crs_grid g, int lmax, hipStream_t s) {
     }
   }
   const int64_t nk = krow(L, L) + 1 + kTabPad, ne = 4 + erow(L, L) + 2 + kTabPad;
-  for (auto* t : {&plan->bp, &plan->be, &plan->gi}) {
+  for (auto* t : {&plan->bp, &plan->be, &plan->gi, &plan->he, &plan->re}) {
     t->alloc((size_t)nk);
     hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, t->p + nk - kTabPad, (int64_t)kTabPad, 0.0);
   }
   plan->ep.alloc((size_t)ne);
   hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, plan->ep.p + ne - kTabPad, (int64_t)kTabPad, 0.0);
   hipLaunchKernelGGL(k_rec_tables, dim3((L / 2 + 256) / 256, L + 1), dim3(256), 0, s, L, plan->bp.p, plan->be.p,
-                     plan->gi.p, plan->ep.p);
+                     plan->gi.p, plan->he.p, plan->re.p, plan->ep.p);
   CRS_HIP(hipGetLastError());
   DevBuf<double> dpm;
   DevBuf<int> dpe;
@@ -607,8 +664,8 @@ ShtPlan& get_plan(crs_grid g, int lmax, hipStream_t s) {
   plan->ks.alloc((size_t)(L + 1) * plan->nslots);
   plan->st.alloc((size_t)(L + 1) * plan->nslots);
   hipLaunchKernelGGL(k_start_table, dim3((plan->nslots + 127) / 128, L + 1), dim3(128), 0, s, plan->bp.p, plan->be.p,
-                     plan->gi.p, plan->ep.p, g->d_zs.p, g->d_ss.p, g->d_ys.p, dpm.p, dpe.p, L, plan->nslots,
-                     g->pol_pairs, g->pol_tiles, plan->npairs, kSkipThreshold, kFp64Normal, plan->ks.p, plan->st.p,
+                     plan->gi.p, plan->ep.p, g->d_zs.p, g->d_ss.p, g->d_ya.p, g->d_yc.p, dpm.p, dpe.p, L, plan->nslots,
+                     g->pol_pairs, g->pol_tiles, g->eq_pairs, plan->npairs, kSkipThreshold, kFp64Normal, plan->ks.p, plan->st.p,
                      dcnt.p);
   CRS_HIP(hipGetLastError());
   CRS_HIP(hipMemcpyAsync(cnt, dcnt.p, sizeof(cnt), hipMemcpyDeviceToHost, s));

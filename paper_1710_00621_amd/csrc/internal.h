@@ -101,7 +101,7 @@ constexpr size_t kMaxLds = 160 * 1024;  // LDS bytes one workgroup may use (gfx9
 // ---------------------------------------------------------------- grids
 // Per-(grid, lmax) Legendre plan: start table and recurrence tables.  Ring
 // pairs sit in slots in tiles of 64 (grid.hip): the polar ones first, padded
-// to whole tiles, then the others.
+// to whole tiles, then the others, the last (up to 32) twice in a tile of their own.
 struct ShtPlan {
   int lmax = 0;
   int npairs = 0, nslots = 0;
@@ -109,6 +109,7 @@ struct ShtPlan {
   int64_t fp64_triples = 0;    // triples whose |lambda| reaches the float64 normal range
   int64_t nominal_triples = 0; // npairs * (L+1)(L+2)/2
   DevBuf<double> bp, be, gi;   // rows of m (krow): recurrence coefficients b_k (polar, equator form), 1 / g_{k+1}
+  DevBuf<double> he, re;       // rows of m (krow): h_k and 1 / eps_{m+2k+1} (equator form)
   DevBuf<double> ep;           // (1, 0, 1, 0), then rows of m (erow): eps_lm, l = m .. L + 1
   DevBuf<int> ks;              // [L+1][nslots]: first k evaluated, a multiple of 8 (INT_MAX = never)
   DevBuf<double2> st;          // [L+1][nslots]: (q, d) there
@@ -189,10 +190,11 @@ struct crs_grid_s {
   // device ring tables
   crs::DevBuf<double2> d_bf;      // Bluestein filter spectra per distinct length
   crs::DevBuf<double2> d_tw2;     // exp(-2 pi i t / kBlueMax), t < kBlueMax (power-of-two FFTs)
-  // ring pair slots (see slot_layout): polar pairs and tiles, all slots; per
-  // slot z of the north ring, sin(theta) and y = -sin^2 or -z^2
-  int pol_pairs = 0, pol_tiles = 0, nslots = 0;
-  crs::DevBuf<double> d_zs, d_ss, d_ys;
+  // ring pair slots (see slot_layout): polar pairs and tiles, pairs of the
+  // equator's tile, all slots; per slot z of the north ring, sin(theta), and
+  // ya, yc with ya yc = sin^2 (polar) or z^2
+  int pol_pairs = 0, pol_tiles = 0, eq_pairs = 0, nslots = 0;
+  crs::DevBuf<double> d_zs, d_ss, d_ya, d_yc;
   crs::DevBuf<double2> d_tw;      // twiddles exp(-2 pi i t / N) per distinct N
   std::vector<crs::RingClass> ring_classes;  // by (tier, Bluestein, odd radix)
   std::vector<crs::DevBuf<crs::RingInfo>> d_ring_class;
@@ -222,11 +224,11 @@ struct MapSkip {
 };
 
 struct LegArgs {
-  const double *bp, *be, *gi, *ep;  // ShtPlan tables
+  const double *bp, *be, *gi, *he, *re, *ep;  // ShtPlan tables
   const int* ks;
   const double2* st;
-  const double *zs, *ys;            // per slot
-  int lmax, npairs, nring, nslots, pol_tiles, pol_pairs;
+  const double *zs, *ya, *yc;       // per slot
+  int lmax, npairs, nring, nslots, pol_tiles, pol_pairs, eq_pairs;
   MapSkip skip;
   // optional compaction: the launch's map slots s < *mcount are the maps
   // mlist[s] (ascending), the slots past *mcount are empty; without it slot

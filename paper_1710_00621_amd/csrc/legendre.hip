@@ -23,11 +23,40 @@
 // near the poles (upper signs) y = -sin^2 theta and b_k = 1 - eps_{l+1}^2 -
 // eps_l^2 - g_k - g_{k+1}, near the equator (lower signs) y = -z^2 and b_k =
 // eps_{l+1}^2 + eps_l^2 - g_k - g_{k+1}.  Both b_k and y vanish where the
-// recurrence's characteristic roots meet, so nothing cancels: against 80-bit
-// arithmetic over all rings and m the functions are 10 (Nside 64, L 128) to 35
-// (Nside 512, L 1024) times closer than the one-step recurrence in l.  Tiles
-// of 64 ring pairs use one form each (grid.hip lays the pairs out in slots so
-// that every tile lies well inside one form's range).
+// recurrence's characteristic roots meet, so nothing cancels in q and d.  What
+// would add up over the steps is kept out: an error of y is the same in every
+// step (a shifted ring), so y is the exact product of two doubles inside the
+// FMA that adds b_k, and the tables form b_k without subtracting equal terms
+// (grid.hip).
+//
+// Even functions next to the equator.  There neighbouring q have opposite signs
+// and size |lambda / z|, so that eps_{l+1} q_k + eps_l q_{k-1} cancels by a factor
+// of 1 / |z|.  The 32 ring pairs next to the equator therefore run in a third
+// form: the same recurrence, and
+//     lambda_{m+2k} = p_k / eps_{l+1},  p_k = d_k + h_k q_k,  h_k = eps_{l+1} (eps_{l+1} - eps_l)
+// (l = m + 2k, d_k with the lower sign), whose terms do not cancel.  They sit
+// twice in a tile of their own, whose first half hands on q (for O) and whose
+// second half p (for E): the tile costs what any other does, and no wave holds
+// more registers.  (Tried: q and p of 64 pairs one after the other in one wave,
+// twice the LDS traffic and a longer chain: Nside 128 / L 256 x3, Legendre
+// kernels, synthesis 24.8 us instead of 19.9, adjoint 27.8 instead of 20.3; the
+// same inside the last belt group's wave, so that no further partial vector is
+// written: its loads wait for its own stores, Nside 1024 / L 2000 adjoint 769 us
+// instead of 565.)  Without the third form: 18.8, 19.2, 541.
+//
+// Relative rms error of F_m over all m, random coefficients, by |z| (each
+// scheme emulated on the CPU against 80-bit arithmetic; the one-step recurrence
+// in l / q alone / with the equator's form):
+//                        Nside 256, L 512             Nside 1024, L 2000
+//     0      .. 0.0025   7.6e-16 9.4e-15 5.9e-16     1.9e-15 3.0e-14 1.3e-15
+//     0.01   .. 0.02     9.4e-16 2.5e-15 7.3e-16     1.8e-15 2.6e-15 1.3e-15
+//     0.05   .. 0.1      8.8e-16 8.0e-16 6.4e-16     1.9e-15 1.4e-15 1.3e-15
+//     0.3    .. 0.5      1.7e-15 1.2e-15 1.2e-15     3.6e-15 2.4e-15 2.4e-15
+//     0.71   .. 0.8      3.6e-15 1.7e-15 1.7e-15     8.0e-15 4.6e-15 4.6e-15
+//     0.97   .. 1        5.2e-14 1.1e-15 1.1e-15     3.4e-13 1.8e-15 1.8e-15
+//
+// Tiles of 64 ring pairs use one form each (grid.hip lays the pairs out in slots
+// so that every tile lies well inside one form's range).
 //
 // Each (ring pair, m) starts at the last multiple of 8 in k at or before the
 // first l where |lambda_lm| reaches 2^-100 (start table from grid.hip); before
@@ -45,6 +74,8 @@
 namespace crs {
 
 namespace {
+
+enum Form { POLAR, BELT, EQUATOR };  // of the recurrence (a tile's)
 
 // Tables and wave-uniform inputs are read through the constant address space
 // so that they become scalar (SMEM) loads.
@@ -118,16 +149,18 @@ __device__ __forceinline__ bool leg_any(const LegArgs& a, int s0, int n, int ns)
   return any;
 }
 // Ring pairs p0 .. of a tile: pair p0 + i in slot i, valid below limit.  full:
-// all 64 are valid and none is the equator ring, its own pair.
+// all 64 are valid and none is the equator ring, its own pair.  The last tile,
+// the equator's, holds its (at most 32) pairs twice: p0 + i % 32 in slot i.
 struct TilePairs {
   int p0, limit;
   bool full;
 };
-__device__ __forceinline__ TilePairs tile_pairs(const LegArgs& a, int tile, bool polar) {
+template <int F>
+__device__ __forceinline__ TilePairs tile_pairs(const LegArgs& a, int tile) {
   TilePairs t;
-  t.p0 = polar ? tile * 64 : (tile - a.pol_tiles) * 64 + a.pol_pairs;
-  t.limit = polar ? a.pol_pairs : a.npairs;
-  t.full = t.p0 + 64 <= t.limit && 2 * (t.p0 + 63) + 1 < a.nring;
+  t.p0 = F == POLAR ? tile * 64 : F == BELT ? (tile - a.pol_tiles) * 64 + a.pol_pairs : a.npairs - a.eq_pairs;
+  t.limit = F == POLAR ? a.pol_pairs : F == BELT ? a.npairs - a.eq_pairs : a.npairs;
+  t.full = F != EQUATOR && t.p0 + 64 <= t.limit;
   return t;
 }
 
@@ -143,21 +176,24 @@ __device__ __forceinline__ void block_coords(int ntiles, int& mb, int& tile) {
 }
 
 // ----------------------------------------------------------- recurrence
-// State of one lane's ring pair: (q, d) before step k, k a multiple of 8.
+// State of one lane's ring pair: (q, d) before step k, k a multiple of 8; y =
+// -ya yc (yc = ya = z outside the polar form).
 struct RecState {
-  double y, q, d;
+  double ya, yc, q, d;
   int ks;     // the lane's start
   int nx;     // next start in the wave (uniform)
   int first;  // first start in the wave (uniform)
 };
+template <int F>
 __device__ __forceinline__ void rec_init(RecState& r, const LegArgs& a, int m, int slot, bool in) {
-  r.y = in ? a.ys[slot] : 0.0;
+  r.ya = in ? a.ya[slot] : 0.0;
+  r.yc = F == POLAR && in ? a.yc[slot] : 0.0;
   r.ks = in ? a.ks[(size_t)m * a.nslots + slot] : INT_MAX;
   r.q = r.d = 0.0;
   r.nx = r.first = wave_min(r.ks);
 }
 
-// Coefficients of N steps from k0 (scalar registers)
+// Coefficients of N steps from k0 (scalar registers), and h_k of eight
 template <int N>
 struct RecCoef {
   double b[N], g[N];
@@ -173,12 +209,23 @@ __device__ __forceinline__ RecCoef<N> rec_coef(cdouble* b, cdouble* gi, int k0) 
   return c;
 }
 
+struct RecH {
+  double h[8];
+};
+__device__ __forceinline__ RecH rec_h(cdouble* he, int k0) {
+  RecH c;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) c.h[i] = he[k0 + i];
+  return c;
+}
+
 // Eight steps of the signed q_k, k = k0 .. k0 + 7, with the coefficients from
-// C.b[O] on, each pair (even, odd k) handed to put(i / 2, q_i, q_{i+1}).  Lanes
-// whose start is k0 join first.
-template <bool POLAR, int O, int N, class Put>
-__device__ __forceinline__ void rec8(RecState& r, const RecCoef<N>& C, const LegArgs& a, int m, int slot, int k0,
-                                     Put&& put) {
+// C.b[O] on, each pair (even, odd k) handed to put(i / 2, q_i, q_{i+1}), in the
+// equator form with p_i, p_{i+1} (p_k = eps_{m+2k+1} lambda_{m+2k}) after them.
+// Lanes whose start is k0 join first.
+template <int F, int O, int N, class Put>
+__device__ __forceinline__ void rec8(RecState& r, const RecCoef<N>& C, const RecH& H, const LegArgs& a, int m, int slot,
+                                     int k0, Put&& put) {
   if (r.nx == k0) {
     if (r.ks == k0) {
       const double2 v = a.st[(size_t)m * a.nslots + slot];
@@ -188,35 +235,48 @@ __device__ __forceinline__ void rec8(RecState& r, const RecCoef<N>& C, const Leg
     }
     r.nx = wave_min(r.ks > k0 ? r.ks : INT_MAX);
   }
+  const double yc = F == POLAR ? r.yc : r.ya;
 #pragma unroll
   for (int i = 0; i < 8; i += 2) {
+    const double t0 = fma(-r.ya, yc, C.b[O + i]), t1 = fma(-r.ya, yc, C.b[O + i + 1]);
     const double qe = r.q;
-    r.d = fma(r.y + C.b[O + i], qe, r.d);
-    if (POLAR) {
+    const double pe = F == EQUATOR ? fma(H.h[i], qe, r.d) : 0.0;
+    r.d = fma(t0, qe, r.d);
+    if constexpr (F == POLAR) {
       const double qo = fma(C.g[O + i], r.d, qe);
       put(i / 2, qe, qo);
-      r.d = fma(r.y + C.b[O + i + 1], qo, r.d);
+      r.d = fma(t1, qo, r.d);
       r.q = fma(C.g[O + i + 1], r.d, qo);
     } else {
-      const double qo = fma(-C.g[O + i], r.d, -qe);  // the recurrence runs on -qo
-      put(i / 2, qe, qo);
-      r.d = fma(-(r.y + C.b[O + i + 1]), qo, r.d);
+      const double qo = fma(-C.g[O + i], r.d, -qe);  // the recurrence runs on -qo and -d there
+      if constexpr (F == EQUATOR)
+        put(i / 2, qe, qo, pe, fma(H.h[i + 1], qo, -r.d));
+      else
+        put(i / 2, qe, qo);
+      r.d = fma(-t1, qo, r.d);
       r.q = fma(C.g[O + i + 1], r.d, -qo);
     }
   }
 }
+template <int F, int O, int N, class Put>
+__device__ __forceinline__ void rec8(RecState& r, const RecCoef<N>& C, const LegArgs& a, int m, int slot, int k0,
+                                     Put&& put) {
+  static_assert(F != EQUATOR);
+  rec8<F, O>(r, C, RecH{}, a, m, slot, k0, put);
+}
 
-// Tile groups: the polar tiles in groups of T, then the others, so that a wave
-// runs one form (chosen once) and its tiles share the coefficients.
+// Tile groups: the polar tiles in groups of T, then the belt's, so that a wave
+// runs one form (chosen once) and its tiles share the coefficients; the
+// equator's tile is a group of its own.
 struct TileRange {
-  int t0, tend;
-  bool polar;
+  int t0, tend, form;
 };
 template <int T>
 __device__ __forceinline__ TileRange tile_range(const LegArgs& a, int tg) {
-  const int np = (a.pol_tiles + T - 1) / T;
-  if (tg < np) return {tg * T, a.pol_tiles, true};
-  return {a.pol_tiles + (tg - np) * T, a.nslots / 64, false};
+  const int np = (a.pol_tiles + T - 1) / T, te = a.nslots / 64 - 1;
+  if (tg < np) return {tg * T, a.pol_tiles, POLAR};
+  const int t0 = a.pol_tiles + (tg - np) * T;
+  return t0 < te ? TileRange{t0, te, BELT} : TileRange{te, te + 1, EQUATOR};
 }
 
 // Wave-private LDS tile of q: row k / 2 holds the pairs (q_k, q_{k+1}) of 64
@@ -242,11 +302,17 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // they add), which is why the recurrence's three operations per two l matter.
 // One wave owns (m, T tiles of 64 ring pairs, 4 C16 + C4 maps); a block of 8
 // steps goes through the wave's LDS tile into the A operands.
-template <int C16, int C4, int T, bool POLAR>
+//
+// The equator's tile (T = 1) has q of its ring pairs in rows 0 .. 31 and p of the
+// same pairs in rows 32 .. 63, whose E columns take B = u_l / eps_{l+1}: O comes
+// from the first rows and E from the others, at the cost of a tile of the belt.
+template <int C16, int C4, int T, int F>
 __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int t0, int tend, int map0, int ns,
                                          const double* __restrict__ u, int64_t ustride,
                                          double2* __restrict__ phase, int64_t pstride, double2* qsh) {
+  static_assert(F != EQUATOR || T == 1);
   constexpr int NG = C16 + C4, NMW = 4 * C16 + C4;
+  constexpr int RB = F == EQUATOR ? 2 : 4;  // blocks of 16 rows with ring pairs of their own
   const int L = a.lmax;
   const bool mok = mw <= L;  // a block's last waves may lie past L: they only join its stores
   const int m = min(mw, L);
@@ -262,11 +328,12 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
   for (int g = 0; g < NG; ++g) cslot[g] = g < C16 ? map0 + 4 * g + ((lane >> 2) & 3) : map0 + 4 * C16 + (g - C16);
   RecState r[T];
   int kst = INT_MAX;
-  cdouble* cb = as_const((POLAR ? a.bp : a.be) + krow(L, m));
+  cdouble* cb = as_const((F == POLAR ? a.bp : a.be) + krow(L, m));
   cdouble* cg = as_const(a.gi + krow(L, m));
+  cdouble* ch = as_const(a.he + krow(L, m));
 #pragma unroll
   for (int t = 0; t < T; ++t) {
-    rec_init(r[t], a, m, (t0 + t) * 64 + lane, t0 + t < tend && mok);
+    rec_init<F>(r[t], a, m, (t0 + t) * 64 + lane, t0 + t < tend && mok);
     kst = min(kst, r[t].first);
   }
   v4d D16[T][4][C16 > 0 ? C16 : 1];
@@ -292,11 +359,17 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
             2 * (k1 + 2 * kq) + par;
   const double* ep = par ? a.ep : a.ep + 4 + erow(L, m) + 1 + 2 * (k1 + 2 * kq);
   const int64_t estep = par ? 0 : 16;
-  double un[NG][3], en[4];
+  const double* rp = a.re + krow(L, m) + k1 + 2 * kq;  // equator: 1 / eps_{l+1} of the two even l
+  double un[NG][3], en[4], rn[2];
   auto load = [&](int k0) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) en[i] = ep[i];
     ep += estep;
+    if (F == EQUATOR) {
+      rn[0] = rp[0];
+      rn[1] = rp[1];
+      rp += 8;
+    }
     if (2 * (k0 + 7) + 3 <= n) {
 #pragma unroll
       for (int g = 0; g < NG; ++g)
@@ -316,18 +389,27 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
     for (int g = 0; g < NG; ++g) up[g] += 16;
   };
   RecCoef<8> C{};
+  RecH H{};
   if (kst < K) {
     load(kst);
     C = rec_coef<8>(cb, cg, kst);
+    if (F == EQUATOR) H = rec_h(ch, kst);
   }
   const bool two = C16 < 2 || map0 + 4 < ns;  // the second group of four has maps
   for (int k0 = kst; k0 < K; k0 += 8) {
     k0 = __builtin_amdgcn_readfirstlane(k0);
-    double B0[NG], B1[NG];
+    double B0[NG], B1[NG], P0[NG], P1[NG];  // P: equator, rows of p
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
-      B0[g] = fma(en[1], un[g][1], en[0] * un[g][0]);
-      B1[g] = fma(en[3], un[g][2], en[2] * un[g][1]);
+      if (F == EQUATOR) {
+        P0[g] = rn[0] * un[g][0];
+        P1[g] = rn[1] * un[g][1];
+        B0[g] = un[g][0];  // (of O columns)
+        B1[g] = un[g][1];
+      } else {
+        B0[g] = fma(en[1], un[g][1], en[0] * un[g][0]);
+        B1[g] = fma(en[3], un[g][2], en[2] * un[g][1]);
+      }
     }
     load(k0 + 8);  // past K: in bounds, unused
     RecCoef<8> Cn;
@@ -335,9 +417,15 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
 #pragma unroll
     for (int t = 0; t < T; ++t) {
       if (T > 1 && r[t].first > k0) continue;
-      rec8<POLAR, 0>(r[t], C, a, m, (t0 + t) * 64 + lane, k0,
-                     [&](int i, double qe, double qo) { qt[i * kQRowSyn + lane] = make_double2(qe, qo); });
+      if constexpr (F == EQUATOR)
+        rec8<F, 0>(r[t], C, H, a, m, (t0 + t) * 64 + lane, k0, [&](int i, double qe, double qo, double pe, double po) {
+          qt[i * kQRowSyn + lane] = lane < 32 ? make_double2(qe, qo) : make_double2(pe, po);
+        });
+      else
+        rec8<F, 0>(r[t], C, a, m, (t0 + t) * 64 + lane, k0,
+                   [&](int i, double qe, double qo) { qt[i * kQRowSyn + lane] = make_double2(qe, qo); });
       if (T == 1) C = rec_coef<8>(cb, cg, k0 + 8);  // the next block's, during the products
+      if (F == EQUATOR) H = rec_h(ch, k0 + 8);
       wave_fence();
       double2 A[4];
 #pragma unroll
@@ -347,20 +435,20 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
 #pragma unroll
         for (int g = 0; g < C16; ++g)
           if (g == 0 || two)
-            D16[t][rb][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[rb].x, B0[g], D16[t][rb][g], 0, 0, 0);
+            D16[t][rb][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[rb].x, rb < RB ? B0[g] : P0[g], D16[t][rb][g], 0, 0, 0);
 #pragma unroll
         for (int c = 0; c < C4; ++c)
-          D4[t][rb][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[rb].x, B0[C16 + c], D4[t][rb][c], 0, 0, 0);
+          D4[t][rb][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[rb].x, rb < RB ? B0[C16 + c] : P0[C16 + c], D4[t][rb][c], 0, 0, 0);
       }
 #pragma unroll
       for (int rb = 0; rb < 4; ++rb) {
 #pragma unroll
         for (int g = 0; g < C16; ++g)
           if (g == 0 || two)
-            D16[t][rb][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[rb].y, B1[g], D16[t][rb][g], 0, 0, 0);
+            D16[t][rb][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[rb].y, rb < RB ? B1[g] : P1[g], D16[t][rb][g], 0, 0, 0);
 #pragma unroll
         for (int c = 0; c < C4; ++c)
-          D4[t][rb][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[rb].y, B1[C16 + c], D4[t][rb][c], 0, 0, 0);
+          D4[t][rb][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[rb].y, rb < RB ? B1[C16 + c] : P1[C16 + c], D4[t][rb][c], 0, 0, 0);
       }
       wave_fence();
     }
@@ -374,12 +462,23 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     if (t0 + t >= tend) break;
-    const TilePairs tp = tile_pairs(a, t0 + t, POLAR);
+    const TilePairs tp = tile_pairs<F>(a, t0 + t);
+    if constexpr (F == EQUATOR) {  // E of rows 32 .. 63 beside O of the same pairs
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+        for (int g = 0; g < C16; ++g)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) D16[t][rb][g][q] = par ? D16[t][rb][g][q] : D16[t][rb + 2][g][q];
+#pragma unroll
+        for (int c = 0; c < C4; ++c) D4[t][rb][c] = par ? D4[t][rb][c] : D4[t][rb + 2][c];
+      }
+    }
     const double* zt = a.zs + (t0 + t) * 64;
     if constexpr (C16 == 0) {
       // one to three maps: straight to the phase array
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
+      for (int rb = 0; rb < RB; ++rb) {
         // D: block (t / 4) % 4, row t / 16 of it, column t % 4
         const int i = 16 * rb + 4 * ((lane >> 2) & 3) + kq;
         const double cz = cm * zt[i];
@@ -401,7 +500,7 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
       double* xs = reinterpret_cast<double*>(qsh);  // [row 16][N, S][map][wave][cos, sin]
       static_assert(16 * 2 * NMW * 4 <= 4 * 4 * kQRowSyn, "a row block of every map fits the tiles' LDS");
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) {
+      for (int rb = 0; rb < RB; ++rb) {
         __syncthreads();
         auto put = [&](int row, int ms, double D) {
           const double cz = cm * zt[16 * rb + row];
@@ -430,7 +529,7 @@ __device__ __forceinline__ void syn_wave(const LegArgs& a, int mw, int wave, int
 }
 
 template <int C16, int C4, int T>
-__global__ __launch_bounds__(256) void k_leg_syn(LegArgs a, int nmaps, const double* __restrict__ u,
+__global__ __launch_bounds__(256, C4 == 1 && T == 4 ? 4 : 1) void k_leg_syn(LegArgs a, int nmaps, const double* __restrict__ u,
                                                  int64_t ustride, double2* __restrict__ phase,
                                                  int64_t pstride, int ntg) {
   constexpr int NMW = 4 * C16 + C4;
@@ -444,10 +543,12 @@ __global__ __launch_bounds__(256) void k_leg_syn(LegArgs a, int nmaps, const dou
   const int ns = leg_nslots(a, nmaps);
   if (!leg_any(a, map0, NMW, ns)) return;
   const TileRange tr = tile_range<T>(a, tg);
-  if (tr.polar)
-    syn_wave<C16, C4, T, true>(a, m, wave, tr.t0, tr.tend, map0, ns, u, ustride, phase, pstride, qsh);
+  if (tr.form == POLAR)
+    syn_wave<C16, C4, T, POLAR>(a, m, wave, tr.t0, tr.tend, map0, ns, u, ustride, phase, pstride, qsh);
+  else if (tr.form == BELT)
+    syn_wave<C16, C4, T, BELT>(a, m, wave, tr.t0, tr.tend, map0, ns, u, ustride, phase, pstride, qsh);
   else
-    syn_wave<C16, C4, T, false>(a, m, wave, tr.t0, tr.tend, map0, ns, u, ustride, phase, pstride, qsh);
+    syn_wave<C16, C4, 1, EQUATOR>(a, m, wave, tr.t0, tr.tend, map0, ns, u, ustride, phase, pstride, qsh);
 }
 
 // --------------------------------------------------------------- adjoint
@@ -455,7 +556,9 @@ __global__ __launch_bounds__(256) void k_leg_syn(LegArgs a, int nmaps, const dou
 // pairs), with H_E = H_N + H_S and H_O = z (H_N - H_S) held in registers for
 // the wave's T tiles of 64 ring pairs, then v_{m+2k} = eps_{l+1} W^E_k + eps_l
 // W^E_{k-1} and v_{m+2k+1} = W^O_k: one partial v per T tiles (fixed order, no
-// atomics).  T sets the partial sums' traffic (one (L+1)^2 vector per map and T
+// atomics).  In the equator's tile q and H_O sit in slots 0 .. 31, p and H_E in the
+// others (zeros elsewhere), and v_{m+2k} = W^E_k / eps_{l+1}.  T sets the partial
+// sums' traffic (one (L+1)^2 vector per map and T
 // tiles, written here and read by the tile sum).
 
 // Zero partial below the first evaluated k and the row pointers of a column.
@@ -474,10 +577,10 @@ __device__ __forceinline__ AdjOut adj_out(const LegArgs& a, double* vpart, int64
 }
 // H of N ring pairs i0 + 16 (j / IN) + j % IN of a tile in a lane's column (ph:
 // the map's phase array at (ring 0, m, part); par: 0 E, 1 O; in: the tile exists)
-template <int N, int IN>
-__device__ __forceinline__ void adj_h(const LegArgs& a, const double* ph, int tile, bool polar, bool in, int i0, int par,
+template <int F, int N, int IN>
+__device__ __forceinline__ void adj_h(const LegArgs& a, const double* ph, int tile, bool in, int i0, int par,
                                       double (&H)[N]) {
-  const TilePairs tp = tile_pairs(a, tile, polar);
+  const TilePairs tp = tile_pairs<F>(a, tile);
   const int64_t rstep = 2 * (int64_t)(a.lmax + 1);
   const double* z = a.zs + tile * 64 + i0;
   const double sg = par ? -1.0 : 1.0;
@@ -500,9 +603,9 @@ __device__ __forceinline__ void adj_h(const LegArgs& a, const double* ph, int ti
 #pragma unroll
     for (int j = 0; j < N; ++j) {
       const int i = 16 * (j / IN) + j % IN;
-      const int p = tp.p0 + i0 + i, rs = a.nring - 1 - p;
+      const int p = tp.p0 + (F == EQUATOR ? (i0 + i) & 31 : i0 + i), rs = a.nring - 1 - p;
       H[j] = 0.0;
-      if (in && p < tp.limit) {
+      if (in && p < tp.limit && (F != EQUATOR || (i0 + i < 32) == (par != 0))) {
         const double hn = ph[(int64_t)p * rstep];
         const double hs = rs != p ? ph[(int64_t)rs * rstep] : 0.0;  // the equator ring is its own pair
         H[j] = fma(sg, hs, hn) * (par ? z[i] : 1.0);
@@ -516,7 +619,7 @@ __device__ __forceinline__ void adj_h(const LegArgs& a, const double* ph, int ti
 // (j = t % 4: column (E cos, E sin, O cos, O sin), b = (t / 4) % 4, i = t / 16);
 // operand k index t / 16: pair 16 s + b + 4 (t / 16) of H register s; A rows:
 // k = k0 + 8 x + 2 (t % 4) + {0, 1}.  The blocks are summed once per 16 steps.
-template <int NM, int T, bool POLAR>
+template <int NM, int T, int F>
 __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t0, int tend, int map0, int ns,
                                           const double2* __restrict__ phase, int64_t pstride,
                                           double* __restrict__ vpart, int64_t vstride, int64_t tstride, double2* qt) {
@@ -535,13 +638,13 @@ __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t
   for (int t = 0; t < T; ++t) {
     const int s0 = (t0 + t) * 64;
     const bool in = t0 + t < tend;
-    rec_init(r[t], a, m, s0 + lane, in);
+    rec_init<F>(r[t], a, m, s0 + lane, in);
     kst = min(kst, r[t].first);
 #pragma unroll
     for (int c = 0; c < NM; ++c) {
       const double* ph =
           reinterpret_cast<const double*>(phase + (int64_t)leg_map(a, min(map0 + c, ns - 1)) * pstride) + 2 * m + cs;
-      adj_h<4, 1>(a, ph, t0 + t, POLAR, in, b + 4 * hi, par, H[t][c]);
+      adj_h<F, 4, 1>(a, ph, t0 + t, in, b + 4 * hi, par, H[t][c]);
     }
   }
   // zero partial below the first evaluated k (all of it if no lane starts)
@@ -550,9 +653,11 @@ __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t
   for (int c = 0; c < NM; ++c)
     if (out[c].ok && par == 0)
       for (int x = lane >> 2; x < zend; x += 16) out[c].vb[x] = 0.0;
-  cdouble* cb = as_const((POLAR ? a.bp : a.be) + krow(L, m));
+  cdouble* cb = as_const((F == POLAR ? a.bp : a.be) + krow(L, m));
   cdouble* cg = as_const(a.gi + krow(L, m));
+  cdouble* ch = as_const(a.he + krow(L, m));
   const double* er = a.ep + 4 + erow(L, m);
+  const double* rr = a.re + krow(L, m);
   const double cm = m == 0 ? 1.0 : 1.4142135623730951;
   const int kl = 8 * b1 + 2 * (lane >> 4) + b0;  // this lane's k - k0 after the block sums
   // lane of W_{k-1}: the lane of k - 1, whose carry for k = k0 is the last block's k0 + 15
@@ -564,8 +669,8 @@ __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t
   for (int k0 = kst; k0 < K; k0 += 16) {
     k0 = __builtin_amdgcn_readfirstlane(k0);
     const RecCoef<16> C = rec_coef<16>(cb, cg, k0);
-    const double ea = par ? 1.0 : er[2 * (k0 + kl) + 1];
-    const double eb = par ? 0.0 : er[2 * (k0 + kl)];
+    const double ea = par ? 1.0 : F == EQUATOR ? rr[k0 + kl] : er[2 * (k0 + kl) + 1];
+    const double eb = par || F == EQUATOR ? 0.0 : er[2 * (k0 + kl)];
     double D[4][NM];
 #pragma unroll
     for (int x = 0; x < 4; ++x)
@@ -575,10 +680,18 @@ __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t
     for (int t = 0; t < T; ++t) {
       if (r[t].first >= k0 + 16) continue;
       const int slot = (t0 + t) * 64 + lane;
-      rec8<POLAR, 0>(r[t], C, a, m, slot, k0,
-                     [&](int i, double qe, double qo) { qt[i * kQRowAdj4 + lane] = make_double2(qe, qo); });
-      rec8<POLAR, 8>(r[t], C, a, m, slot, k0 + 8,
-                     [&](int i, double qe, double qo) { qt[(4 + i) * kQRowAdj4 + lane] = make_double2(qe, qo); });
+      auto put = [&](int i, double qe, double qo) { qt[i * kQRowAdj4 + lane] = make_double2(qe, qo); };
+      if constexpr (F == EQUATOR) {
+        rec8<F, 0>(r[t], C, rec_h(ch, k0), a, m, slot, k0, [&](int i, double qe, double qo, double pe, double po) {
+          put(i, lane < 32 ? qe : pe, lane < 32 ? qo : po);
+        });
+        rec8<F, 8>(r[t], C, rec_h(ch, k0 + 8), a, m, slot, k0 + 8, [&](int i, double qe, double qo, double pe, double po) {
+          put(4 + i, lane < 32 ? qe : pe, lane < 32 ? qo : po);
+        });
+      } else {
+        rec8<F, 0>(r[t], C, a, m, slot, k0, put);
+        rec8<F, 8>(r[t], C, a, m, slot, k0 + 8, [&](int i, double qe, double qo) { put(4 + i, qe, qo); });
+      }
       wave_fence();
       double2 A[2][4];
 #pragma unroll
@@ -625,10 +738,12 @@ __global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0
   const int ns = leg_nslots(a, nmaps);
   if (!leg_any(a, map0, NM, ns)) return;
   const TileRange tr = tile_range<T>(a, tg);
-  if (tr.polar)
-    adj4_wave<NM, T, true>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+  if (tr.form == POLAR)
+    adj4_wave<NM, T, POLAR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+  else if (tr.form == BELT)
+    adj4_wave<NM, T, BELT>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
   else
-    adj4_wave<NM, T, false>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj4_wave<NM, 1, EQUATOR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
 }
 
 // Groups of four maps: v_mfma_f64_16x16x4, column j = t % 16 = 4 map + 2 (E, O)
@@ -636,7 +751,7 @@ __global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0
 // pairs that block b of k_leg_adj4 takes from H register s, and the four
 // accumulators b are added as its blocks are: a map's result does not depend
 // on how many maps run beside it.
-template <int T, bool POLAR>
+template <int T, int F>
 __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int t0, int tend, int map0, int ns,
                                            const double2* __restrict__ phase, int64_t pstride,
                                            double* __restrict__ vpart, int64_t vstride, int64_t tstride, double2* qt) {
@@ -655,18 +770,20 @@ __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int 
   for (int t = 0; t < T; ++t) {
     const int s0 = (t0 + t) * 64;
     const bool in = t0 + t < tend;
-    rec_init(r[t], a, m, s0 + lane, in);
+    rec_init<F>(r[t], a, m, s0 + lane, in);
     kst = min(kst, r[t].first);
     const double* ph =
         reinterpret_cast<const double*>(phase + (int64_t)leg_map(a, min(slot, ns - 1)) * pstride) + 2 * m + cs;
-    adj_h<16, 4>(a, ph, t0 + t, POLAR, in, 4 * kq, par, H[t]);
+    adj_h<F, 16, 4>(a, ph, t0 + t, in, 4 * kq, par, H[t]);
   }
   const int zend = min(2 * min(kst, K), n + 1);
   if (out.ok && par == 0)
     for (int x = kq; x < zend; x += 4) out.vb[x] = 0.0;
-  cdouble* cb = as_const((POLAR ? a.bp : a.be) + krow(L, m));
+  cdouble* cb = as_const((F == POLAR ? a.bp : a.be) + krow(L, m));
   cdouble* cg = as_const(a.gi + krow(L, m));
+  cdouble* ch = as_const(a.he + krow(L, m));
   const double* er = a.ep + 4 + erow(L, m);
+  const double* rr = a.re + krow(L, m);
   const double cm = m == 0 ? 1.0 : 1.4142135623730951;
   double Wp = 0.0;  // D[3] of the last block: its row 15 sits in lanes 48..63
   for (int k0 = kst; k0 < K; k0 += 16) {
@@ -679,10 +796,18 @@ __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int 
     for (int t = 0; t < T; ++t) {
       if (r[t].first >= k0 + 16) continue;
       const int sl = (t0 + t) * 64 + lane;
-      rec8<POLAR, 0>(r[t], C, a, m, sl, k0,
-                     [&](int i, double qe, double qo) { qt[i * kQRowAdj16 + lane] = make_double2(qe, qo); });
-      rec8<POLAR, 8>(r[t], C, a, m, sl, k0 + 8,
-                     [&](int i, double qe, double qo) { qt[(4 + i) * kQRowAdj16 + lane] = make_double2(qe, qo); });
+      auto put = [&](int i, double qe, double qo) { qt[i * kQRowAdj16 + lane] = make_double2(qe, qo); };
+      if constexpr (F == EQUATOR) {
+        rec8<F, 0>(r[t], C, rec_h(ch, k0), a, m, sl, k0, [&](int i, double qe, double qo, double pe, double po) {
+          put(i, lane < 32 ? qe : pe, lane < 32 ? qo : po);
+        });
+        rec8<F, 8>(r[t], C, rec_h(ch, k0 + 8), a, m, sl, k0 + 8, [&](int i, double qe, double qo, double pe, double po) {
+          put(4 + i, lane < 32 ? qe : pe, lane < 32 ? qo : po);
+        });
+      } else {
+        rec8<F, 0>(r[t], C, a, m, sl, k0, put);
+        rec8<F, 8>(r[t], C, a, m, sl, k0 + 8, [&](int i, double qe, double qo) { put(4 + i, qe, qo); });
+      }
       wave_fence();
       double A[16];
 #pragma unroll
@@ -700,7 +825,8 @@ __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int 
       const double prev = q == 0 ? Wp : W[q > 0 ? q - 1 : 0];
       const double Wm = lane_get(kq == 3 ? prev : W[q], (lane + 48) & 63);
       const int x = 2 * (k0 + kq + 4 * q);
-      const double ea = par ? 1.0 : er[x + 1], eb = par ? 0.0 : er[x];
+      const double ea = par ? 1.0 : F == EQUATOR ? rr[k0 + kq + 4 * q] : er[x + 1];
+      const double eb = par || F == EQUATOR ? 0.0 : er[x];
       if (out.ok && x + par <= n) out.vb[x + par] = cm * fma(eb, Wm, ea * W[q]);
     }
     Wp = W[3];
@@ -721,10 +847,12 @@ __global__ __launch_bounds__(256, 2) void k_leg_adj16(LegArgs a, int nmaps, cons
   const int ns = leg_nslots(a, nmaps);
   if (!leg_any(a, map0, 4, ns)) return;
   const TileRange tr = tile_range<T>(a, tg);
-  if (tr.polar)
-    adj16_wave<T, true>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+  if (tr.form == POLAR)
+    adj16_wave<T, POLAR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+  else if (tr.form == BELT)
+    adj16_wave<T, BELT>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
   else
-    adj16_wave<T, false>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj16_wave<1, EQUATOR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
 }
 
 // Squared functions (M_diag setup, Sect. 5): v_lm = sum_r lambda_lm^2 G_m(r) of
@@ -754,45 +882,67 @@ __global__ __launch_bounds__(256) void k_leg_adj_sq(LegArgs a, const double2* __
   const int lane = threadIdx.x & 63;
   const int n = L - m, K = n / 2 + 1, slot = tile * 64 + lane;
   RecState r;
-  rec_init(r, a, m, slot, true);
-  const double* ph = reinterpret_cast<const double*>(phase) + 2 * m;
-  double G[2][1];
-  adj_h<1, 1>(a, ph, tile, tile < a.pol_tiles, true, lane, 0, G[0]);
-  adj_h<1, 1>(a, ph + 1, tile, tile < a.pol_tiles, true, lane, 0, G[1]);
+  const bool polar = tile < a.pol_tiles;
+  if (polar)
+    rec_init<POLAR>(r, a, m, slot, true);
+  else
+    rec_init<EQUATOR>(r, a, m, slot, true);
+  // north plus south (the equator's pairs once)
+  const bool last = tile == a.nslots / 64 - 1;
+  const TilePairs tp = polar ? tile_pairs<POLAR>(a, tile) : last ? tile_pairs<EQUATOR>(a, tile) : tile_pairs<BELT>(a, tile);
+  double2 G = make_double2(0.0, 0.0);
+  const int pair = tp.p0 + lane, south = a.nring - 1 - pair;
+  if (pair < tp.limit && !(last && lane >= 32)) {
+    G = phase[(int64_t)pair * (L + 1) + m];
+    if (south != pair) {
+      const double2 g = phase[(int64_t)south * (L + 1) + m];
+      G.x += g.x;
+      G.y += g.y;
+    }
+  }
   const double z = a.zs[slot];
   double* vb = vpart + (int64_t)tile * tstride + moff(L, m);
   const int np = m == 0 ? 1 : 2;
   const int zend = min(2 * min(r.first, K), n + 1);
   for (int x = lane; x < zend * np; x += 64) vb[x < zend ? x : n + 1 + x - zend] = 0.0;
-  const bool polar = tile < a.pol_tiles;
   cdouble* cb = as_const((polar ? a.bp : a.be) + krow(L, m));
   cdouble* cg = as_const(a.gi + krow(L, m));
+  cdouble* ch = as_const(a.he + krow(L, m));
   cdouble* er = as_const(a.ep + 4 + erow(L, m));
+  cdouble* re = as_const(a.re + krow(L, m));
   double qm = 0.0;  // q_{k-1}
   for (int k0 = r.first; k0 < K; k0 += 8) {
     k0 = __builtin_amdgcn_readfirstlane(k0);
     const RecCoef<8> C = rec_coef<8>(cb, cg, k0);
-    double q[8];
-    auto put = [&](int i, double qe, double qo) {
-      q[2 * i] = qe;
-      q[2 * i + 1] = qo;
-    };
-    if (polar)
-      rec8<true, 0>(r, C, a, m, slot, k0, put);
-    else
-      rec8<false, 0>(r, C, a, m, slot, k0, put);
+    double q[8], le[8];  // le: lambda_{m+2k}
+    if (polar) {
+      rec8<POLAR, 0>(r, C, a, m, slot, k0, [&](int i, double qe, double qo) {
+        q[2 * i] = qe;
+        q[2 * i + 1] = qo;
+      });
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        le[i] = fma(er[2 * (k0 + i)], qm, er[2 * (k0 + i) + 1] * q[i]);
+        qm = q[i];
+      }
+    } else {
+      rec8<EQUATOR, 0>(r, C, rec_h(ch, k0), a, m, slot, k0, [&](int i, double qe, double qo, double pe, double po) {
+        q[2 * i] = qe;
+        q[2 * i + 1] = qo;
+        le[2 * i] = re[k0 + 2 * i] * pe;
+        le[2 * i + 1] = re[k0 + 2 * i + 1] * po;
+      });
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int x = 2 * (k0 + 4 * h + i);
-        const double le = fma(er[x], qm, er[x + 1] * q[4 * h + i]);
-        const double lo = z * q[4 * h + i];
-        qm = q[4 * h + i];
+        const double lo = z * q[4 * h + i], ev = le[4 * h + i];
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-          wb[(4 * i + c) * kRedRow + lane] = le * le * G[c][0];
-          wb[(4 * i + 2 + c) * kRedRow + lane] = lo * lo * G[c][0];
+          const double g = c ? G.y : G.x;
+          wb[(4 * i + c) * kRedRow + lane] = ev * ev * g;
+          wb[(4 * i + 2 + c) * kRedRow + lane] = lo * lo * g;
         }
       }
       wave_fence();
@@ -918,7 +1068,7 @@ static unsigned leg_blocks(int L, int ntg) { return (unsigned)(((L + 1 + 3) / 4 
 
 // tile groups of T (tile_range)
 static int tile_groups(int pol_tiles, int nslots, int T) {
-  return (pol_tiles + T - 1) / T + (nslots / 64 - pol_tiles + T - 1) / T;
+  return (pol_tiles + T - 1) / T + (nslots / 64 - 1 - pol_tiles + T - 1) / T + 1;
 }
 
 void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const double* u, int64_t ustride,
