@@ -124,8 +124,11 @@ int crs_sht_reserve(crs_grid g, int lmax, int nmaps, crs_stream s);
  * Preconditions: the (grid, lmax) Legendre tables already exist (created by
  * any earlier sht_synth / sht_adjoint on that pair, or by a model using it);
  * otherwise CRS_EINVAL.  A request whose scratch exceeds 64 MiB (e.g. more
- * than about two maps at HEALPix Nside 256 / lmax 512) returns CRS_EINVAL
- * with the needed size in the message.  All calls on one GPU share that
+ * than three maps at HEALPix Nside 256 / lmax 512) returns CRS_EINVAL with the
+ * needed size in the message.  The scratch is, per map, nrings (lmax + 1) complex
+ * numbers and the partial sums that the kernel keeps beside the result, vectors
+ * of (lmax + 1)^2 numbers: at most one per 128 pairs of rings (north and south),
+ * at least one.  All calls on one GPU share that
  * GPU's array: calls that overlap in time on one GPU (different streams or
  * threads) race and must be serialised by the caller.  Nothing in the array
  * needs clearing between calls: every scratch entry is written before it is

@@ -1,4 +1,5 @@
 // Error handling, profiling hooks and the public transform entry points.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -304,8 +305,8 @@ int crs_sht_reserve(crs_grid g, int lmax, int nmaps, crs_stream st) {
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 1);
     const int64_t pst = (int64_t)g->nring * (lmax + 1);
     w.phase.alloc((size_t)nmaps * pst);
-    // the largest tile count of any adjoint variant (one 64-pair tile per wave)
-    w.vpart.alloc((size_t)(p.nslots / 64) * nmaps * nalm);
+    // the most partial vectors of any adjoint variant beside the result (one 64-pair tile per wave)
+    w.vpart.alloc((size_t)(p.nslots / 64 - 1) * nmaps * nalm);
     CRS_HIP(hipStreamSynchronize(s));
     return CRS_OK;
   });
@@ -351,9 +352,7 @@ int sht_adjoint(crs_grid g, int lmax, int nmaps, const double* map, int64_t map_
     const LegChoice lc = leg_choice(p.npairs, lmax, nmaps);
     const int ntiles = leg_adjoint_tiles(lc, g, false);
     w.phase.alloc((size_t)nmaps * pst);
-    // one tile: the Legendre kernel's partial is the result
-    const bool direct = ntiles == 1;
-    if (!direct) w.vpart.alloc((size_t)ntiles * nmaps * nalm);
+    w.vpart.alloc((size_t)(ntiles - 1) * nmaps * nalm);
     {
       ProfScope ps(FAM_RING, bytes_work(ring_bytes(g, lmax, nmaps, RING_ADJOINT)), s);
       launch_ring(g, lmax, RING_ADJOINT, nmaps, w.phase.p, pst, map, nullptr, map_stride,
@@ -361,11 +360,10 @@ int sht_adjoint(crs_grid g, int lmax, int nmaps, const double* map, int64_t map_
     }
     {
       ProfScope ps(FAM_LEG_ADJ, leg_work(p, nmaps), s);
-      launch_leg_adjoint(lc, leg_args(g, p), nmaps, w.phase.p, pst, direct ? alm : w.vpart.p,
-                         direct ? alm_stride : nalm, (int64_t)nmaps * nalm, false, s);
+      launch_leg_adjoint(lc, leg_args(g, p), nmaps, w.phase.p, pst,
+                         AdjDst{alm, alm_stride, w.vpart.p, nalm, (int64_t)nmaps * nalm, 0, ntiles}, false, s);
     }
-    if (!direct)
-      launch_tile_sum(nalm, nmaps, w.vpart.p, nalm, ntiles, (int64_t)nmaps * nalm, alm, alm_stride, s);
+    launch_tile_sum(nalm, nmaps, w.vpart.p, nalm, ntiles - 1, (int64_t)nmaps * nalm, alm, alm_stride, s);
     return CRS_OK;
   });
 }
@@ -422,7 +420,11 @@ int sht_adjoint_noalloc(crs_grid g, int lmax, int nmaps, const double* map, int6
     const LegChoice lc = leg_choice(p.npairs, lmax, nmaps);
     const int ntiles = leg_adjoint_tiles(lc, g, false);
     const size_t phase_bytes = align256((size_t)nmaps * pst * sizeof(double2));
-    const size_t part_bytes = align256((size_t)ntiles * nmaps * nalm * sizeof(double));
+    // Partial vectors beside the result, per map: one per tile group after the
+    // first, but no more than one per 128 ring pairs.  Where the groups are more
+    // (small grids, whose tiles are padded) they take turns.
+    const int parts = std::min(ntiles - 1, std::max(1, ((p.npairs + 63) / 64 + 1) / 2));
+    const size_t part_bytes = align256((size_t)parts * nmaps * nalm * sizeof(double));
     CRS_CHECK(phase_bytes + part_bytes <= kNoAllocScratchBytes, CRS_EINVAL,
               "sht_adjoint_noalloc needs " + std::to_string(phase_bytes + part_bytes) +
                   " bytes of scratch for this (grid, lmax, nmaps); its limit is " +
@@ -431,17 +433,23 @@ int sht_adjoint_noalloc(crs_grid g, int lmax, int nmaps, const double* map, int6
     double2* phase = reinterpret_cast<double2*>(base);
     double* vpart = reinterpret_cast<double*>(base + phase_bytes);
     // every entry of both scratch regions is written before it is read: the
-    // ring stage writes all m <= lmax of every ring and map, and every tile of
-    // the Legendre adjoint writes its whole partial vector
+    // ring stage writes all m <= lmax of every ring and map, and every tile
+    // group of the Legendre adjoint writes its whole partial vector
     {
       ProfScope ps(FAM_RING, bytes_work(ring_bytes(g, lmax, nmaps, RING_ADJOINT)), s);
       launch_ring(g, lmax, RING_ADJOINT, nmaps, phase, pst, map, nullptr, map_stride, nullptr, 1, s);
     }
-    {
-      ProfScope ps(FAM_LEG_ADJ, leg_work(p, nmaps), s);
-      launch_leg_adjoint(lc, leg_args(g, p), nmaps, phase, pst, vpart, nalm, (int64_t)nmaps * nalm, false, s);
+    const int64_t tstride = (int64_t)nmaps * nalm;
+    for (int g0 = 0; g0 < ntiles;) {
+      const int ng = std::min(ntiles - g0, g0 == 0 ? parts + 1 : parts);
+      {
+        ProfScope ps(FAM_LEG_ADJ, g0 == 0 ? leg_work(p, nmaps) : Work3{}, s);
+        launch_leg_adjoint(lc, leg_args(g, p), nmaps, phase, pst, AdjDst{alm, alm_stride, vpart, nalm, tstride, g0, ng},
+                           false, s);
+      }
+      launch_tile_sum(nalm, nmaps, vpart, nalm, g0 == 0 ? ng - 1 : ng, tstride, alm, alm_stride, s);
+      g0 += ng;
     }
-    launch_tile_sum(nalm, nmaps, vpart, nalm, ntiles, (int64_t)nmaps * nalm, alm, alm_stride, s);
     return CRS_OK;
   });
 }

@@ -1010,8 +1010,7 @@ void exec_bands(Exec& e, OpKind kind, const double* in, hipStream_t s0, const do
     }
     {
       ProfScope ps(FAM_LEG_ADJ, group_work(e, gi, FAM_LEG_ADJ, skip_done, pinv), s, tag);
-      launch_leg_adjoint(g.leg, la, g.nmaps, g.phase.p, g.pst, g.vpart.p, g.nalm, (int64_t)g.nmaps * g.nalm, false,
-                         s);
+      launch_leg_adjoint(g.leg, la, g.nmaps, g.phase.p, g.pst, adj_dst(g.vpart.p, g.nalm, g.nmaps, g.ntiles), false, s);
     }
   };
   // The groups' mixing and active-map kernels run as one launch each on the
@@ -1120,8 +1119,8 @@ void exec_rhs_bands(Exec& e, const std::vector<std::vector<const double*>>& d,
                        g.wptr.p, npix);
     CRS_HIP(hipGetLastError());
     launch_ring(g.grid, g.lmax, RING_ADJOINT, g.nmaps, g.phase.p, g.pst, g.pix.p, nullptr, npix, nullptr, 1, s);
-    launch_leg_adjoint(g.leg, leg_args(g.grid, *g.plan), g.nmaps, g.phase.p, g.pst, g.vpart.p, g.nalm,
-                       (int64_t)g.nmaps * g.nalm, false, s);
+    launch_leg_adjoint(g.leg, leg_args(g.grid, *g.plan), g.nmaps, g.phase.p, g.pst,
+                       adj_dst(g.vpart.p, g.nalm, g.nmaps, g.ntiles), false, s);
   }
   // the pointer tables were uploaded from host temporaries: finish before they go
   CRS_HIP(hipStreamSynchronize(s));

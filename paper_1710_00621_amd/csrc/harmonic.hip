@@ -171,7 +171,7 @@ int scratch_adjoint(ShtScratch& w, crs_grid g, int L, int nm, const double* map,
   }
   {
     ProfScope ps(FAM_LEG_ADJ, leg_work(p, nm), s);
-    launch_leg_adjoint(c, la, nm, w.phase.p, pst, w.parts.p, nalm_of(L), (int64_t)nm * nalm_of(L), false, s);
+    launch_leg_adjoint(c, la, nm, w.phase.p, pst, adj_dst(w.parts.p, nalm_of(L), nm, nt), false, s);
   }
   return nt;
 }

@@ -253,12 +253,27 @@ LegChoice leg_autotune(const LegArgs& a, int nmaps, double* uhat, double2* phase
 // phase: [nmaps][nring][L+1] double2 (cos, sin parts)
 void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const double* u, int64_t ustride,
                       double2* phase, int64_t pstride, hipStream_t s);
-// Adjoint: writes ntiles partial vectors vpart[tile][map][nalm], ntiles as
-// returned here for the same choice and square flag as the launch.
+// Adjoint: one partial vector per tile group and map, as many groups as
+// returned here for the same choice and square flag as the launch.  The first
+// group's goes to v0 + map v0stride (the result's own place: only the others
+// need scratch, and launch_tile_sum adds them to it), the following ones to
+// v + i tstride + map vstride.  g0, ng: the launch's groups (all: 0, the count;
+// with g0 > 0 group g0 + i goes to v + i tstride).
+struct AdjDst {
+  double* v0;
+  int64_t v0stride;
+  double* v;
+  int64_t vstride, tstride;
+  int g0, ng;
+};
+// all groups to v[group][map][nalm]
+inline AdjDst adj_dst(double* v, int64_t nalm, int nmaps, int ng) {
+  const int64_t t = (int64_t)nmaps * nalm;
+  return {v, nalm, v + t, nalm, t, 0, ng};
+}
 int leg_adjoint_tiles(const LegChoice& c, crs_grid g, bool square);
 void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const double2* phase, int64_t pstride,
-                        double* vpart, int64_t vstride, int64_t tstride, bool square,
-                        hipStream_t s);
+                        const AdjDst& dst, bool square, hipStream_t s);
 
 // Ring FFT stage.
 enum RingMode { RING_SYNTH = 0, RING_ADJOINT = 1, RING_ROUNDTRIP = 2, RING_DIAG = 3 };
@@ -277,7 +292,7 @@ void launch_ring(crs_grid g, int lmax, RingMode mode, int nmaps, double2* phase,
                  const double* const* weights, int maps_per_weight, hipStream_t s,
                  MapSkip skip = MapSkip{});
 
-// out[map] = sum_t in[t][map] elementwise over the packed alm index.
+// out[map] += sum_t in[t][map] elementwise over the packed alm index, in order of t.
 void launch_tile_sum(int64_t nalm, int nmaps, const double* in, int64_t istride, int ntiles, int64_t tstride,
                      double* out, int64_t ostride, hipStream_t s);
 

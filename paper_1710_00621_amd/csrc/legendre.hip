@@ -566,13 +566,18 @@ struct AdjOut {
   double* vb;  // index l - m of the lane's part
   bool ok;
 };
-__device__ __forceinline__ AdjOut adj_out(const LegArgs& a, double* vpart, int64_t vstride, int64_t tstride, int tg,
-                                          int m, int slot, int ns, int cs) {
+// the map's vector in group tg's partial
+__device__ __forceinline__ double* adj_part(const AdjDst& d, int tg, int map) {
+  if (tg == 0) return d.v0 + (int64_t)map * d.v0stride;
+  return d.v + (int64_t)(tg - (d.g0 == 0 ? 1 : d.g0)) * d.tstride + (int64_t)map * d.vstride;
+}
+__device__ __forceinline__ AdjOut adj_out(const LegArgs& a, const AdjDst& dst, int tg, int m, int slot, int ns,
+                                          int cs) {
   AdjOut o;
   const int L = a.lmax;
   o.ok = slot < ns && !(m == 0 && cs);
   const int mp = leg_map(a, min(slot, ns - 1));
-  o.vb = vpart + (int64_t)tg * tstride + (int64_t)mp * vstride + moff(L, m) + (cs && m > 0 ? L - m + 1 : 0);
+  o.vb = adj_part(dst, tg, mp) + moff(L, m) + (cs && m > 0 ? L - m + 1 : 0);
   return o;
 }
 // H of N ring pairs i0 + 16 (j / IN) + j % IN of a tile in a lane's column (ph:
@@ -621,8 +626,8 @@ __device__ __forceinline__ void adj_h(const LegArgs& a, const double* ph, int ti
 // k = k0 + 8 x + 2 (t % 4) + {0, 1}.  The blocks are summed once per 16 steps.
 template <int NM, int T, int F>
 __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t0, int tend, int map0, int ns,
-                                          const double2* __restrict__ phase, int64_t pstride,
-                                          double* __restrict__ vpart, int64_t vstride, int64_t tstride, double2* qt) {
+                                          const double2* __restrict__ phase, int64_t pstride, const AdjDst& dst,
+                                          double2* qt) {
   const int L = a.lmax;
   const int lane = threadIdx.x & 63;
   const int b = (lane >> 2) & 3, b0 = b & 1, b1 = b >> 1, hi = lane >> 4;
@@ -633,7 +638,7 @@ __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t
   AdjOut out[NM];
   int kst = INT_MAX;
 #pragma unroll
-  for (int c = 0; c < NM; ++c) out[c] = adj_out(a, vpart, vstride, tstride, tg, m, map0 + c, ns, cs);
+  for (int c = 0; c < NM; ++c) out[c] = adj_out(a, dst, tg, m, map0 + c, ns, cs);
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     const int s0 = (t0 + t) * 64;
@@ -726,11 +731,11 @@ __device__ __forceinline__ void adj4_wave(const LegArgs& a, int m, int tg, int t
 
 template <int NM, int T>
 __global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0, const double2* __restrict__ phase,
-                                                  int64_t pstride, double* __restrict__ vpart, int64_t vstride,
-                                                  int64_t tstride, int ntg) {
+                                                  int64_t pstride, AdjDst dst) {
   __shared__ double2 qsh[4][8 * kQRowAdj4];
   int mb, tg;
-  block_coords(ntg, mb, tg);
+  block_coords(dst.ng, mb, tg);
+  tg += dst.g0;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = mb * 4 + wave;
   if (m > a.lmax) return;
@@ -739,11 +744,11 @@ __global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0
   if (!leg_any(a, map0, NM, ns)) return;
   const TileRange tr = tile_range<T>(a, tg);
   if (tr.form == POLAR)
-    adj4_wave<NM, T, POLAR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj4_wave<NM, T, POLAR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, dst, qsh[wave]);
   else if (tr.form == BELT)
-    adj4_wave<NM, T, BELT>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj4_wave<NM, T, BELT>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, dst, qsh[wave]);
   else
-    adj4_wave<NM, 1, EQUATOR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj4_wave<NM, 1, EQUATOR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, dst, qsh[wave]);
 }
 
 // Groups of four maps: v_mfma_f64_16x16x4, column j = t % 16 = 4 map + 2 (E, O)
@@ -753,8 +758,8 @@ __global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0
 // on how many maps run beside it.
 template <int T, int F>
 __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int t0, int tend, int map0, int ns,
-                                           const double2* __restrict__ phase, int64_t pstride,
-                                           double* __restrict__ vpart, int64_t vstride, int64_t tstride, double2* qt) {
+                                           const double2* __restrict__ phase, int64_t pstride, const AdjDst& dst,
+                                           double2* qt) {
   const int L = a.lmax;
   const double* qd = reinterpret_cast<const double*>(qt);
   const int lane = threadIdx.x & 63;
@@ -762,7 +767,7 @@ __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int 
   const int par = (lane >> 1) & 1, cs = lane & 1;
   const int n = L - m, K = n / 2 + 1;
   const int slot = map0 + ((lane >> 2) & 3);
-  const AdjOut out = adj_out(a, vpart, vstride, tstride, tg, m, slot, ns, cs);
+  const AdjOut out = adj_out(a, dst, tg, m, slot, ns, cs);
   RecState r[T];
   double H[T][16];
   int kst = INT_MAX;
@@ -835,11 +840,11 @@ __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int 
 
 template <int T>
 __global__ __launch_bounds__(256, 2) void k_leg_adj16(LegArgs a, int nmaps, const double2* __restrict__ phase,
-                                                      int64_t pstride, double* __restrict__ vpart, int64_t vstride,
-                                                      int64_t tstride, int ntg) {
+                                                      int64_t pstride, AdjDst dst) {
   __shared__ double2 qsh[4][8 * kQRowAdj16];
   int mb, tg;
-  block_coords(ntg, mb, tg);
+  block_coords(dst.ng, mb, tg);
+  tg += dst.g0;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = mb * 4 + wave;
   if (m > a.lmax) return;
@@ -848,11 +853,11 @@ __global__ __launch_bounds__(256, 2) void k_leg_adj16(LegArgs a, int nmaps, cons
   if (!leg_any(a, map0, 4, ns)) return;
   const TileRange tr = tile_range<T>(a, tg);
   if (tr.form == POLAR)
-    adj16_wave<T, POLAR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj16_wave<T, POLAR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, dst, qsh[wave]);
   else if (tr.form == BELT)
-    adj16_wave<T, BELT>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj16_wave<T, BELT>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, dst, qsh[wave]);
   else
-    adj16_wave<1, EQUATOR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, vpart, vstride, tstride, qsh[wave]);
+    adj16_wave<1, EQUATOR>(a, m, tg, tr.t0, tr.tend, map0, ns, phase, pstride, dst, qsh[wave]);
 }
 
 // Squared functions (M_diag setup, Sect. 5): v_lm = sum_r lambda_lm^2 G_m(r) of
@@ -870,10 +875,11 @@ __device__ __forceinline__ double add_xor16(double v) {
   return x + y;
 }
 __global__ __launch_bounds__(256) void k_leg_adj_sq(LegArgs a, const double2* __restrict__ phase,
-                                                    double* __restrict__ vpart, int64_t tstride, int ntg) {
+                                                    AdjDst dst) {
   __shared__ double red[4][16 * kRedRow];
   int mb, tile;
-  block_coords(ntg, mb, tile);
+  block_coords(dst.ng, mb, tile);
+  tile += dst.g0;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int m = mb * 4 + wave;
   const int L = a.lmax;
@@ -901,7 +907,7 @@ __global__ __launch_bounds__(256) void k_leg_adj_sq(LegArgs a, const double2* __
     }
   }
   const double z = a.zs[slot];
-  double* vb = vpart + (int64_t)tile * tstride + moff(L, m);
+  double* vb = adj_part(dst, tile, 0) + moff(L, m);
   const int np = m == 0 ? 1 : 2;
   const int zend = min(2 * min(r.first, K), n + 1);
   for (int x = lane; x < zend * np; x += 64) vb[x < zend ? x : n + 1 + x - zend] = 0.0;
@@ -1118,13 +1124,11 @@ int leg_adjoint_tiles(const LegChoice& c, crs_grid g, bool square) {
 }
 
 void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const double2* phase, int64_t pstride,
-                        double* vpart, int64_t vstride, int64_t tstride, bool square,
-                        hipStream_t s) {
-  const int ntg = tile_groups(a.pol_tiles, a.nslots, square ? 1 : c.adj_t);
-  const unsigned nb = leg_blocks(a.lmax, ntg);
+                        const AdjDst& dst, bool square, hipStream_t s) {
+  const unsigned nb = leg_blocks(a.lmax, dst.ng);
   if (square) {
     CRS_CHECK(nmaps == 1, CRS_EINVAL, "the squared adjoint takes one map");
-    hipLaunchKernelGGL(k_leg_adj_sq, dim3(nb), dim3(256), 0, s, a, phase, vpart, tstride, ntg);
+    hipLaunchKernelGGL(k_leg_adj_sq, dim3(nb), dim3(256), 0, s, a, phase, dst);
     CRS_HIP(hipGetLastError());
     return;
   }
@@ -1132,10 +1136,10 @@ void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const d
   const int g16 = g.n16;
 #define CRS_ADJ16(TT)                                                                                 \
   hipLaunchKernelGGL((k_leg_adj16<TT>), dim3(nb, g16), dim3(256), 0, s, a, nmaps, phase, pstride,     \
-                     vpart, vstride, tstride, ntg)
+                     dst)
 #define CRS_ADJ4(N, TT)                                                                               \
-  hipLaunchKernelGGL((k_leg_adj4<N, TT>), dim3(nb, (nmaps - 4 * g16 + N - 1) / N), dim3(256), 0, s, a, nmaps, 4 * g16, phase,        \
-                     pstride, vpart, vstride, tstride, ntg)
+  hipLaunchKernelGGL((k_leg_adj4<N, TT>), dim3(nb, (nmaps - 4 * g16 + N - 1) / N), dim3(256), 0, s, a, \
+                     nmaps, 4 * g16, phase, pstride, dst)
 #define CRS_ADJ4T(N)                                                                                  \
   do {                                                                                                \
     if (c.adj_t == 4) CRS_ADJ4(N, 4);                                                                 \
@@ -1183,9 +1187,9 @@ LegChoice leg_autotune(const LegArgs& a0, int nmaps, double* uhat, double2* phas
   const int64_t pst = (int64_t)a.nring * (L + 1);
   LegChoice best = default_choice(a.npairs, L, nmaps);
   const int tiles = a.nslots / 64;
-  // the largest partial-sum count of any candidate (one tile per wave)
+  // the largest partial-sum count of any candidate (one tile per wave; the first goes to uhat)
   DevBuf<double> vpart;
-  vpart.alloc((size_t)tiles * nmaps * nalm);
+  vpart.alloc((size_t)(tiles - 1) * nmaps * nalm);
   CRS_HIP(hipMemsetAsync(uhat, 0, (size_t)nmaps * nalm * sizeof(double), s));
   CRS_HIP(hipMemsetAsync(phase, 0, (size_t)nmaps * pst * sizeof(double2), s));
   const int reps = 3;
@@ -1208,8 +1212,9 @@ LegChoice leg_autotune(const LegArgs& a0, int nmaps, double* uhat, double2* phas
     c.adj_t = t;
     const int nt = tile_groups(a.pol_tiles, a.nslots, t);
     const float ms = time_launches([&] {
-      launch_leg_adjoint(c, a, nmaps, phase, pst, vpart.p, nalm, (int64_t)nmaps * nalm, false, s);
-      launch_tile_sum(nalm, nmaps, vpart.p, nalm, nt, (int64_t)nmaps * nalm, uhat, nalm, s);
+      launch_leg_adjoint(c, a, nmaps, phase, pst, AdjDst{uhat, nalm, vpart.p, nalm, (int64_t)nmaps * nalm, 0, nt}, false,
+                         s);
+      launch_tile_sum(nalm, nmaps, vpart.p, nalm, nt - 1, (int64_t)nmaps * nalm, uhat, nalm, s);
     }, reps, s);
     if (ms < tbest) {
       tbest = ms;
@@ -1232,7 +1237,7 @@ __global__ void k_tile_sum(int64_t nalm, const double* __restrict__ in, int64_t 
   const int map = blockIdx.y;
   const double* __restrict__ src = in + (int64_t)map * istride;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nalm; i += (int64_t)gridDim.x * blockDim.x) {
-    double acc = 0.0;
+    double acc = out[(int64_t)map * ostride + i];
     for (int t = 0; t < ntiles; ++t) acc += src[(int64_t)t * tstride + i];
     out[(int64_t)map * ostride + i] = acc;
   }
@@ -1241,6 +1246,7 @@ __global__ void k_tile_sum(int64_t nalm, const double* __restrict__ in, int64_t 
 
 void launch_tile_sum(int64_t nalm, int nmaps, const double* in, int64_t istride, int ntiles, int64_t tstride,
                      double* out, int64_t ostride, hipStream_t s) {
+  if (ntiles < 1) return;
   const int64_t nb = std::min<int64_t>((nalm + 255) / 256, 4096);
   hipLaunchKernelGGL(k_tile_sum, dim3((unsigned)nb, nmaps), dim3(256), 0, s, nalm, in, istride, ntiles, tstride,
                      out, ostride);

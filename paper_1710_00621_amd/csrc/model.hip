@@ -213,11 +213,11 @@ void build_diag(crs_model m, hipStream_t s) {
     DevBuf<double2> ph;
     DevBuf<double> vp, out;
     ph.alloc((size_t)pst);
-    vp.alloc((size_t)ntiles * nalm);
+    vp.alloc((size_t)(ntiles - 1) * nalm);
     out.alloc((size_t)nalm);
     launch_ring(b.grid, b.lmax, RING_DIAG, 1, ph.p, pst, b.tau.p, nullptr, b.grid->npix, nullptr, 1, s);
-    launch_leg_adjoint(lc, leg_args(b.grid, p), 1, ph.p, pst, vp.p, nalm, nalm, true, s);
-    launch_tile_sum(nalm, 1, vp.p, nalm, ntiles, nalm, out.p, nalm, s);
+    launch_leg_adjoint(lc, leg_args(b.grid, p), 1, ph.p, pst, AdjDst{out.p, nalm, vp.p, nalm, nalm, 0, ntiles}, true, s);
+    launch_tile_sum(nalm, 1, vp.p, nalm, ntiles - 1, nalm, out.p, nalm, s);
     dg[nu].resize(nalm);
     CRS_HIP(hipMemcpyAsync(dg[nu].data(), out.p, nalm * sizeof(double), hipMemcpyDeviceToHost, s));
     CRS_HIP(hipStreamSynchronize(s));
