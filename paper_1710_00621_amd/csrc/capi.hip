@@ -326,7 +326,7 @@ int sht_synth(crs_grid g, int lmax, int nmaps, const double* alm, int64_t alm_st
     w.phase.alloc((size_t)nmaps * pst);
     {
       ProfScope ps(FAM_LEG_SYNTH, leg_work(p, nmaps), s);
-      launch_leg_synth(leg_choice(p.npairs, lmax, nmaps), leg_args(g, p), nmaps, alm, alm_stride, w.phase.p, pst, s);
+      launch_leg_synth(leg_choice(g, lmax, nmaps), leg_args(g, p), nmaps, alm, alm_stride, w.phase.p, pst, s);
     }
     {
       ProfScope ps(FAM_RING, bytes_work(ring_bytes(g, lmax, nmaps, RING_SYNTH)), s);
@@ -349,7 +349,7 @@ int sht_adjoint(crs_grid g, int lmax, int nmaps, const double* map, int64_t map_
     GridWork& w = *g->work;
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 1);
     const int64_t pst = (int64_t)g->nring * (lmax + 1);
-    const LegChoice lc = leg_choice(p.npairs, lmax, nmaps);
+    const LegChoice lc = leg_choice(g, lmax, nmaps);
     const int ntiles = leg_adjoint_tiles(lc, g, false);
     w.phase.alloc((size_t)nmaps * pst);
     w.vpart.alloc((size_t)(ntiles - 1) * nmaps * nalm);
@@ -417,7 +417,7 @@ int sht_adjoint_noalloc(crs_grid g, int lmax, int nmaps, const double* map, int6
     ShtPlan& p = *it->second;
     const int64_t nalm = (int64_t)(lmax + 1) * (lmax + 1);
     const int64_t pst = (int64_t)g->nring * (lmax + 1);
-    const LegChoice lc = leg_choice(p.npairs, lmax, nmaps);
+    const LegChoice lc = leg_choice(g, lmax, nmaps);
     const int ntiles = leg_adjoint_tiles(lc, g, false);
     const size_t phase_bytes = align256((size_t)nmaps * pst * sizeof(double2));
     // Partial vectors beside the result, per map: one per tile group after the
@@ -475,7 +475,7 @@ int crs_legendre_choice(crs_grid g, int lmax, int nmaps, int* out) {
   return guarded([&] {
     CRS_CHECK(g != nullptr && out != nullptr, CRS_EINVAL, "grid or out is NULL");
     CRS_CHECK(lmax >= 0 && nmaps >= 1, CRS_EINVAL, "lmax < 0 or nmaps < 1");
-    const LegChoice c = leg_choice((g->nring + 1) / 2, lmax, nmaps);
+    const LegChoice c = leg_choice(g, lmax, nmaps);
     out[0] = 1;
     out[1] = c.syn_t;
     out[2] = 1;

@@ -649,8 +649,7 @@ int64_t exec_plan_bytes(const std::vector<crs_model>& models, int nrhs) {
     const crs_grid g = kv.first.first;
     const int L = kv.first.second, nm = kv.second;
     const int64_t nalm = (int64_t)(L + 1) * (L + 1);
-    const int npairs = (g->nring + 1) / 2;
-    const LegChoice c = leg_choice(npairs, L, nm);
+    const LegChoice c = leg_choice(g, L, nm);
     bytes += (int64_t)nm * nalm * 8;                          // uhat
     bytes += (int64_t)nm * g->nring * (L + 1) * 16;           // phase
     bytes += (int64_t)leg_adjoint_tiles(c, g, false) * nm * nalm * 8;  // adjoint partial sums
@@ -750,7 +749,7 @@ std::unique_ptr<Exec> make_exec(const std::vector<crs_model>& models, int nrhs, 
     g.mcount.alloc(1);
     g.phase.alloc((size_t)g.nmaps * g.pst);
     g.leg = autotune ? leg_autotune(leg_args(g.grid, *g.plan), g.nmaps, g.uhat.p, g.phase.p, s)
-                     : leg_choice(g.plan->npairs, g.lmax, g.nmaps);
+                     : leg_choice(g.grid, g.lmax, g.nmaps);
     g.ntiles = leg_adjoint_tiles(g.leg, g.grid, false);
     std::vector<const double*> wa, wp, ta;
     for (const SlotDev& sl : g.hslots) {

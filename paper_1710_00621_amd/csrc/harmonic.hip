@@ -127,13 +127,13 @@ void launch_map_op(int op, double* x, const double* b, const double* y, const do
 
 // ------------------------------------------------------ transform scratch
 void ShtScratch::reserve(crs_grid g, int L, int nm, hipStream_t s) {
-  ShtPlan& p = get_plan(g, L, s);
+  get_plan(g, L, s);
   LegChoice c;
   auto it = choice.find(std::make_pair(g, L));
   if (it != choice.end() && it->second.first >= nm) {
     c = it->second.second;
   } else {
-    c = leg_choice(p.npairs, L, nm);
+    c = leg_choice(g, L, nm);
     choice[std::make_pair(g, L)] = std::make_pair(nm, c);
   }
   hat.alloc((size_t)nalm_of(L) * nm);

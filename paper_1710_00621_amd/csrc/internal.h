@@ -236,7 +236,7 @@ struct LegArgs {
   const int* mlist = nullptr;
   const int* mcount = nullptr;
 };
-// Tiles of 64 ring pairs per wave of the Legendre kernels for a (ring pairs,
+// Tiles of 64 ring pairs per wave of the Legendre kernels for a (grid layout,
 // L, maps) shape.  leg_choice gives the autotuned choice for the shape if one
 // was recorded (leg_autotune), else the measured default rules; the
 // environment variables CRS_LEG_TS and CRS_LEG_TA override either (tuning and
@@ -245,7 +245,7 @@ struct LegArgs {
 struct LegChoice {
   int syn_t = 1, adj_t = 1;
 };
-LegChoice leg_choice(int npairs, int lmax, int nmaps);
+LegChoice leg_choice(crs_grid g, int lmax, int nmaps);
 // Times every valid variant of both transforms on the given buffers (their
 // contents are overwritten; vpart is allocated internally) and records the
 // fastest per transform for the shape.  Returns the recorded choice.

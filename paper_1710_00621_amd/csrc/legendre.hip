@@ -1055,13 +1055,15 @@ static void apply_env(LegChoice& c, int nmaps) {
 }
 
 static std::mutex g_tune_mu;
-static std::map<std::tuple<int, int, int>, LegChoice> g_tuned;  // (npairs, L, nmaps)
+// (ring pairs, polar tiles, slots, L, maps): the same pairs may be laid out in other tiles
+static std::map<std::tuple<int, int, int, int, int>, LegChoice> g_tuned;
 
-LegChoice leg_choice(int npairs, int L, int nmaps) {
+LegChoice leg_choice(crs_grid g, int L, int nmaps) {
+  const int npairs = (g->nring + 1) / 2;
   LegChoice c;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    auto it = g_tuned.find(std::make_tuple(npairs, L, nmaps));
+    auto it = g_tuned.find(std::make_tuple(npairs, g->pol_tiles, g->nslots, L, nmaps));
     c = it != g_tuned.end() ? it->second : default_choice(npairs, L, nmaps);
   }
   apply_env(c, nmaps);
@@ -1224,7 +1226,7 @@ LegChoice leg_autotune(const LegArgs& a0, int nmaps, double* uhat, double2* phas
   CRS_HIP(hipStreamSynchronize(s));
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tuned[std::make_tuple(a.npairs, L, nmaps)] = best;
+    g_tuned[std::make_tuple(a.npairs, a.pol_tiles, a.nslots, L, nmaps)] = best;
   }
   // the environment overrides apply to a tuned choice as to the default one
   apply_env(best, nmaps);

@@ -1,0 +1,18 @@
+"""What the autotuner records for a shape holds for grids of the same tiles
+only: grids with as many ring pairs in other tiles keep their own choice."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def test_tuned_choice_stays_with_its_layout():
+    import torch
+    from paper_1710_00621_amd import crsolve
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    # 192 ring pairs: five tiles (padded polar slots) and four
+    a, b = crsolve.Grid.healpix(96), crsolve.Grid.gauss_legendre(383, 128)
+    for lmax in range(60, 300, 12):
+        for nmaps in (1, 2, 3, 6):
+            before = crsolve.legendre_choice(b, lmax, nmaps)
+            crsolve.autotune_legendre(a, lmax, nmaps)
+            assert crsolve.legendre_choice(b, lmax, nmaps) == before, (lmax, nmaps)
