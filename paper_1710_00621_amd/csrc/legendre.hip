@@ -968,6 +968,11 @@ __global__ __launch_bounds__(256) void k_leg_adj_sq(LegArgs a, const double2* __
 }  // namespace
 
 // ------------------------------------------------------------ launchers
+// tile groups of T (tile_range)
+static int tile_groups(int pol_tiles, int nslots, int T) {
+  return (pol_tiles + T - 1) / T + (nslots / 64 - 1 - pol_tiles + T - 1) / T + 1;
+}
+
 // Kernel choice: tiles of 64 ring pairs per wave.  More tiles share the operand
 // loads of the synthesis and divide the adjoint's partial sums, fewer leave
 // more waves in flight.  Measured (ms, T = 1 / 2 / 4; adjoint with its tile sum):
@@ -996,7 +1001,9 @@ static int largest_t(long tiles, int L, int tmax, long groups, long want2, long 
 static int syn_tmax(int nmaps) { return nmaps == 1 ? 4 : nmaps <= 4 ? 2 : 1; }
 constexpr int kAdjTmax = 4;
 
-// waves of a launch with one tile and one group of maps per wave
+// waves of a launch with one tile and one group of maps per wave, as the rules and
+// the figures below count them: tiles of 64 ring pairs, without the padding of
+// the polar slots and without the equator's tile
 static long leg_waves(int npairs, int L) { return (long)(L + 1) * ((npairs + 63) / 64); }
 
 // Maps of the adjoint: n16 groups of four on the 16-column kernel, then groups of
@@ -1033,13 +1040,23 @@ static AdjGroups adj_groups(int npairs, int L, int nmaps) {
   return {nmaps / 4 - (3 - nmaps % 4), 3};  // nmaps = 4 n16 + 3 (4 - nmaps % 4)
 }
 
-static LegChoice default_choice(int npairs, int L, int nmaps) {
+static LegChoice default_choice(int npairs, int pol_tiles, int nslots, int L, int nmaps) {
   LegChoice c;
   const long tiles = (npairs + 63) / 64;
   c.syn_t = largest_t(tiles, L, syn_tmax(nmaps), 1, nmaps >= 3 ? 16384 : 8192, 8192);
   const AdjGroups g = adj_groups(npairs, L, nmaps);
   const int rest = nmaps - 4 * g.n16;
   c.adj_t = largest_t(tiles, L, kAdjTmax, g.n16 + (g.nm ? (rest + g.nm - 1) / g.nm : 0), 4096, 6144);
+  // A wave of four tiles with only one or two to run takes nearly as long as a
+  // full one, and the equator's group stays one of few: four tiles only where they
+  // halve the groups of two and leave three.  Adjoint, us, T = 2 / 4: Nside 256 / L
+  // 512 x42 (4 + 4 tiles) 787 / 805, Nside 300 / L 600 x20 (4 + 5) 642 / 754, Nside
+  // 320 / L 640 x30 (4 + 6) 1041 / 1264, Nside 384 / L 768 x20 (6 + 6) 1080 / 1083,
+  // Nside 448 / L 900 x15 (7 + 7) 1220 / 1127, Nside 512 / L 1024 x6 (8 + 8) 661 / 619.
+  if (c.adj_t == 4) {
+    const int g4 = tile_groups(pol_tiles, nslots, 4) - 1, g2 = tile_groups(pol_tiles, nslots, 2) - 1;  // (the equator's apart)
+    if (2 * g4 > g2 || g4 < 3) c.adj_t = 2;
+  }
   return c;
 }
 
@@ -1064,7 +1081,7 @@ LegChoice leg_choice(crs_grid g, int L, int nmaps) {
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(std::make_tuple(npairs, g->pol_tiles, g->nslots, L, nmaps));
-    c = it != g_tuned.end() ? it->second : default_choice(npairs, L, nmaps);
+    c = it != g_tuned.end() ? it->second : default_choice(npairs, g->pol_tiles, g->nslots, L, nmaps);
   }
   apply_env(c, nmaps);
   return c;
@@ -1073,11 +1090,6 @@ LegChoice leg_choice(crs_grid g, int L, int nmaps) {
 // blocks of a launch over ntg tile groups: four consecutive m each, m-blocks
 // rounded up to the XCD order of block_coords
 static unsigned leg_blocks(int L, int ntg) { return (unsigned)(((L + 1 + 3) / 4 + 7) / 8 * 8 * ntg); }
-
-// tile groups of T (tile_range)
-static int tile_groups(int pol_tiles, int nslots, int T) {
-  return (pol_tiles + T - 1) / T + (nslots / 64 - 1 - pol_tiles + T - 1) / T + 1;
-}
 
 void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const double* u, int64_t ustride,
                       double2* phase, int64_t pstride, hipStream_t s) {
@@ -1187,7 +1199,7 @@ LegChoice leg_autotune(const LegArgs& a0, int nmaps, double* uhat, double2* phas
   const int L = a.lmax;
   const int64_t nalm = (int64_t)(L + 1) * (L + 1);
   const int64_t pst = (int64_t)a.nring * (L + 1);
-  LegChoice best = default_choice(a.npairs, L, nmaps);
+  LegChoice best = default_choice(a.npairs, a.pol_tiles, a.nslots, L, nmaps);
   const int tiles = a.nslots / 64;
   // the largest partial-sum count of any candidate (one tile per wave; the first goes to uhat)
   DevBuf<double> vpart;
