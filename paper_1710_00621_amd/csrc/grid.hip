@@ -173,7 +173,7 @@ void gl_nodes(int n, std::vector<double>& z, std::vector<double>& st, std::vecto
 // theta) away from its own end.  The forms meet at 45 degrees; the boundary
 // moves to the nearest whole group of four tiles, else to the nearest whole
 // tile, if that stays within 35 and 55 degrees, else it stays at 45 degrees and
-// the polar slots are padded (HEALPix Nside 2 to 32 and 89 to 96).
+// the polar slots are padded (HEALPix Nside 2 to 56 and 89 to 112).
 //
 // The 32 pairs next to the equator sit in the last tile, each in slots i and 32 +
 // i: the even functions are taken from the second (see legendre.hip).  Beyond
@@ -231,8 +231,8 @@ void grid_finalize(crs_grid g, hipStream_t s) {
               "ring length above 8192 pixels is not supported");
   // Per ring: the complex FFT that the ring kernels run.  Even Nphi uses a
   // half-length complex transform (two real samples per complex word); a
-  // length whose largest prime factor exceeds 7 goes through Bluestein's
-  // chirp convolution with a power-of-two FFT.
+  // length whose largest prime factor exceeds prime_max goes through
+  // Bluestein's chirp convolution with a power-of-two FFT.
   std::vector<RingInfo> info(nr);
   std::map<int, int64_t> tw_of, bf_of;
   std::vector<double2> tw, bf;

@@ -754,8 +754,8 @@ __global__ __launch_bounds__(256) void k_leg_adj4(LegArgs a, int nmaps, int map0
 // Groups of four maps: v_mfma_f64_16x16x4, column j = t % 16 = 4 map + 2 (E, O)
 // + (cos, sin); H takes 32 registers per tile.  K-block 4 s + b holds the ring
 // pairs that block b of k_leg_adj4 takes from H register s, and the four
-// accumulators b are added as its blocks are: a map's result does not depend
-// on how many maps run beside it.
+// accumulators b are added as its blocks are: at one number of tiles per wave a
+// map's sums do not depend on how many maps run beside it.
 template <int T, int F>
 __device__ __forceinline__ void adj16_wave(const LegArgs& a, int m, int tg, int t0, int tend, int map0, int ns,
                                            const double2* __restrict__ phase, int64_t pstride, const AdjDst& dst,
@@ -977,14 +977,13 @@ static int tile_groups(int pol_tiles, int nslots, int T) {
 // loads of the synthesis and divide the adjoint's partial sums, fewer leave
 // more waves in flight.  Measured (ms, T = 1 / 2 / 4; adjoint with its tile sum):
 //                          synthesis               adjoint
-//   Nside 256 / L 512 x1   0.030 / 0.043 / 0.058   0.047 / 0.051 / 0.065   ( 4104 waves at T = 1)
-//   Nside 512 / L 1024 x1  0.134 / 0.101 / 0.112   0.187 / 0.162 / 0.160   (16400)
-//   Nside 1024 / L 2000 x1 0.84  / 0.56  / 0.52    1.09  / 0.82  / 0.76    (64032)
-//   Nside 1024 / L 2000 x4 1.27  / 1.15            3.63  / 2.64  / 2.29
-//   Nside 256 / L 512 x42  0.346 / 0.366           1.04  / 0.89  / 0.86
-//   Nside 512 / L 1024 x4  0.216 / 0.221           0.312 / 0.305 / 0.274
-//   Nside 256 / L 512 x6                           0.143 / 0.128 / 0.157
-//   Nside 256 / L 512 x15                          0.337 / 0.281 / 0.296
+//   Nside 256 / L 512 x1   0.031 / 0.036 / 0.053   0.034 / 0.034 / 0.046   ( 4104 waves at T = 1)
+//   Nside 512 / L 1024 x1  0.131 / 0.096 / 0.107   0.141 / 0.112 / 0.110   (16400)
+//   Nside 1024 / L 2000 x1 0.73  / 0.54  / 0.53    0.97  / 0.68  / 0.63    (64032)
+//   Nside 1024 / L 2000 x4 1.15  / 1.18            3.14  / 2.13  / 1.80
+//   Nside 512 / L 1024 x4  0.236 / 0.230           0.482 / 0.349 / 0.313
+//   Nside 256 / L 512 x6                           0.104 / 0.090 / 0.099
+//   Nside 256 / L 512 x15                          0.267 / 0.213 / 0.230
 // so the rules take the largest T that leaves 8192 waves (synthesis; 16384 from
 // three maps on, whose waves run longer) or 4096 (adjoint; 6144 for T = 4).
 // The autotuner replaces them per shape.
@@ -1013,19 +1012,23 @@ static long leg_waves(int npairs, int L) { return (long)(L + 1) * ((npairs + 63)
 // and there the maps spread over more, shorter ones.  Measured (us, the
 // Legendre kernel alone up to Nside 128, else the whole transform; groups of
 // 1 / 2 / 3 maps / of four, a remainder padded or on its own kernel):
-//   Nside 16 / L 32 x6        8.0 /   9.4 /  10.7 /  11.0   (   33 waves per group)
-//   Nside 64 / L 128 x12     13.7 /  15.4 /  18.3 /  21.1   (  258)
-//   Nside 64 / L 128 x16     18.5 /  16.8 /  18.8 /  22.6
-//   Nside 128 / L 256 x8     32.3 /  29.6 /  31.6 /  34.7   ( 1028)
-//   Nside 128 / L 256 x20              91 /    95 /    96
-//   Nside 256 / L 512 x5              129 /   123 /   142   ( 4104)
-//   Nside 256 / L 512 x10             200 /   206 /   214
-//   Nside 256 / L 512 x16             217 /   212 /   199   (kernel alone)
-//   Nside 256 / L 512 x42             736 /   738 /   743
-//   Nside 512 / L 1024 x6             636 /   591 /   634   (16400)
-//   Nside 512 / L 1024 x10           1016 /  1041 /   997
-//   Nside 1024 / L 2000 x6           3593 /  3081 /  3232   (64032)
-//   Nside 1024 / L 2000 x7           4495 /  4198 /  3880
+//   Nside 16 / L 32 x6        8.5 /  10.0 /  11.4 /  11.9   (   33 waves per group)
+//   Nside 64 / L 128 x12     20.6 /  18.1 /  20.3 /  22.8   (  258)
+//   Nside 64 / L 128 x16     22.6 /  19.0 /  21.9 /  23.6
+//   Nside 90 / L 180 x16     61.2 /  56.4 /  54.9 /  54.5   (  543, whole)
+//   Nside 128 / L 256 x8     39.8 /  33.2 /  32.3 /  35.8   ( 1028)
+//   Nside 128 / L 256 x20     112 /   104 /   104 /   106
+//   Nside 150 / L 300 x10     111 /    98 /   103 /    97   ( 1505)
+//   Nside 192 / L 384 x4       81 /    69 /    75 /    78   ( 2310)
+//   Nside 192 / L 384 x7      116 /   110 /   113 /   104
+//   Nside 256 / L 512 x5      140 /   134 /   125 /   141   ( 4104)
+//   Nside 256 / L 512 x10     247 /   215 /   223 /   228
+//   Nside 256 / L 512 x16     254 /   200 /   211 /   194   (kernel alone)
+//   Nside 256 / L 512 x42     936 /   793 /   788 /   815
+//   Nside 512 / L 1024 x6     775 /   674 /   619 /   660   (16400)
+//   Nside 512 / L 1024 x10   1199 /  1063 /  1084 /  1005
+//   Nside 1024 / L 2000 x6   4146 /  3571 /  3175 /  3316   (64032)
+//   Nside 1024 / L 2000 x7   4811 /  4544 /  4336 /  3684
 struct AdjGroups {
   int n16, nm;  // groups of four, then groups of nm maps (0: none)
 };
@@ -1102,17 +1105,20 @@ void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const dou
   // Large launches carry up to eight maps per wave: the recurrence is shared.
   // Few waves are a matter of latency: one map per wave while all of them are in
   // flight together, then four.  Measured (us, 1 / 4 / up to 8 maps per wave):
-  //   Nside 16 / L 32 x6         7.0 /   9.2 /  11.4   (   33 waves per group)
-  //   Nside 64 / L 128 x12      14.0 /  15.3 /  18.4   (  258)
-  //   Nside 64 / L 128 x24      22.3 /  17.9 /  20.2
-  //   Nside 128 / L 256 x3      18.9 /  20.1 /  19.9   ( 1028)
-  //   Nside 128 / L 256 x8      33.7 /  24.1 /  27.9
-  //   Nside 256 / L 512 x5      98.6 /  76.9 /  54.4   ( 4104)
-  //   Nside 256 / L 512 x12      217 /  99.7 /   102
-  //   Nside 512 / L 1024 x9     1006 /   548 /   576   (16400)
-  //   Nside 512 / L 1024 x16    1782 /   737 /   697
-  // Three maps on one tile run as four, one of them empty (Nside 256: 40 us
-  // instead of 52; Nside 512: 176 and 185).
+  //   Nside 16 / L 32 x6         7.3 /   9.2 /  11.7   (   33 waves per group)
+  //   Nside 64 / L 128 x12      17.7 /  17.5 /  19.1   (  258)
+  //   Nside 64 / L 128 x24      25.8 /  19.9 /  23.6
+  //   Nside 90 / L 180 x16      34.8 /  21.8 /  27.3   (  543)
+  //   Nside 128 / L 256 x3      20.3 /  20.1           ( 1028)
+  //   Nside 128 / L 256 x8      36.0 /  24.4 /  29.4
+  //   Nside 150 / L 300 x8      48.6 /  32.2 /  34.1   ( 1505)
+  //   Nside 192 / L 384 x6      63.0 /  41.4 /  39.9   ( 2310)
+  //   Nside 256 / L 512 x5       104 /  79.1 /  57.9   ( 4104)
+  //   Nside 256 / L 512 x12      221 /   109 /   110
+  //   Nside 512 / L 1024 x9     1007 /   573 /   607   (16400)
+  //   Nside 512 / L 1024 x16    1798 /   776 /   739
+  // Three maps on one tile run as four, one of them empty (without the equator's
+  // tile: Nside 256 40 us instead of 52 for three columns, Nside 512 176 and 185).
   const long w = leg_waves(a.npairs, a.lmax);
   if (nmaps > 1 && c.syn_t == 1 && w * nmaps <= 4096) {
     CRS_SYN(0, 1, 1);

@@ -179,7 +179,7 @@ void map_op(int op, MaskRun& r, double* x, const double* b, const double* y, con
 
 // out = J v = W_h Y_h^T (mask_h) Y_h v at band-limit L, v given as hat
 // vectors in the scratch; map: a level map buffer for the synthesis
-void apply_j(const MaskLevel& lv, int L, const ShtPlan& p, MaskRun& r, double* map, double* out, MapSkip skip,
+void apply_j(const MaskLevel& lv, int L, MaskRun& r, double* map, double* out, MapSkip skip,
              hipStream_t s) {
   const int nm = r.nm;
   synth_ws(lv.grid, L, nm, r.sc.hat.p, map, r, skip, s);
@@ -206,8 +206,6 @@ void vcycle(const MaskMG& mg, MaskRun& r, int h, MapSkip skip, hipStream_t s) {
   }
   const MaskLevel& cv = mg.levels[h + 1];
   const int Lh = lv.lmax, LH = cv.lmax;
-  const ShtPlan& ph = get_plan(lv.grid, Lh, s);
-  const ShtPlan& pH = get_plan(lv.grid, LH, s);
   // x = M_h b
   map_op(MOP_SCALE, r, r.x[h].p, r.b[h].p, nullptr, nullptr, r.sm[h].p, 0.0, np, skip, s);
   // u = Y_h^T x                                               (L_h, N_h)
@@ -219,7 +217,7 @@ void vcycle(const MaskMG& mg, MaskRun& r, int h, MapSkip skip, hipStream_t s) {
   if (mg.exact_j) {
     launch_hat_from(r.sc.hat.p, Lh, (const double*)r.u[h].p, Lh, (const int64_t*)nullptr, nalm_of(Lh),
                     (const double*)nullptr, 0, (int64_t)0, lv.D.p, Lh + 1, r.mc.p, nm, skip, s);
-    apply_j(lv, Lh, ph, r, r.y[h].p, r.jv[h].p, skip, s);
+    apply_j(lv, Lh, r, r.y[h].p, r.jv[h].p, skip, s);
   }
   // r~ = W_h Y_h^T b - D_h u (J D_h u with exact J), at L_H  (L_H, N_h)
   nt = adjoint_ws(lv.grid, LH, nm, r.b[h].p, r, skip, s);
@@ -256,7 +254,7 @@ void vcycle(const MaskMG& mg, MaskRun& r, int h, MapSkip skip, hipStream_t s) {
   if (mg.exact_j) {
     launch_hat_from(r.sc.hat.p, Lh, (const double*)r.ct[h].p, LH, (const int64_t*)nullptr, nalm_of(LH),
                     (const double*)nullptr, 0, (int64_t)0, (const double*)nullptr, 0, r.mc.p, nm, skip, s);
-    apply_j(lv, Lh, ph, r, r.y[h].p, r.jv[h].p, skip, s);
+    apply_j(lv, Lh, r, r.y[h].p, r.jv[h].p, skip, s);
     launch_hat_from(r.sc.hat.p, Lh, (const double*)r.u[h].p, Lh, (const int64_t*)nullptr, nalm_of(Lh),
                     (const double*)r.jv[h].p, Lh, nalm_of(Lh), lv.D.p, Lh + 1, r.mc.p, nm, skip, s);
   } else {
@@ -525,7 +523,6 @@ void exec_mask(Exec& e, const double* r, double* z, bool accumulate, hipStream_t
     }
     const MaskLevel& l0 = mg.levels[0];
     const int L0 = mg.L0;
-    const ShtPlan& p0 = get_plan(l0.grid, L0, s);
     // b_0 = (mask) Y R r_k
     launch_hat_from(run.sc.hat.p, L0, r, L0,
                        run.off_top.p, (int64_t)0, (const double*)nullptr, 0, (int64_t)0, mg.rtop.p, 0, run.mc.p, run.nm, skip, s);

@@ -16,7 +16,6 @@ double ring_bytes(crs_grid g, int lmax, int nmaps, int mode);
 __host__ __device__ inline int64_t moff_h(int L, int m) {
   return (m == 0) ? 0 : (int64_t)(L + 1) + 2 * ((int64_t)(m - 1) * (L + 1) - (int64_t)(m - 1) * m / 2);
 }
-__host__ __device__ inline int64_t tri_h(int L, int m) { return (int64_t)m * (L + 1) - (int64_t)m * (m - 1) / 2; }
 
 // (m, part, l - m) of packed index i (0 <= i < (L+1)^2) in the packed m-major
 // layout: [m = 0: l = 0..L], then for m >= 1 [cos: l = m..L][sin: l = m..L].
