@@ -5,6 +5,7 @@
 // sky maps and recommends Gauss-Legendre grids where exact quadrature is
 // wanted (Sect. 2.1, Sect. 2.2 below eq:Q).
 #include <algorithm>
+#include <array>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -170,31 +171,35 @@ void gl_nodes(int n, std::vector<double>& z, std::vector<double>& st, std::vecto
 
 // Ring pairs in slots, tiles of 64, for the Legendre kernels: every tile runs
 // one form of the recurrence (legendre.hip), whose errors grow as 1 / sin(2
-// theta) away from its own end.  The forms meet at 45 degrees; the boundary
-// moves to the nearest whole group of four tiles, else to the nearest whole
-// tile, if that stays within 35 and 55 degrees, else it stays at 45 degrees and
-// the polar slots are padded (HEALPix Nside 2 to 56 and 89 to 112).
-//
-// The 32 pairs next to the equator sit in the last tile, each in slots i and 32 +
-// i: the even functions are taken from the second (see legendre.hip).  Beyond
-// them (|z| 0.08 at Nside 256, 0.02 at Nside 1024) the even functions'
-// cancellation 1 / |z| is below the sqrt(L) by which rounding adds up in any form.
+// theta) away from its own end.  The 32 pairs next to the equator sit in the
+// last tile, each in slots i and 32 + i: the even functions are taken from the
+// second.  Beyond them (|z| 0.08 at Nside 256, 0.02 at Nside 1024) the even
+// functions' cancellation 1 / |z| is below the sqrt(L) by which rounding adds up
+// in any form.  The polar pairs and the belt's are padded to whole tiles; their
+// boundary lies between 35 and 55 degrees where the tiles are fewest, then the
+// groups of four and of two that the kernels take, without padding of the polar
+// slots if it can (Nside 256 / L 512 x42, adjoint: 787 us, with both parts padded
+// 800), and next to 45 degrees.
 static void slot_layout(crs_grid g) {
   const int np = (g->nring + 1) / 2;
+  const double lo = 0.329, hi = 0.671;  // cos^2 of 55 and 35 degrees
   int p45 = 0;
   while (p45 < np && g->z[p45] * g->z[p45] >= 0.5) ++p45;
-  const double lo = 0.329, hi = 0.671;  // cos^2 of 55 and 35 degrees
-  g->pol_pairs = p45;
-  for (const int unit : {256, 64}) {
-    const int c = (p45 + unit / 2) / unit * unit;
-    if (c <= np && (c == 0 || g->z[c - 1] * g->z[c - 1] >= lo) && (c == np || g->z[c] * g->z[c] <= hi)) {
+  auto up = [](int n, int unit) { return (n + unit - 1) / unit; };
+  std::array<int, 5> best = {INT_MAX, 0, 0, 0, 0};
+  for (int c = 0; c <= np; ++c) {
+    const bool in = (c == 0 || g->z[c - 1] * g->z[c - 1] >= lo) && (c == np || g->z[c] * g->z[c] <= hi);
+    if (!in && c != p45) continue;
+    const int belt = np - c - std::min(32, np - c), a = up(c, 64), b = up(belt, 64);
+    const std::array<int, 5> key = {a + b, up(a, 4) + up(b, 4), up(a, 2) + up(b, 2), c % 64 != 0, std::abs(c - p45)};
+    if (key < best) {
+      best = key;
       g->pol_pairs = c;
-      break;
+      g->pol_tiles = a;
+      g->eq_pairs = std::min(32, np - c);
+      g->nslots = 64 * (a + b + 1);
     }
   }
-  g->pol_tiles = (g->pol_pairs + 63) / 64;
-  g->eq_pairs = std::min(32, np - g->pol_pairs);
-  g->nslots = 64 * (g->pol_tiles + (np - g->pol_pairs - g->eq_pairs + 63) / 64 + 1);
 }
 
 // Two doubles whose product is sin^2 theta = (1 - z)(1 + z) to about 2^-60: the

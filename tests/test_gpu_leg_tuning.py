@@ -9,8 +9,8 @@ def test_tuned_choice_stays_with_its_layout():
     import torch
     from paper_1710_00621_amd import crsolve
     assert torch.cuda.is_available(), "GPU tests need a GPU"
-    # 192 ring pairs: five tiles (padded polar slots) and four
-    a, b = crsolve.Grid.healpix(96), crsolve.Grid.gauss_legendre(383, 128)
+    # 224 ring pairs in five tiles and in four
+    a, b = crsolve.Grid.healpix(112), crsolve.Grid.gauss_legendre(447, 128)
     for lmax in range(60, 300, 12):
         for nmaps in (1, 2, 3, 6):
             before = crsolve.legendre_choice(b, lmax, nmaps)

@@ -10,8 +10,9 @@ from tests.test_zz_no_alloc import _call
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    (("healpix", 90), 180, 33),    # padded polar slots: four and five tiles for three of ring pairs
-    (("healpix", 31), 600, 16),    # 62 pairs, three tile groups taking turns
+    (("healpix", 90), 180, 33),    # 180 pairs in four tile groups, three of them taking turns in two vectors
+    (("healpix", 64), 230, 24),    # 128 pairs in three tile groups, two taking turns in one
+    (("healpix", 31), 600, 16),    # padded polar slots, a partial vector where 64-pair tiles have one
     (("gl", 4, 9), 2500, 1),       # two ring pairs in two forms of the recurrence
     (("gl", 70, 141), 1000, 7),
     (("healpix", 256), 512, 2),    # as many partial vectors as fit
