@@ -176,10 +176,11 @@ void gl_nodes(int n, std::vector<double>& z, std::vector<double>& st, std::vecto
 // second.  Beyond them (|z| 0.08 at Nside 256, 0.02 at Nside 1024) the even
 // functions' cancellation 1 / |z| is below the sqrt(L) by which rounding adds up
 // in any form.  The polar pairs and the belt's are padded to whole tiles; their
-// boundary lies between 35 and 55 degrees where the tiles are fewest, then the
-// groups of four and of two that the kernels take, without padding of the polar
-// slots if it can (Nside 256 / L 512 x42, adjoint: 787 us, with both parts padded
-// 800), and next to 45 degrees.
+// boundary lies between 35 and 55 degrees where the tiles are fewest (adjoint, us,
+// against the nearest multiple of 64: Nside 32 / L 64 x65 44 and 48, Nside 37 / L 90
+// x20 27 and 32, Nside 96 / L 192 x20 72 and 76), then the groups of four and of two
+// that the kernels take, without padding of the polar slots if it can (Nside 256 /
+// L 512 x42: 787, with both parts padded 800), and next to 45 degrees.
 static void slot_layout(crs_grid g) {
   const int np = (g->nring + 1) / 2;
   const double lo = 0.329, hi = 0.671;  // cos^2 of 55 and 35 degrees
