@@ -420,10 +420,9 @@ int sht_adjoint_noalloc(crs_grid g, int lmax, int nmaps, const double* map, int6
     const LegChoice lc = leg_choice(g, lmax, nmaps);
     const int ntiles = leg_adjoint_tiles(lc, g, false);
     const size_t phase_bytes = align256((size_t)nmaps * pst * sizeof(double2));
-    // Partial vectors beside the result, per map: one per tile group after the
-    // first, but no more than one per 128 ring pairs.  Where the groups are more
-    // (small grids, whose tiles are padded) they take turns.
-    const int parts = std::min(ntiles - 1, std::max(1, ((p.npairs + 63) / 64 + 1) / 2));
+    // Partial vectors beside the result, per map.  Where the tile groups after the
+    // first are more, they take turns.
+    const int parts = leg_adjoint_parts(lc, g, lmax, nmaps);
     const size_t part_bytes = align256((size_t)parts * nmaps * nalm * sizeof(double));
     CRS_CHECK(phase_bytes + part_bytes <= kNoAllocScratchBytes, CRS_EINVAL,
               "sht_adjoint_noalloc needs " + std::to_string(phase_bytes + part_bytes) +

@@ -272,6 +272,12 @@ inline AdjDst adj_dst(double* v, int64_t nalm, int nmaps, int ng) {
   return {v, nalm, v + t, nalm, t, 0, ng};
 }
 int leg_adjoint_tiles(const LegChoice& c, crs_grid g, bool square);
+// Partial vectors per map that an adjoint with little scratch keeps beside its
+// result: one per 128 ring pairs, or one per tile group after the first where that
+// is fewer, at the tiles per wave that the waves alone would give (the groups
+// may be more: small grids, whose tiles are padded, and shapes that run fewer tiles
+// per wave than their waves allow).
+int leg_adjoint_parts(const LegChoice& c, crs_grid g, int L, int nmaps);
 void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const double2* phase, int64_t pstride,
                         const AdjDst& dst, bool square, hipStream_t s);
 

@@ -1043,13 +1043,18 @@ static AdjGroups adj_groups(int npairs, int L, int nmaps) {
   return {nmaps / 4 - (3 - nmaps % 4), 3};  // nmaps = 4 n16 + 3 (4 - nmaps % 4)
 }
 
+// tiles per wave of the adjoint by the waves alone
+static int adj_waves_t(int npairs, int L, int nmaps) {
+  const AdjGroups g = adj_groups(npairs, L, nmaps);
+  const int rest = nmaps - 4 * g.n16;
+  return largest_t((npairs + 63) / 64, L, kAdjTmax, g.n16 + (g.nm ? (rest + g.nm - 1) / g.nm : 0), 4096, 6144);
+}
+
 static LegChoice default_choice(int npairs, int pol_tiles, int nslots, int L, int nmaps) {
   LegChoice c;
   const long tiles = (npairs + 63) / 64;
   c.syn_t = largest_t(tiles, L, syn_tmax(nmaps), 1, nmaps >= 3 ? 16384 : 8192, 8192);
-  const AdjGroups g = adj_groups(npairs, L, nmaps);
-  const int rest = nmaps - 4 * g.n16;
-  c.adj_t = largest_t(tiles, L, kAdjTmax, g.n16 + (g.nm ? (rest + g.nm - 1) / g.nm : 0), 4096, 6144);
+  c.adj_t = adj_waves_t(npairs, L, nmaps);
   // A wave of four tiles with only one or two to run takes nearly as long as a
   // full one, and the equator's group stays one of few: four tiles only where they
   // halve the groups of two and leave three.  Adjoint, us, T = 2 / 4: Nside 256 / L
@@ -1141,6 +1146,12 @@ void launch_leg_synth(const LegChoice& c, const LegArgs& a, int nmaps, const dou
 
 int leg_adjoint_tiles(const LegChoice& c, crs_grid g, bool square) {
   return tile_groups(g->pol_tiles, g->nslots, square ? 1 : c.adj_t);
+}
+
+int leg_adjoint_parts(const LegChoice& c, crs_grid g, int L, int nmaps) {
+  const int npairs = (g->nring + 1) / 2;
+  const int t = std::max(c.adj_t, adj_waves_t(npairs, L, nmaps));
+  return std::min(tile_groups(g->pol_tiles, g->nslots, t) - 1, std::max(1, ((npairs + 63) / 64 + 1) / 2));
 }
 
 void launch_leg_adjoint(const LegChoice& c, const LegArgs& a, int nmaps, const double2* phase, int64_t pstride,

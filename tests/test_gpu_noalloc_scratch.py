@@ -15,6 +15,7 @@ CASES = [
     (("healpix", 31), 600, 16),    # padded polar slots, a partial vector where 64-pair tiles have one
     (("gl", 4, 9), 2500, 1),       # two ring pairs in two forms of the recurrence
     (("gl", 70, 141), 1000, 7),
+    (("healpix", 151), 56, 107),   # two tiles per wave where the waves allow four: four tile groups after the first
     (("healpix", 256), 512, 2),    # as many partial vectors as fit
 ]
 
